@@ -563,6 +563,7 @@ GemmSwitches read_gemm_switches() {
     s.no_pair = on("FFTCONV_GEMM_NO_PAIR");
     s.no_bingroup = on("FFTCONV_GEMM_NO_BINGROUP");
     s.no_fast = on("FFTCONV_GEMM_NO_FAST");
+    s.no_thin = on("FFTCONV_GEMM_NO_THIN");
     if (const char *e = getenv("FFTCONV_BG_TILE")) s.bg_tile = atoi(e);
     return s;
 }
@@ -591,6 +592,7 @@ struct Prepared {
     bool akf, bkf;     // the reduction index is the contiguous plane index of A / B
     bool vec;          // 16-byte gathers are possible
     bool bingroup;     // the four-bins-per-line kernel applies
+    bool thin;         // a side of at most four: the vector-unit kernels apply (cgemm_thin.hip)
 };
 
 static hipError_t prepare(const GemmOperand &A, const GemmOperand &B, float *C, FreqLayout layC, long C_rs,
@@ -623,6 +625,7 @@ static hipError_t prepare(const GemmOperand &A, const GemmOperand &B, float *C, 
     out->bingroup = out->vec && !sw.no_bingroup && A.lay.tsh == 2 && B.lay.tsh == 2 && layC.tsh == 2 &&
                     bins % (4 * kXcds) == 0 && (akf || A.rs == 1) && (bkf || B.cs == 1) && C_cs == 1 &&
                     C_rs % 4 == 0 && N % 4 == 0 && ((size_t)C & 15) == 0;
+    out->thin = !sw.no_thin && thin_supported(prm);
     return hipSuccess;
 }
 
@@ -652,6 +655,7 @@ static hipError_t run_tail(GemmParams prm, long full, long rem, LaunchCtx st) {
 static hipError_t launch_prepared(const Prepared &q, LaunchCtx st) {
     const GemmParams &prm = q.prm;
     const GemmSwitches &sw = switches_of(st.sw);
+    if (q.thin) return launch_cgemm_thin(prm, st);
     if (q.bingroup) return launch_cgemm_bingroup(prm, q.akf, q.bkf, st);
     const int shape = pick_tile(sw);
     if (q.vec && shape == 3 && sw.tile < 0 && !sw.no_tail) {
@@ -726,7 +730,7 @@ bool cgemm_pair_supported(const GemmProblem &g1, const GemmProblem &g2, const Ge
     Prepared q1, q2;
     if (prepare(g1.A, g1.B, g1.C, g1.layC, g1.C_rs, g1.C_cs, g1.M, g1.N, g1.K, g1.bins, sw, &q1) != hipSuccess) return false;
     if (prepare(g2.A, g2.B, g2.C, g2.layC, g2.C_rs, g2.C_cs, g2.M, g2.N, g2.K, g2.bins, sw, &q2) != hipSuccess) return false;
-    return q1.vec && q2.vec && !q1.bingroup && !q2.bingroup;
+    return q1.vec && q2.vec && !q1.bingroup && !q2.bingroup && !q1.thin && !q2.thin;
 }
 
 hipError_t launch_cgemm_pair(const GemmProblem &g1, const GemmProblem &g2, LaunchCtx st) {
@@ -734,7 +738,7 @@ hipError_t launch_cgemm_pair(const GemmProblem &g1, const GemmProblem &g2, Launc
     const GemmSwitches &sw = switches_of(st.sw);
     if (hipError_t e = prepare(g1.A, g1.B, g1.C, g1.layC, g1.C_rs, g1.C_cs, g1.M, g1.N, g1.K, g1.bins, sw, &q1); e != hipSuccess) return e;
     if (hipError_t e = prepare(g2.A, g2.B, g2.C, g2.layC, g2.C_rs, g2.C_cs, g2.M, g2.N, g2.K, g2.bins, sw, &q2); e != hipSuccess) return e;
-    if (!(q1.vec && q2.vec) || q1.bingroup || q2.bingroup) return hipErrorInvalidValue;
+    if (!(q1.vec && q2.vec) || q1.bingroup || q2.bingroup || q1.thin || q2.thin) return hipErrorInvalidValue;
     GemmPairParams pp;
     pp.p1 = q1.prm; pp.p2 = q2.prm; pp.n1 = 0;
     if (q1.akf && q1.bkf) return pair_second<true, true>(q2, pp, st);

@@ -22,6 +22,10 @@ __device__ __forceinline__ float flip(float v, unsigned sign) {
     return __builtin_bit_cast(float, __builtin_bit_cast(unsigned, v) ^ sign);
 }
 
+// Contractions with a side of at most four (cgemm_thin.hip).
+bool thin_supported(const GemmParams &prm);
+hipError_t launch_cgemm_thin(const GemmParams &prm, LaunchCtx st);
+
 constexpr int kXcds = 8;   // workgroup i is placed on XCD i % kXcds
 
 }  // namespace fc
