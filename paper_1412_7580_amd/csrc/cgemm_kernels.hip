@@ -564,6 +564,7 @@ GemmSwitches read_gemm_switches() {
     s.no_bingroup = on("FFTCONV_GEMM_NO_BINGROUP");
     s.no_fast = on("FFTCONV_GEMM_NO_FAST");
     s.no_thin = on("FFTCONV_GEMM_NO_THIN");
+    s.no_split = on("FFTCONV_GEMM_NO_SPLIT");
     if (const char *e = getenv("FFTCONV_BG_TILE")) s.bg_tile = atoi(e);
     return s;
 }
@@ -592,6 +593,7 @@ struct Prepared {
     bool akf, bkf;     // the reduction index is the contiguous plane index of A / B
     bool vec;          // 16-byte gathers are possible
     bool bingroup;     // the four-bins-per-line kernel applies
+    bool split;        // bound by the fp32 matrix cores: the bf16 kernel applies (cgemm_split.hip)
     bool thin;         // a side of at most four: the vector-unit kernels apply (cgemm_thin.hip)
 };
 
@@ -626,6 +628,7 @@ static hipError_t prepare(const GemmOperand &A, const GemmOperand &B, float *C, 
                     bins % (4 * kXcds) == 0 && (akf || A.rs == 1) && (bkf || B.cs == 1) && C_cs == 1 &&
                     C_rs % 4 == 0 && N % 4 == 0 && ((size_t)C & 15) == 0;
     out->thin = !sw.no_thin && thin_supported(prm);
+    out->split = prm.fast && !out->bingroup && (akf || !bkf) && !sw.no_split && sw.tile < 0 && split_pays(prm);
     return hipSuccess;
 }
 
@@ -657,6 +660,7 @@ static hipError_t launch_prepared(const Prepared &q, LaunchCtx st) {
     const GemmSwitches &sw = switches_of(st.sw);
     if (q.thin) return launch_cgemm_thin(prm, st);
     if (q.bingroup) return launch_cgemm_bingroup(prm, q.akf, q.bkf, st);
+    if (q.split) return launch_cgemm_split(prm, q.akf, q.bkf, st);
     const int shape = pick_tile(sw);
     if (q.vec && shape == 3 && sw.tile < 0 && !sw.no_tail) {
         // a short last round (at most a quarter of the resident workgroups): split its tiles
@@ -739,6 +743,8 @@ hipError_t launch_cgemm_pair(const GemmProblem &g1, const GemmProblem &g2, Launc
     if (hipError_t e = prepare(g1.A, g1.B, g1.C, g1.layC, g1.C_rs, g1.C_cs, g1.M, g1.N, g1.K, g1.bins, sw, &q1); e != hipSuccess) return e;
     if (hipError_t e = prepare(g2.A, g2.B, g2.C, g2.layC, g2.C_rs, g2.C_cs, g2.M, g2.N, g2.K, g2.bins, sw, &q2); e != hipSuccess) return e;
     if (!(q1.vec && q2.vec) || q1.bingroup || q2.bingroup || q1.thin || q2.thin) return hipErrorInvalidValue;
+    if (q1.split && q2.split && !q1.bkf && !q2.bkf && q1.akf != q2.akf)
+        return launch_cgemm_split_pair(q1.prm, q1.akf, q2.prm, q2.akf, st);
     GemmPairParams pp;
     pp.p1 = q1.prm; pp.p2 = q2.prm; pp.n1 = 0;
     if (q1.akf && q1.bkf) return pair_second<true, true>(q2, pp, st);

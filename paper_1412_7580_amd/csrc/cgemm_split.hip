@@ -1,0 +1,235 @@
+// Per-bin complex contraction on the bf16 matrix cores, for layers whose channels and samples are
+// many enough that the fp32 ones are the bound (see split_pays()).
+//
+// Same operation as cgemm_kernels.hip (the Cgemm row of Table 1 of the fbfft paper), same layout,
+// same order of workgroups.  Every fp32 operand value is cut, without loss, into three bf16 terms
+// (x = h + m + l: each is the rounded value of what the ones before it leave, and 8 + 8 + 8 bits
+// hold the whole significand), and a real product is the six bf16 products hh, hm, mh, mm, hl,
+// lh, which are exact and are summed in fp32 by v_mfma_f32_32x32x16_bf16.  What is left out (ml,
+// lm, ll) is at most 2^-23 of |a b| and of either sign, 2^-26 on average: below the rounding of the
+// fp32 sum itself.  The fp32 MFMA does 2 of K in 64 cycles, the six products do 16 of K in 192.
+//     Cr += Ar Br - Ai Bi,   Ci += Ar Bi + Ai Br      (four real products, no cancellation)
+// Relative 2-norm error of the passes against 64 bits, three-product fp32 form -> this: 128 samples,
+// 384 -> 384 channels, 13x13: 4.5e-7 / 4.9e-7 / 2.9e-7 -> 2.1e-7 / 2.3e-7 / 1.8e-7.
+//
+// Workgroup = 4 waves, a 64x64 tile, each wave one MFMA tile of 32x32 (re and im accumulators).  K is
+// walked in tiles of 16 through one LDS image of both operands, cut on the way from the staging
+// registers; the next tile's global loads are in flight while the current one is multiplied, and
+// the barriers around the image are covered by the compute unit's other workgroups (four, at 128
+// registers: a build that spilled to stay there was 10 % slower on the backward pair).  128x64
+// tiles and two tiles of staging measured no faster, K tiles of 32 slower.  That layer's training
+// step 485 -> 433 us; 128 x 256 -> 256 240 -> 219, 128 x 192 -> 192 163 -> 144, 8x8 images, 256 x 128 -> 128 88 -> 74.
+#include "gemm_params.hpp"
+#include "bf16_split.hpp"
+
+namespace fc {
+
+constexpr unsigned kOutside = 0x80000000u;       // byte offset past every buffer range
+
+constexpr int ROWS = 64, TK = 16, KQ = TK / 4;
+
+// Loader of one operand tile (ROWS x TK) with the "row" index being m (or n) and the
+// reduction index k.  KF: k is the contiguous plane index, and a unit of work is four
+// consecutive k of one row, as one 16-byte gather; else the row index is contiguous, lanes run
+// along the rows and a unit is four 4-byte gathers (as many cache lines a byte as wider loads
+// would touch, and the four k that one LDS word pair holds meet in one lane).
+// LDS image: [6 = (re, im) x (h, m, l)][k / 4][row] of four bf16; RP rows a plane, so that both
+// kinds of unit store, and the fragments load, without bank conflicts.
+template <bool KF>
+struct SplitLoader {
+    static constexpr int RP = ROWS + 8, PLANE = KQ * RP * 8, BYTES = 6 * PLANE;
+    float re[4], im[4];
+    unsigned off;        // byte offset of this lane's unit from the tile's base, which is uniform
+
+    static __device__ __forceinline__ int row_of(int tid) { return KF ? tid / KQ : tid % ROWS; }
+    static __device__ __forceinline__ int kq_of(int tid) { return KF ? tid % KQ : tid / ROWS; }
+
+    // The strided index moves in whole plane tiles (fast_addressing() in cgemm_kernels.hip), so an
+    // address is a uniform base that changes with the K tile and an offset that never does.
+    __device__ __forceinline__ void prepare(const FreqLayout &lay, long rs, long cs, int r0, int R, int tid) {
+        const int rr = row_of(tid), kk = 4 * kq_of(tid);
+        const size_t o = KF ? (size_t)rr * rs * lay.bins * 2 + lay.part(kk)
+                            : lay.part(rr) + (size_t)kk * cs * lay.bins * 2;
+        off = r0 + rr < R ? (unsigned)(o * sizeof(float)) : kOutside;
+    }
+
+    __device__ __forceinline__ void load(const float *base, const FreqLayout &lay, long rs, long cs, int bin, int r0,
+                                         int k0, int K, int tid) {
+        size_t o = (size_t)bin * (2u << lay.tsh);
+        if constexpr (KF) o += (size_t)r0 * rs * lay.bins * 2 + lay.part(k0);
+        else o += lay.part(r0) + (size_t)k0 * cs * lay.bins * 2;
+        const BufferView buf(base + o);
+        const unsigned im_bytes = 4u << lay.tsh;
+        const int kk = k0 + 4 * kq_of(tid);
+        if constexpr (KF) {                               // K is a multiple of 4
+            const unsigned v = kk < K ? off : kOutside;
+            buf.load4(re, v, 0);
+            buf.load4(im, v, im_bytes);
+        } else {
+            const unsigned kstep = (unsigned)(cs * lay.bins * 8);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const unsigned v = kk + j < K ? off : kOutside;
+                re[j] = buf.load1(v, j * kstep);
+                im[j] = buf.load1(v, j * kstep + im_bytes);
+            }
+        }
+    }
+
+    // Terms of the staged values into the LDS image; `sign` conjugates.
+    __device__ __forceinline__ void store(char *img, unsigned sign, int tid) const {
+        char *q = img + (kq_of(tid) * RP + row_of(tid)) * 8;
+        uint2 h, m, l;
+        split4(re[0], re[1], re[2], re[3], h, m, l);
+        *reinterpret_cast<uint2 *>(q) = h;
+        *reinterpret_cast<uint2 *>(q + PLANE) = m;
+        *reinterpret_cast<uint2 *>(q + 2 * PLANE) = l;
+        split4(flip(im[0], sign), flip(im[1], sign), flip(im[2], sign), flip(im[3], sign), h, m, l);
+        *reinterpret_cast<uint2 *>(q + 3 * PLANE) = h;
+        *reinterpret_cast<uint2 *>(q + 4 * PLANE) = m;
+        *reinterpret_cast<uint2 *>(q + 5 * PLANE) = l;
+    }
+
+    // MFMA fragment of plane c: lane half lk holds k 8 lk .. 8 lk + 7.
+    static __device__ __forceinline__ bf16x8 fragment(const char *img, int c, int row, int lk) {
+        const char *q = img + c * PLANE + (2 * lk * RP + row) * 8;
+        const uint2 a = *reinterpret_cast<const uint2 *>(q), b = *reinterpret_cast<const uint2 *>(q + RP * 8);
+        return __builtin_bit_cast(bf16x8, make_uint4(a.x, a.y, b.x, b.y));
+    }
+};
+
+// One workgroup's share of the contraction: workgroup number wg of prm's grid.
+template <bool AKF, bool BKF>
+__device__ __forceinline__ void cgemm_split_body(const GemmParams &prm, const unsigned wg, char *smem) {
+    using LoadA = SplitLoader<AKF>;
+    using LoadB = SplitLoader<BKF>;
+    char *As = smem, *Bs = As + LoadA::BYTES;
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave >> 1, wn = wave & 1;
+
+    // XCD-aware decomposition of the flat workgroup index (see file header).
+    const int tiles = prm.tiles_m * prm.tiles_n;
+    const int xcd = wg % kXcds, slot = wg / kXcds;
+    const int bins_per_xcd = prm.bins / kXcds;
+    const int bin = xcd * bins_per_xcd + slot / tiles;
+    const int tile = slot % tiles;
+    const int tm = tile / prm.tiles_n, tn = tile % prm.tiles_n;
+    const int m0 = tm * ROWS, n0 = tn * ROWS;
+    const int M = prm.M, N = prm.N, K = prm.K;
+
+    floatx16 acc_r, acc_i;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) { acc_r[v] = 0.f; acc_i[v] = 0.f; }
+
+    LoadA la;
+    LoadB lb;
+    la.prepare(prm.layA, prm.a_rs, prm.a_cs, m0, M, tid);
+    lb.prepare(prm.layB, prm.b_cs, prm.b_rs, n0, N, tid);     // B(k, n): the loader's row index is n
+    auto issue = [&](int k0) {
+        la.load(prm.A, prm.layA, prm.a_rs, prm.a_cs, bin, m0, k0, K, tid);
+        lb.load(prm.B, prm.layB, prm.b_cs, prm.b_rs, bin, n0, k0, K, tid);
+    };
+    const int lrow = lane & 31, lk = lane >> 5;
+    issue(0);
+    for (int k0 = 0; k0 < K; k0 += TK) {
+        if (k0) __syncthreads();                 // every wave has read the previous tile
+        la.store(As, prm.a_sign, tid);
+        lb.store(Bs, prm.b_sign, tid);
+        __syncthreads();
+        if (k0 + TK < K) issue(k0 + TK);
+        __builtin_amdgcn_sched_barrier(0);       // ... and the gathers stay in front of the products
+        bf16x8 ar[3], ai[3], br[3], bi[3];
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+            br[t] = LoadB::fragment(Bs, t, wn * 32 + lrow, lk);
+            bi[t] = LoadB::fragment(Bs, 3 + t, wn * 32 + lrow, lk);
+            ar[t] = LoadA::fragment(As, t, wm * 32 + lrow, lk);
+            ai[t] = LoadA::fragment(As, 3 + t, wm * 32 + lrow, lk);
+        }
+        // one component after the other: registers for one sum of small products, and the
+        // negated terms take the place of the others
+        multiply_split(acc_i, ar, bi, ai, br);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t < 3; ++t) bi[t] = negated(bi[t]);
+        multiply_split(acc_r, ar, br, ai, bi);
+    }
+
+    // D layout of the 32x32 MFMA: lane l, register v -> row 8*(v/4) + 4*(l/32) + v%4, col l%32.
+    // The lane halves trade places between the components, so that one store covers a row's real
+    // parts (lanes 0 .. 31) and its imaginary parts (32 .. 63): whole runs of the layout, half the
+    // write requests.
+    const int comp = lk, nl = wn * 32 + lrow, ml = wm * 32;
+    const bool n_ok = n0 + nl < N;
+    const size_t row = (size_t)prm.c_rs * prm.layC.bins * 2;              // floats per step of m
+    char *cb = reinterpret_cast<char *>(prm.C + (size_t)bin * (2u << prm.layC.tsh) + prm.layC.part(n0) + (size_t)m0 * row);
+    const unsigned lo = (unsigned)((prm.layC.part(nl) + ((size_t)comp << prm.layC.tsh)) * sizeof(float));
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int mv = ml + 8 * (v / 4) + (v % 4);
+        float q0 = acc_r[v], q1 = acc_i[v];
+        swap_halves(q0, q1);                                              // rows mv and mv + 4
+        if (n_ok && m0 + mv < M) *reinterpret_cast<float *>(cb + (size_t)mv * row * sizeof(float) + lo) = q0;
+        if (n_ok && m0 + mv + 4 < M) *reinterpret_cast<float *>(cb + (size_t)(mv + 4) * row * sizeof(float) + lo) = q1;
+    }
+}
+
+constexpr int kSplitLds = SplitLoader<true>::BYTES + SplitLoader<false>::BYTES;
+
+template <bool AKF, bool BKF>
+__global__ void __launch_bounds__(256, 3) cgemm_split_kernel(GemmParams prm) {
+    __shared__ __align__(16) char smem[kSplitLds];
+    cgemm_split_body<AKF, BKF>(prm, blockIdx.x, smem);
+}
+
+// Both contractions of the backward pass in one launch (see cgemm_pair_kernel in
+// cgemm_kernels.hip): workgroups [0, n1) work on p1, the rest on p2.
+struct SplitPairParams {
+    GemmParams p1, p2;
+    unsigned n1;
+};
+template <bool AKF1, bool AKF2>
+__global__ void __launch_bounds__(256, 3) cgemm_split_pair_kernel(SplitPairParams pp) {
+    __shared__ __align__(16) char smem[kSplitLds];
+    if (blockIdx.x < pp.n1) cgemm_split_body<AKF1, false>(pp.p1, blockIdx.x, smem);
+    else cgemm_split_body<AKF2, false>(pp.p2, blockIdx.x - pp.n1, smem);
+}
+
+static long tile_grid(GemmParams &p) {
+    p.tiles_m = (p.M + ROWS - 1) / ROWS;
+    p.tiles_n = (p.N + ROWS - 1) / ROWS;
+    return (long)p.bins * p.tiles_m * p.tiles_n;
+}
+
+// The matrix cores bound a contraction whose products per operand element are many: a bin's M N K
+// products against its M K + K N + M N elements, which the fp32 form balances at about 30 (64 x 64 x
+// 128: 26; 16384 x 64 x 64: 32).  Below that both forms wait for memory and the bf16 one only draws
+// more power, which the transforms that follow pay in clock (27x27 and 56x56 layers at 26 and 32: the
+// contraction 5 .. 9 % faster, the step 1 .. 2 % slower); at 51 .. 77
+// it is 10 .. 19 % faster.
+bool split_pays(const GemmParams &p) {
+    const double m = p.M, n = p.N, k = p.K;
+    return m * n * k >= 48.0 * (m * k + k * n + m * n);
+}
+
+hipError_t launch_cgemm_split(GemmParams p, bool akf, bool bkf, LaunchCtx st) {
+    const long grid = tile_grid(p);
+    if (grid > 0x7fffffffL) return hipErrorInvalidValue;
+    auto go = [&](auto k) { launch_kernel(k, dim3((unsigned)grid), dim3(256), 0, st, p); return hipGetLastError(); };
+    if (akf && bkf) return go(cgemm_split_kernel<true, true>);
+    if (akf) return go(cgemm_split_kernel<true, false>);
+    return bkf ? hipErrorInvalidValue : go(cgemm_split_kernel<false, false>);
+}
+
+hipError_t launch_cgemm_split_pair(const GemmParams &p1, bool akf1, const GemmParams &p2, bool akf2, LaunchCtx st) {
+    SplitPairParams pp{p1, p2, 0};
+    const long n1 = tile_grid(pp.p1), n2 = tile_grid(pp.p2);
+    if (n1 + n2 > 0x7fffffffL) return hipErrorInvalidValue;
+    pp.n1 = (unsigned)n1;     // a multiple of the XCD count, as bins is
+    auto go = [&](auto k) { launch_kernel(k, dim3((unsigned)(n1 + n2)), dim3(256), 0, st, pp); return hipGetLastError(); };
+    if (akf1) return akf2 ? hipErrorInvalidValue : go(cgemm_split_pair_kernel<true, false>);
+    return akf2 ? go(cgemm_split_pair_kernel<false, true>) : hipErrorInvalidValue;
+}
+
+}  // namespace fc

@@ -10,11 +10,11 @@ namespace fc {
 // that one dispatch (their elapsed time is the kernel's own execution time, without the gaps
 // that events recorded between launches would include).
 // Switches of the contraction for A/B runs (environment variables FFTCONV_GEMM_TILE, _NO_TAIL,
-// _NO_PAIR, _NO_BINGROUP, _NO_FAST, _NO_THIN and FFTCONV_BG_TILE), read once when a handle is created; none
+// _NO_PAIR, _NO_BINGROUP, _NO_FAST, _NO_THIN, _NO_SPLIT and FFTCONV_BG_TILE), read once when a handle is created; none
 // changes a result beyond rounding.  All off by default.
 struct GemmSwitches {
     int tile = -1;          // 0..5: another tile shape, single kernels only; -1: the default
-    bool no_tail = false, no_pair = false, no_bingroup = false, no_fast = false, no_thin = false;
+    bool no_tail = false, no_pair = false, no_bingroup = false, no_fast = false, no_thin = false, no_split = false;
     int bg_tile = 0;        // per-wave tile of the four-bins-per-line kernel
 };
 GemmSwitches read_gemm_switches();
