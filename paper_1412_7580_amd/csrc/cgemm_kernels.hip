@@ -538,8 +538,8 @@ static hipError_t run_gemm(GemmParams prm, LaunchCtx st) {
 }
 
 // Tile shapes (M x N on four waves): 0 128x128, 1 64x128, 2 128x64, 3 64x64; 4 and 5 are 64x64
-// with 2 and 4 tiles of register staging ahead.  3 is the default, the others are kept for
-// A/B runs.  1-, 2- and 8-wave workgroups and TK = 8 / 32 were also measured; none beat 3.
+// with 2 and 4 tiles of register staging ahead.  6 and 7 are 32x128 and 128x32.  3 is the
+// default, 6 and 7 serve narrow sides (narrow_tile), the others are kept for A/B runs.  1-, 2- and 8-wave workgroups and TK = 8 / 32 were also measured; none beat 3.
 template <bool AKF, bool BKF, bool VEC>
 static hipError_t dispatch_tile(int shape, GemmParams prm, LaunchCtx st) {
     switch (shape) {
@@ -549,6 +549,8 @@ static hipError_t dispatch_tile(int shape, GemmParams prm, LaunchCtx st) {
         case 3: return run_gemm<2, 2, 1, 1, 16, AKF, BKF, VEC, 3>(prm, st);
         case 4: return run_gemm<2, 2, 1, 1, 16, AKF, BKF, VEC, 3, 2>(prm, st);
         case 5: return run_gemm<2, 2, 1, 1, 16, AKF, BKF, VEC, 3, 4>(prm, st);
+        case 6: return run_gemm<1, 4, 1, 1, 16, AKF, BKF, VEC, 3>(prm, st);
+        case 7: return run_gemm<4, 1, 1, 1, 16, AKF, BKF, VEC, 3>(prm, st);
         default: return hipErrorInvalidValue;
     }
 }
@@ -571,10 +573,28 @@ GemmSwitches read_gemm_switches() {
 static const GemmSwitches kDefaultSwitches{};
 static const GemmSwitches &switches_of(const GemmSwitches *sw) { return sw ? *sw : kDefaultSwitches; }
 
+// A side of at most 32 against one of at least 128 (a few images served through a wide layer, a
+// layer of few channels): 32x128 or 128x32 tiles, as half of every 64x64 tile and of its products
+// would be padding: 8 images, 256 -> 256 channels, 27x27, weights ahead 117 -> 91 us a pass, bprop 155 ->
+// 125; 128 images, 32 -> 32 channels 40 -> 36.  Not where that leaves compute units without a workgroup
+// (112 workgroups: 33 -> 35).  Under fast addressing the longer tile's per-lane offsets must fit, too.
+static bool narrow_tile(const GemmParams &prm) {
+    if (!((prm.M <= 32 && prm.N >= 128) || (prm.N <= 32 && prm.M >= 128))) return false;
+    const int longer = prm.M > prm.N ? prm.M : prm.N;
+    if ((long)prm.bins * ((longer + 127) / 128) < 256) return false;
+    if (!prm.fast) return true;
+    long stride = prm.a_rs > prm.a_cs ? prm.a_rs : prm.a_cs;
+    for (long s : {prm.b_rs, prm.b_cs, prm.c_rs}) stride = s > stride ? s : stride;
+    return (double)stride * prm.bins * 2 * 4 * 129 < 2147483648.0;
+}
+
 // 64x64 tiles on four waves with one tile of register staging ahead (shape 3) measured fastest
 // for every layer shape tried (more workgroups in flight beat the larger tiles' operand reuse
 // and the deeper staging's registers).
-static int pick_tile(const GemmSwitches &sw) { return sw.tile >= 0 ? sw.tile : 3; }
+static int pick_tile(const GemmSwitches &sw, const GemmParams &prm) {
+    if (sw.tile >= 0) return sw.tile;
+    return narrow_tile(prm) ? (prm.M <= 32 ? 6 : 7) : 3;
+}
 
 // Fast addressing of an operand (see TileLoader::prepare_fast): one index of the matrix is the
 // contiguous plane index, the other moves `stride` planes per step.  When that stride is a
@@ -661,7 +681,7 @@ static hipError_t launch_prepared(const Prepared &q, LaunchCtx st) {
     if (q.thin) return launch_cgemm_thin(prm, st);
     if (q.bingroup) return launch_cgemm_bingroup(prm, q.akf, q.bkf, st);
     if (q.split) return launch_cgemm_split(prm, q.akf, q.bkf, st);
-    const int shape = pick_tile(sw);
+    const int shape = pick_tile(sw, prm);
     if (q.vec && shape == 3 && sw.tile < 0 && !sw.no_tail) {
         // a short last round (at most a quarter of the resident workgroups): split its tiles
         GemmParams p2 = prm;
