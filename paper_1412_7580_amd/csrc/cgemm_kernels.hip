@@ -577,8 +577,11 @@ static const GemmSwitches &switches_of(const GemmSwitches *sw) { return sw ? *sw
 // layer of few channels): 32x128 or 128x32 tiles, as half of every 64x64 tile and of its products
 // would be padding: 8 images, 256 -> 256 channels, 27x27, weights ahead 117 -> 91 us a pass, bprop 155 ->
 // 125; 128 images, 32 -> 32 channels 40 -> 36.  Not where that leaves compute units without a workgroup
-// (112 workgroups: 33 -> 35).  Under fast addressing the longer tile's per-lane offsets must fit, too.
-static bool narrow_tile(const GemmParams &prm) {
+// (112 workgroups: 33 -> 35), nor with
+// gathers of 4 bytes or runs of four planes, where the gathers are the bound, nor
+// for two K tiles or fewer (16 images 160x160, 16 -> 48 channels: 129 -> 131).  Under fast addressing the longer tile's per-lane offsets must fit, too.
+static bool narrow_tile(const GemmParams &prm, bool vec) {
+    if (!vec || prm.layA.tsh < 3 || prm.K < 32) return false;
     if (!((prm.M <= 32 && prm.N >= 128) || (prm.N <= 32 && prm.M >= 128))) return false;
     const int longer = prm.M > prm.N ? prm.M : prm.N;
     if ((long)prm.bins * ((longer + 127) / 128) < 256) return false;
@@ -591,9 +594,9 @@ static bool narrow_tile(const GemmParams &prm) {
 // 64x64 tiles on four waves with one tile of register staging ahead (shape 3) measured fastest
 // for every layer shape tried (more workgroups in flight beat the larger tiles' operand reuse
 // and the deeper staging's registers).
-static int pick_tile(const GemmSwitches &sw, const GemmParams &prm) {
+static int pick_tile(const GemmSwitches &sw, const GemmParams &prm, bool vec) {
     if (sw.tile >= 0) return sw.tile;
-    return narrow_tile(prm) ? (prm.M <= 32 ? 6 : 7) : 3;
+    return narrow_tile(prm, vec) ? (prm.M <= 32 ? 6 : 7) : 3;
 }
 
 // Fast addressing of an operand (see TileLoader::prepare_fast): one index of the matrix is the
@@ -648,7 +651,7 @@ static hipError_t prepare(const GemmOperand &A, const GemmOperand &B, float *C, 
                     bins % (4 * kXcds) == 0 && (akf || A.rs == 1) && (bkf || B.cs == 1) && C_cs == 1 &&
                     C_rs % 4 == 0 && N % 4 == 0 && ((size_t)C & 15) == 0;
     out->thin = !sw.no_thin && thin_supported(prm);
-    out->split = prm.fast && !out->bingroup && (akf || !bkf) && !sw.no_split && sw.tile < 0 && split_pays(prm);
+    out->split = !out->bingroup && (akf || !bkf) && !sw.no_split && sw.tile < 0 && split_pays(prm, out->vec) && !narrow_tile(prm, out->vec);
     return hipSuccess;
 }
 
@@ -680,8 +683,8 @@ static hipError_t launch_prepared(const Prepared &q, LaunchCtx st) {
     const GemmSwitches &sw = switches_of(st.sw);
     if (q.thin) return launch_cgemm_thin(prm, st);
     if (q.bingroup) return launch_cgemm_bingroup(prm, q.akf, q.bkf, st);
-    if (q.split) return launch_cgemm_split(prm, q.akf, q.bkf, st);
-    const int shape = pick_tile(sw, prm);
+    if (q.split) return launch_cgemm_split(prm, q.akf, q.bkf, q.vec, st);
+    const int shape = pick_tile(sw, prm, q.vec);
     if (q.vec && shape == 3 && sw.tile < 0 && !sw.no_tail) {
         // a short last round (at most a quarter of the resident workgroups): split its tiles
         GemmParams p2 = prm;
@@ -764,7 +767,7 @@ hipError_t launch_cgemm_pair(const GemmProblem &g1, const GemmProblem &g2, Launc
     if (hipError_t e = prepare(g2.A, g2.B, g2.C, g2.layC, g2.C_rs, g2.C_cs, g2.M, g2.N, g2.K, g2.bins, sw, &q2); e != hipSuccess) return e;
     if (!(q1.vec && q2.vec) || q1.bingroup || q2.bingroup || q1.thin || q2.thin) return hipErrorInvalidValue;
     if (q1.split && q2.split && !q1.bkf && !q2.bkf && q1.akf != q2.akf)
-        return launch_cgemm_split_pair(q1.prm, q1.akf, q2.prm, q2.akf, st);
+        return launch_cgemm_split_pair(q1.prm, q1.akf, q2.prm, true, st);
     GemmPairParams pp;
     pp.p1 = q1.prm; pp.p2 = q2.prm; pp.n1 = 0;
     if (q1.akf && q1.bkf) return pair_second<true, true>(q2, pp, st);

@@ -1,5 +1,5 @@
 // Per-bin complex contraction on the bf16 matrix cores, for layers whose channels and samples are
-// many enough that the fp32 ones are the bound (see split_pays()).
+// many enough that the fp32 ones would be the bound (see split_pays()).
 //
 // Same operation as cgemm_kernels.hip (the Cgemm row of Table 1 of the fbfft paper), same layout,
 // same order of workgroups.  Every fp32 operand value is cut, without loss, into three bf16 terms
@@ -22,11 +22,17 @@
 #include "gemm_params.hpp"
 #include "bf16_split.hpp"
 
+#include <type_traits>
+
 namespace fc {
 
 constexpr unsigned kOutside = 0x80000000u;       // byte offset past every buffer range
 
 constexpr int ROWS = 64, TK = 16, KQ = TK / 4;
+
+// How an operand's tile is read.  Fast: see prepare().  Vec: 16-byte gathers along k with general
+// index arithmetic.  Scalar: 4-byte gathers, any strides and extents.
+enum : int { kFast = 0, kVec = 1, kScalar = 2 };
 
 // Loader of one operand tile (ROWS x TK) with the "row" index being m (or n) and the
 // reduction index k.  KF: k is the contiguous plane index, and a unit of work is four
@@ -35,7 +41,7 @@ constexpr int ROWS = 64, TK = 16, KQ = TK / 4;
 // would touch, and the four k that one LDS word pair holds meet in one lane).
 // LDS image: [6 = (re, im) x (h, m, l)][k / 4][row] of four bf16; RP rows a plane, so that both
 // kinds of unit store, and the fragments load, without bank conflicts.
-template <bool KF>
+template <bool KF, int MODE>
 struct SplitLoader {
     static constexpr int RP = ROWS + 8, PLANE = KQ * RP * 8, BYTES = 6 * PLANE;
     float re[4], im[4];
@@ -47,6 +53,7 @@ struct SplitLoader {
     // The strided index moves in whole plane tiles (fast_addressing() in cgemm_kernels.hip), so an
     // address is a uniform base that changes with the K tile and an offset that never does.
     __device__ __forceinline__ void prepare(const FreqLayout &lay, long rs, long cs, int r0, int R, int tid) {
+        if constexpr (MODE != kFast) return;
         const int rr = row_of(tid), kk = 4 * kq_of(tid);
         const size_t o = KF ? (size_t)rr * rs * lay.bins * 2 + lay.part(kk)
                             : lay.part(rr) + (size_t)kk * cs * lay.bins * 2;
@@ -54,7 +61,11 @@ struct SplitLoader {
     }
 
     __device__ __forceinline__ void load(const float *base, const FreqLayout &lay, long rs, long cs, int bin, int r0,
-                                         int k0, int K, int tid) {
+                                         int k0, int R, int K, int tid) {
+        if constexpr (MODE != kFast) {
+            load_general(base, lay, rs, cs, bin, r0 + row_of(tid), k0 + 4 * kq_of(tid), R, K);
+            return;
+        }
         size_t o = (size_t)bin * (2u << lay.tsh);
         if constexpr (KF) o += (size_t)r0 * rs * lay.bins * 2 + lay.part(k0);
         else o += lay.part(r0) + (size_t)k0 * cs * lay.bins * 2;
@@ -73,6 +84,30 @@ struct SplitLoader {
                 re[j] = buf.load1(v, j * kstep);
                 im[j] = buf.load1(v, j * kstep + im_bytes);
             }
+        }
+    }
+
+    __device__ __forceinline__ void load_general(const float *base, const FreqLayout &lay, long rs, long cs, int bin,
+                                                 int r, int kk, int R, int K) {
+        const unsigned im_off = 1u << lay.tsh;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { re[j] = 0.f; im[j] = 0.f; }
+        if (r >= R) return;
+        if constexpr (KF && MODE == kVec) {
+            if (kk < K) {                                 // K is a multiple of 4
+                const float *q = base + lay.index(r * rs + kk * cs, bin, 0);
+                const float4 a = *reinterpret_cast<const float4 *>(q), b = *reinterpret_cast<const float4 *>(q + im_off);
+                re[0] = a.x; re[1] = a.y; re[2] = a.z; re[3] = a.w;
+                im[0] = b.x; im[1] = b.y; im[2] = b.z; im[3] = b.w;
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (kk + j < K) {
+                    const float *q = base + lay.index(r * rs + (kk + j) * cs, bin, 0);
+                    re[j] = q[0];
+                    im[j] = q[im_off];
+                }
         }
     }
 
@@ -99,10 +134,10 @@ struct SplitLoader {
 };
 
 // One workgroup's share of the contraction: workgroup number wg of prm's grid.
-template <bool AKF, bool BKF>
+template <bool AKF, bool BKF, int MODE>
 __device__ __forceinline__ void cgemm_split_body(const GemmParams &prm, const unsigned wg, char *smem) {
-    using LoadA = SplitLoader<AKF>;
-    using LoadB = SplitLoader<BKF>;
+    using LoadA = SplitLoader<AKF, MODE>;
+    using LoadB = SplitLoader<BKF, MODE>;
     char *As = smem, *Bs = As + LoadA::BYTES;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -127,8 +162,8 @@ __device__ __forceinline__ void cgemm_split_body(const GemmParams &prm, const un
     la.prepare(prm.layA, prm.a_rs, prm.a_cs, m0, M, tid);
     lb.prepare(prm.layB, prm.b_cs, prm.b_rs, n0, N, tid);     // B(k, n): the loader's row index is n
     auto issue = [&](int k0) {
-        la.load(prm.A, prm.layA, prm.a_rs, prm.a_cs, bin, m0, k0, K, tid);
-        lb.load(prm.B, prm.layB, prm.b_cs, prm.b_rs, bin, n0, k0, K, tid);
+        la.load(prm.A, prm.layA, prm.a_rs, prm.a_cs, bin, m0, k0, M, K, tid);
+        lb.load(prm.B, prm.layB, prm.b_cs, prm.b_rs, bin, n0, k0, N, K, tid);
     };
     const int lrow = lane & 31, lk = lane >> 5;
     issue(0);
@@ -162,6 +197,17 @@ __device__ __forceinline__ void cgemm_split_body(const GemmParams &prm, const un
     // write requests.
     const int comp = lk, nl = wn * 32 + lrow, ml = wm * 32;
     const bool n_ok = n0 + nl < N;
+    if (MODE != kFast) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int m = m0 + ml + 8 * (v / 4) + (v % 4);
+            float q0 = acc_r[v], q1 = acc_i[v];
+            swap_halves(q0, q1);
+            if (n_ok && m < M) prm.C[prm.layC.index(m * prm.c_rs + (n0 + nl) * prm.c_cs, bin, comp)] = q0;
+            if (n_ok && m + 4 < M) prm.C[prm.layC.index((m + 4) * prm.c_rs + (n0 + nl) * prm.c_cs, bin, comp)] = q1;
+        }
+        return;
+    }
     const size_t row = (size_t)prm.c_rs * prm.layC.bins * 2;              // floats per step of m
     char *cb = reinterpret_cast<char *>(prm.C + (size_t)bin * (2u << prm.layC.tsh) + prm.layC.part(n0) + (size_t)m0 * row);
     const unsigned lo = (unsigned)((prm.layC.part(nl) + ((size_t)comp << prm.layC.tsh)) * sizeof(float));
@@ -175,12 +221,12 @@ __device__ __forceinline__ void cgemm_split_body(const GemmParams &prm, const un
     }
 }
 
-constexpr int kSplitLds = SplitLoader<true>::BYTES + SplitLoader<false>::BYTES;
+constexpr int kSplitLds = SplitLoader<true, kFast>::BYTES + SplitLoader<false, kFast>::BYTES;
 
-template <bool AKF, bool BKF>
+template <bool AKF, bool BKF, int MODE>
 __global__ void __launch_bounds__(256, 3) cgemm_split_kernel(GemmParams prm) {
     __shared__ __align__(16) char smem[kSplitLds];
-    cgemm_split_body<AKF, BKF>(prm, blockIdx.x, smem);
+    cgemm_split_body<AKF, BKF, MODE>(prm, blockIdx.x, smem);
 }
 
 // Both contractions of the backward pass in one launch (see cgemm_pair_kernel in
@@ -189,11 +235,11 @@ struct SplitPairParams {
     GemmParams p1, p2;
     unsigned n1;
 };
-template <bool AKF1, bool AKF2>
+template <bool AKF1, bool AKF2, int MODE>
 __global__ void __launch_bounds__(256, 3) cgemm_split_pair_kernel(SplitPairParams pp) {
     __shared__ __align__(16) char smem[kSplitLds];
-    if (blockIdx.x < pp.n1) cgemm_split_body<AKF1, false>(pp.p1, blockIdx.x, smem);
-    else cgemm_split_body<AKF2, false>(pp.p2, blockIdx.x - pp.n1, smem);
+    if (blockIdx.x < pp.n1) cgemm_split_body<AKF1, false, MODE>(pp.p1, blockIdx.x, smem);
+    else cgemm_split_body<AKF2, false, MODE>(pp.p2, blockIdx.x - pp.n1, smem);
 }
 
 static long tile_grid(GemmParams &p) {
@@ -202,34 +248,52 @@ static long tile_grid(GemmParams &p) {
     return (long)p.bins * p.tiles_m * p.tiles_n;
 }
 
-// The matrix cores bound a contraction whose products per operand element are many: a bin's M N K
-// products against its M K + K N + M N elements, which the fp32 form balances at about 30 (64 x 64 x
-// 128: 26; 16384 x 64 x 64: 32).  Below that both forms wait for memory and the bf16 one only draws
-// more power, which the transforms that follow pay in clock (27x27 and 56x56 layers at 26 and 32: the
-// contraction 5 .. 9 % faster, the step 1 .. 2 % slower); at 51 .. 77
-// it is 10 .. 19 % faster.
-bool split_pays(const GemmParams &p) {
+// A bin's M N K products against its M K + K N + M N elements, by the layout's runs.  With runs of 32
+// or 64 planes (bases up to 16) gathers are whole lines and the products bound a layer early (fp32
+// form -> this, training step, us): 15 products an element (16 samples, 512 -> 512 channels, 8x8) 168 ->
+// 147, 16 (32 x 64 -> 64, 13x13) 46 -> 42, 43 (128 x 128 -> 128) 95 -> 86, 55 163 -> 144.  With runs of 8 or
+// 16 the gathers do, and the bf16 form's power costs the transforms behind it clock: 26 (128 x 64 ->
+// 64, 27x27) 120 -> 114 on one card and 124 on another, 32 (56x56, padded) 305 -> 310; 43 (64 x 256 ->
+// 256, 28x28 / 32x32) 545 -> 504 / 717 -> 679, 45 (128 x 96 -> 256, 27x27) 456 -> 407.  Runs of four and
+// single planes are the gathers' alone (64 x 63 -> 129, 45x45: 491 -> 513), and
+// 4-byte gathers count as short runs (128 x 37 -> 65, 13x13: 80 either way).
+bool split_pays(const GemmParams &p, bool vec) {
+    if (p.layA.tsh < 3) return false;
     const double m = p.M, n = p.N, k = p.K;
-    return m * n * k >= 48.0 * (m * k + k * n + m * n);
+    return m * n * k >= (p.layA.tsh >= 5 && vec ? 12.0 : 40.0) * (m * k + k * n + m * n);
 }
 
-hipError_t launch_cgemm_split(GemmParams p, bool akf, bool bkf, LaunchCtx st) {
+// go(integral_constant mode)
+template <class F>
+static hipError_t with_mode(int mode, F &&go) {
+    if (mode == kFast) return go(std::integral_constant<int, kFast>{});
+    if (mode == kVec) return go(std::integral_constant<int, kVec>{});
+    return go(std::integral_constant<int, kScalar>{});
+}
+
+hipError_t launch_cgemm_split(GemmParams p, bool akf, bool bkf, bool vec, LaunchCtx st) {
     const long grid = tile_grid(p);
-    if (grid > 0x7fffffffL) return hipErrorInvalidValue;
-    auto go = [&](auto k) { launch_kernel(k, dim3((unsigned)grid), dim3(256), 0, st, p); return hipGetLastError(); };
-    if (akf && bkf) return go(cgemm_split_kernel<true, true>);
-    if (akf) return go(cgemm_split_kernel<true, false>);
-    return bkf ? hipErrorInvalidValue : go(cgemm_split_kernel<false, false>);
+    if (grid > 0x7fffffffL || (!akf && bkf)) return hipErrorInvalidValue;
+    return with_mode(p.fast ? kFast : vec ? kVec : kScalar, [&](auto md) {
+        constexpr int MODE = decltype(md)::value;
+        auto k = akf ? (bkf ? cgemm_split_kernel<true, true, MODE> : cgemm_split_kernel<true, false, MODE>)
+                     : cgemm_split_kernel<false, false, MODE>;
+        launch_kernel(k, dim3((unsigned)grid), dim3(256), 0, st, p);
+        return hipGetLastError();
+    });
 }
 
-hipError_t launch_cgemm_split_pair(const GemmParams &p1, bool akf1, const GemmParams &p2, bool akf2, LaunchCtx st) {
+hipError_t launch_cgemm_split_pair(const GemmParams &p1, bool akf1, const GemmParams &p2, bool vec, LaunchCtx st) {
     SplitPairParams pp{p1, p2, 0};
     const long n1 = tile_grid(pp.p1), n2 = tile_grid(pp.p2);
     if (n1 + n2 > 0x7fffffffL) return hipErrorInvalidValue;
     pp.n1 = (unsigned)n1;     // a multiple of the XCD count, as bins is
-    auto go = [&](auto k) { launch_kernel(k, dim3((unsigned)(n1 + n2)), dim3(256), 0, st, pp); return hipGetLastError(); };
-    if (akf1) return akf2 ? hipErrorInvalidValue : go(cgemm_split_pair_kernel<true, false>);
-    return akf2 ? go(cgemm_split_pair_kernel<false, true>) : hipErrorInvalidValue;
+    return with_mode(p1.fast && p2.fast ? kFast : vec ? kVec : kScalar, [&](auto md) {
+        constexpr int MODE = decltype(md)::value;
+        auto k = akf1 ? cgemm_split_pair_kernel<true, false, MODE> : cgemm_split_pair_kernel<false, true, MODE>;
+        launch_kernel(k, dim3((unsigned)(n1 + n2)), dim3(256), 0, st, pp);
+        return hipGetLastError();
+    });
 }
 
 }  // namespace fc

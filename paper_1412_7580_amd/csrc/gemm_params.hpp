@@ -22,11 +22,11 @@ __device__ __forceinline__ float flip(float v, unsigned sign) {
     return __builtin_bit_cast(float, __builtin_bit_cast(unsigned, v) ^ sign);
 }
 
-// Contractions bound by the matrix cores, with fast addressing (cgemm_split.hip).  A pair is bprop
-// (A along the reduction) and accGrad (A along the rows), in either order.
-bool split_pays(const GemmParams &prm);
-hipError_t launch_cgemm_split(GemmParams prm, bool akf, bool bkf, LaunchCtx st);
-hipError_t launch_cgemm_split_pair(const GemmParams &p1, bool akf1, const GemmParams &p2, bool akf2, LaunchCtx st);
+// Contractions on the bf16 matrix cores (cgemm_split.hip).  vec: 16-byte gathers are possible.  A pair is
+// bprop (A along the reduction) and accGrad (A along the rows), akf1 saying which comes first.
+bool split_pays(const GemmParams &prm, bool vec);
+hipError_t launch_cgemm_split(GemmParams prm, bool akf, bool bkf, bool vec, LaunchCtx st);
+hipError_t launch_cgemm_split_pair(const GemmParams &p1, bool akf1, const GemmParams &p2, bool vec, LaunchCtx st);
 
 // Contractions with a side of at most four (cgemm_thin.hip).
 bool thin_supported(const GemmParams &prm);
