@@ -1,4 +1,4 @@
-// fp32 products on the bf16 matrix cores: the lossless cut of a value into three bf16 terms,
+// fp32 products on the bf16 matrix cores: the cut of a value into three bf16 terms (Dekker's splitting),
 // the six-product complex multiply-accumulate, and bounds-checked buffer loads for the gathers.
 #pragma once
 #include "gemm_params.hpp"
@@ -16,8 +16,10 @@ __device__ __forceinline__ unsigned pack_bf16(float a, float b) {        // v_cv
 __device__ __forceinline__ float low_of(unsigned p) { return __builtin_bit_cast(float, p << 16); }
 __device__ __forceinline__ float high_of(unsigned p) { return __builtin_bit_cast(float, p & 0xffff0000u); }
 
-// (a, b) = h + m + l, exactly: rounding to 8 bits leaves a remainder of at most 16 significant
-// bits, rounding that one of at most 8, and both subtractions are exact.
+// (a, b) = h + m + l: rounding to 8 bits leaves a remainder of at most 16 significant bits, rounding
+// that one of at most 8, and both subtractions are exact.  So the cut is, where h stays finite
+// (below 3.39e38) and l, which may end 23 bits under h, does not fall under bf16's smallest
+// subnormal, 2^-133: for sizes from 2^-110 on.  Conversion and matrix cores keep subnormals.
 __device__ __forceinline__ void split2(float a, float b, unsigned &h, unsigned &m, unsigned &l) {
     h = pack_bf16(a, b);
     const float ra = a - low_of(h), rb = b - high_of(h);
@@ -59,6 +61,23 @@ __device__ __forceinline__ void multiply_split(floatx16 &c, const bf16x8 (&ar)[3
     c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ai[0], bi[0], c, 0, 0, 0);
 #pragma unroll
     for (int v = 0; v < 16; ++v) c[v] += low[v];
+}
+
+// fp32 spans more than that, so the operands are cut at a power of two of their own.  2^16 makes the
+// cut exact for everything below 2^111, subnormals too (all are whole numbers of 2^-149).  What is larger,
+// and products whose sums pass 2^96, leave an infinity or a NaN in the sums; then one operand,
+// the other, and last both are halved instead.  (Halved, the cut is exact from 2^-109 on: 2^-205
+// of what made it necessary, or less.)
+constexpr float kScaleUp = 65536.f, kScaleDown = 0.5f;
+constexpr int kScalings = 4;
+__device__ __forceinline__ float scale_a(int attempt) { return attempt & 1 ? kScaleDown : kScaleUp; }
+__device__ __forceinline__ float scale_b(int attempt) { return attempt & 2 ? kScaleDown : kScaleUp; }
+
+// 0 for finite sums, else NaN.
+__device__ __forceinline__ float non_finite(const floatx16 &c, float t) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) t = fmaf(c[v], 0.f, t);
+    return t;
 }
 
 // Loads from a base that is uniform over the wave at per-lane byte offsets below 2^31; an offset

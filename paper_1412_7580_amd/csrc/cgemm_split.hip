@@ -4,7 +4,8 @@
 // Same operation as cgemm_kernels.hip (the Cgemm row of Table 1 of the fbfft paper), same layout,
 // same order of workgroups.  Every fp32 operand value is cut, without loss, into three bf16 terms
 // (x = h + m + l: each is the rounded value of what the ones before it leave, and 8 + 8 + 8 bits
-// hold the whole significand), and a real product is the six bf16 products hh, hm, mh, mm, hl,
+// hold the whole significand; bf16_split.hpp has the range and what widens it to all of fp32), and a
+// real product is the six bf16 products hh, hm, mh, mm, hl,
 // lh, which are exact and are summed in fp32 by v_mfma_f32_32x32x16_bf16.  What is left out (ml,
 // lm, ll) is at most 2^-23 of |a b| and of either sign, 2^-26 on average: below the rounding of the
 // fp32 sum itself.  The fp32 MFMA does 2 of K in 64 cycles, the six products do 16 of K in 192.
@@ -111,15 +112,16 @@ struct SplitLoader {
         }
     }
 
-    // Terms of the staged values into the LDS image; `sign` conjugates.
-    __device__ __forceinline__ void store(char *img, unsigned sign, int tid) const {
+    // Terms of the staged values, times `scale`, into the LDS image; `sign` conjugates.
+    __device__ __forceinline__ void store(char *img, float scale, unsigned sign, int tid) const {
         char *q = img + (kq_of(tid) * RP + row_of(tid)) * 8;
         uint2 h, m, l;
-        split4(re[0], re[1], re[2], re[3], h, m, l);
+        split4(scale * re[0], scale * re[1], scale * re[2], scale * re[3], h, m, l);
         *reinterpret_cast<uint2 *>(q) = h;
         *reinterpret_cast<uint2 *>(q + PLANE) = m;
         *reinterpret_cast<uint2 *>(q + 2 * PLANE) = l;
-        split4(flip(im[0], sign), flip(im[1], sign), flip(im[2], sign), flip(im[3], sign), h, m, l);
+        const float si = flip(scale, sign);
+        split4(si * im[0], si * im[1], si * im[2], si * im[3], h, m, l);
         *reinterpret_cast<uint2 *>(q + 3 * PLANE) = h;
         *reinterpret_cast<uint2 *>(q + 4 * PLANE) = m;
         *reinterpret_cast<uint2 *>(q + 5 * PLANE) = l;
@@ -133,14 +135,25 @@ struct SplitLoader {
     }
 };
 
-// One workgroup's share of the contraction: workgroup number wg of prm's grid.
+// This lane's number, computed anew at each place that asks, so that neither it nor what follows
+// from it takes registers in between.
+__device__ __forceinline__ int lane_number() {
+    unsigned zero = 0;
+    asm volatile("" : "+v"(zero));
+    return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero));
+}
+
+// One workgroup's share of the contraction, workgroup number wg of prm's grid, with the operands cut at
+// the given powers of two.  False, for all of the workgroup, if that left a sum that is not finite:
+// nothing is stored then, unless it is the last attempt.
 template <bool AKF, bool BKF, int MODE>
-__device__ __forceinline__ void cgemm_split_body(const GemmParams &prm, const unsigned wg, char *smem) {
+__device__ __forceinline__ bool cgemm_split_attempt(const GemmParams &prm, const unsigned wg, const int wave, const float scale_a,
+                                                    const float scale_b, const bool last, char *smem) {
     using LoadA = SplitLoader<AKF, MODE>;
     using LoadB = SplitLoader<BKF, MODE>;
     char *As = smem, *Bs = As + LoadA::BYTES;
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int lane = lane_number(), tid = wave * 64 + lane;
     const int wm = wave >> 1, wn = wave & 1;
 
     // XCD-aware decomposition of the flat workgroup index (see file header).
@@ -169,8 +182,8 @@ __device__ __forceinline__ void cgemm_split_body(const GemmParams &prm, const un
     issue(0);
     for (int k0 = 0; k0 < K; k0 += TK) {
         if (k0) __syncthreads();                 // every wave has read the previous tile
-        la.store(As, prm.a_sign, tid);
-        lb.store(Bs, prm.b_sign, tid);
+        la.store(As, scale_a, prm.a_sign, tid);
+        lb.store(Bs, scale_b, prm.b_sign, tid);
         __syncthreads();
         if (k0 + TK < K) issue(k0 + TK);
         __builtin_amdgcn_sched_barrier(0);       // ... and the gathers stay in front of the products
@@ -191,22 +204,32 @@ __device__ __forceinline__ void cgemm_split_body(const GemmParams &prm, const un
         multiply_split(acc_r, ar, br, ai, bi);
     }
 
+    if (!last) {
+        // one flag a wave, beside the image: the next attempt writes it after barriers of its own
+        int *redo = reinterpret_cast<int *>(Bs + LoadB::BYTES);
+        const bool bad = __ballot(non_finite(acc_i, non_finite(acc_r, 0.f)) != 0.f) != 0;
+        if (lane_number() == 0) redo[wave] = bad;
+        __syncthreads();                         // ... and every wave has read the image
+        if (redo[0] | redo[1] | redo[2] | redo[3]) return false;
+    }
+    const float unscale = 1.f / (scale_a * scale_b);                      // a power of two
+
     // D layout of the 32x32 MFMA: lane l, register v -> row 8*(v/4) + 4*(l/32) + v%4, col l%32.
     // The lane halves trade places between the components, so that one store covers a row's real
     // parts (lanes 0 .. 31) and its imaginary parts (32 .. 63): whole runs of the layout, half the
     // write requests.
-    const int comp = lk, nl = wn * 32 + lrow, ml = wm * 32;
+    const int out = lane_number(), comp = out >> 5, nl = wn * 32 + (out & 31), ml = wm * 32;
     const bool n_ok = n0 + nl < N;
     if (MODE != kFast) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int m = m0 + ml + 8 * (v / 4) + (v % 4);
-            float q0 = acc_r[v], q1 = acc_i[v];
+            float q0 = unscale * acc_r[v], q1 = unscale * acc_i[v];
             swap_halves(q0, q1);
             if (n_ok && m < M) prm.C[prm.layC.index(m * prm.c_rs + (n0 + nl) * prm.c_cs, bin, comp)] = q0;
             if (n_ok && m + 4 < M) prm.C[prm.layC.index((m + 4) * prm.c_rs + (n0 + nl) * prm.c_cs, bin, comp)] = q1;
         }
-        return;
+        return true;
     }
     const size_t row = (size_t)prm.c_rs * prm.layC.bins * 2;              // floats per step of m
     char *cb = reinterpret_cast<char *>(prm.C + (size_t)bin * (2u << prm.layC.tsh) + prm.layC.part(n0) + (size_t)m0 * row);
@@ -214,17 +237,31 @@ __device__ __forceinline__ void cgemm_split_body(const GemmParams &prm, const un
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
         const int mv = ml + 8 * (v / 4) + (v % 4);
-        float q0 = acc_r[v], q1 = acc_i[v];
+        float q0 = unscale * acc_r[v], q1 = unscale * acc_i[v];
         swap_halves(q0, q1);                                              // rows mv and mv + 4
         if (n_ok && m0 + mv < M) *reinterpret_cast<float *>(cb + (size_t)mv * row * sizeof(float) + lo) = q0;
         if (n_ok && m0 + mv + 4 < M) *reinterpret_cast<float *>(cb + (size_t)(mv + 4) * row * sizeof(float) + lo) = q1;
     }
+    return true;
 }
 
-constexpr int kSplitLds = SplitLoader<true, kFast>::BYTES + SplitLoader<false, kFast>::BYTES;
+// The attempts, of which all but the rarest data take one.  The empty asm keeps the compiler from
+// holding what the attempts have in common in registers through the K loop.
+template <bool AKF, bool BKF, int MODE>
+__device__ __forceinline__ void cgemm_split_body(const GemmParams &prm, const unsigned wg, char *smem) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#pragma unroll 1
+    for (int i = 0; i < kScalings; ++i) {
+        unsigned w = wg;
+        asm volatile("" : "+s"(w));
+        if (cgemm_split_attempt<AKF, BKF, MODE>(prm, w, wave, scale_a(i), scale_b(i), i == kScalings - 1, smem)) return;
+    }
+}
+
+constexpr int kSplitLds = SplitLoader<true, kFast>::BYTES + SplitLoader<false, kFast>::BYTES + 4 * (int)sizeof(int);
 
 template <bool AKF, bool BKF, int MODE>
-__global__ void __launch_bounds__(256, 3) cgemm_split_kernel(GemmParams prm) {
+__global__ void __launch_bounds__(256, MODE == kFast ? 4 : 3) cgemm_split_kernel(GemmParams prm) {
     __shared__ __align__(16) char smem[kSplitLds];
     cgemm_split_body<AKF, BKF, MODE>(prm, blockIdx.x, smem);
 }
@@ -236,7 +273,7 @@ struct SplitPairParams {
     unsigned n1;
 };
 template <bool AKF1, bool AKF2, int MODE>
-__global__ void __launch_bounds__(256, 3) cgemm_split_pair_kernel(SplitPairParams pp) {
+__global__ void __launch_bounds__(256, MODE == kFast ? 4 : 3) cgemm_split_pair_kernel(SplitPairParams pp) {
     __shared__ __align__(16) char smem[kSplitLds];
     if (blockIdx.x < pp.n1) cgemm_split_body<AKF1, false, MODE>(pp.p1, blockIdx.x, smem);
     else cgemm_split_body<AKF2, false, MODE>(pp.p2, blockIdx.x - pp.n1, smem);

@@ -76,3 +76,60 @@ def test_tile_edges(hd, S, f, fo, side):
 def test_rectangular_basis(hd):
     _check(hd, 20, 37, 75, 30, 19, 7, 4)
     _check(hd, 9, 3, 16, 30, 19, 5, 4)
+
+
+# powers of two on x, wt and gy
+ENDS = {"small_x": (-124, 0, 0), "small_wt": (0, -124, 0), "small_gy": (0, 0, -124), "large_x": (None, -30, -30),
+        "large_gy": (-30, -30, None), "apart_x": (116, -120, -120), "apart_wt": (-120, 116, -120),
+        "apart_gy": (-120, -120, 116), "product": (58, 52, 48)}
+
+
+@pytest.mark.parametrize("powers", ENDS.values(), ids=ENDS.keys())
+def test_ends_of_the_range(hd, powers):
+    """A layer of the bf16 form with operands at the ends of fp32's range, results inside it.
+    small: spectra of about 2^-120, whose bf16 remainders of the third order, 2^-137 and less, lie under
+    the smallest bf16 subnormal (2^-133).  large: planes of one value each with their sum, the zero
+    bin, between bf16's largest finite value (3.3895e38) and fp32's (3.4028e38); the other bins lie far
+    enough below it for the sum of a real and an imaginary part.  apart: one operand large, the other
+    small.  product: ordinary operands whose products are large.  The bound is the file's: every
+    step is a rounding of 2^-24 here, too (subnormals start 2^-6 below the small spectra's size, and
+    what they round is 2^-29 of it)."""
+    import torch
+    import torch.nn.functional as F
+    S = f = fo = 64
+    h, k = 13, 3
+    g = torch.Generator().manual_seed(3)
+    t = [torch.randn(S, f, h, h, generator=g), torch.randn(fo, f, k, k, generator=g),
+         torch.randn(S, fo, h - k + 1, h - k + 1, generator=g)]
+    for i, p in enumerate(powers):
+        if p is None:
+            n = t[i].shape[2] * t[i].shape[3]
+            t[i] = torch.sign(t[i][:, :, :1, :1]).expand_as(t[i]).contiguous() * (3.3995e38 / n)
+        else:
+            t[i] = t[i] * 2.0 ** p
+    (dx, dw, dg), (x, w, gy) = (o.cuda() for o in t), (o.double() for o in t)
+    passes = {"fprop": (0, 1, lambda: hd.fft_conv_fprop(dx, dw), lambda: F.conv2d(x, w)),
+              "bprop": (2, 1, lambda: hd.fft_conv_bprop(dg, dw, h, h), lambda: F.conv_transpose2d(gy, w)),
+              "accgrad": (0, 2, lambda: hd.fft_conv_accgrad(dx, dg),
+                          lambda: F.conv2d(x.transpose(0, 1), gy.transpose(0, 1)).transpose(0, 1))}
+    for p, (a, b, got, ref) in passes.items():
+        pa, pb = powers[a], powers[b]
+        if pa is not None and pb is not None and not -128 < pa + pb < 118:
+            continue                                        # the result itself would leave the range
+        r = ref()
+        assert r.abs().max() < 1e38 and r.abs().max() > 1e-36
+        assert _relerr(got(), r) <= TOL, (p, powers)
+
+
+def test_values_that_are_not_finite_stay_in_their_sample(hd):
+    import torch
+    import torch.nn.functional as F
+    g = torch.Generator().manual_seed(4)
+    x, w = torch.randn(64, 64, 13, 13, generator=g), torch.randn(64, 64, 3, 3, generator=g)
+    ref = F.conv2d(x.double(), w.double())
+    x[5, 7, 3, 3] = float("inf")
+    x[9, 1, 0, 0] = float("nan")
+    got = hd.fft_conv_fprop(x.cuda(), w.cuda()).cpu()
+    other = [s for s in range(64) if s not in (5, 9)]
+    assert not torch.isfinite(got[5]).any() and not torch.isfinite(got[9]).any()
+    assert float((got[other].double() - ref[other]).abs().max() / ref.abs().max()) <= TOL
