@@ -16,7 +16,7 @@
 // on XCD i % 8), so that the tiles of one bin, and neighbouring bins that share cache
 // lines in the plane-tiled layout, meet in the same L2.
 #include "kernels.hpp"
-#include "gemm_params.hpp"
+#include "gemm_rules.hpp"
 
 #include <cstdlib>
 #include <type_traits>
@@ -573,88 +573,6 @@ GemmSwitches read_gemm_switches() {
 static const GemmSwitches kDefaultSwitches{};
 static const GemmSwitches &switches_of(const GemmSwitches *sw) { return sw ? *sw : kDefaultSwitches; }
 
-// A side of at most 32 against one of at least 128 (a few images served through a wide layer, a
-// layer of few channels): 32x128 or 128x32 tiles, as half of every 64x64 tile and of its products
-// would be padding: 8 images, 256 -> 256 channels, 27x27, weights ahead 117 -> 91 us a pass, bprop 155 ->
-// 125; 128 images, 32 -> 32 channels 40 -> 36.  Not where that leaves compute units without a workgroup
-// (112 workgroups: 33 -> 35), nor with
-// gathers of 4 bytes or runs of four planes, where the gathers are the bound, nor
-// for two K tiles or fewer (16 images 160x160, 16 -> 48 channels: 129 -> 131).  Under fast addressing the longer tile's per-lane offsets must fit, too.
-static bool narrow_tile(const GemmParams &prm, bool vec) {
-    if (!vec || prm.layA.tsh < 3 || prm.K < 32) return false;
-    if (!((prm.M <= 32 && prm.N >= 128) || (prm.N <= 32 && prm.M >= 128))) return false;
-    const int longer = prm.M > prm.N ? prm.M : prm.N;
-    if ((long)prm.bins * ((longer + 127) / 128) < 256) return false;
-    if (!prm.fast) return true;
-    long stride = prm.a_rs > prm.a_cs ? prm.a_rs : prm.a_cs;
-    for (long s : {prm.b_rs, prm.b_cs, prm.c_rs}) stride = s > stride ? s : stride;
-    return (double)stride * prm.bins * 2 * 4 * 129 < 2147483648.0;
-}
-
-// 64x64 tiles on four waves with one tile of register staging ahead (shape 3) measured fastest
-// for every layer shape tried (more workgroups in flight beat the larger tiles' operand reuse
-// and the deeper staging's registers).
-static int pick_tile(const GemmSwitches &sw, const GemmParams &prm, bool vec) {
-    if (sw.tile >= 0) return sw.tile;
-    return narrow_tile(prm, vec) ? (prm.M <= 32 ? 6 : 7) : 3;
-}
-
-// Fast addressing of an operand (see TileLoader::prepare_fast): one index of the matrix is the
-// contiguous plane index, the other moves `stride` planes per step.  When that stride is a
-// whole number of plane tiles, a step of the strided index adds a constant to the element index,
-// whatever the contiguous index is, so addresses split into a uniform part and a per-lane
-// part.  The per-lane part must fit an unsigned 32-bit byte offset: 64 steps of the strided index.
-static bool fast_addressing(const FreqLayout &lay, long stride, int bins) {
-    const long T = 1L << lay.tsh;
-    if (stride <= 0 || stride % T != 0) return false;
-    return (double)stride * bins * 2 * 4 * 65 < 2147483648.0;
-}
-
-// Kernel parameters of one contraction and the kernel variant it can use.
-struct Prepared {
-    GemmParams prm;
-    bool akf, bkf;     // the reduction index is the contiguous plane index of A / B
-    bool vec;          // 16-byte gathers are possible
-    bool bingroup;     // the four-bins-per-line kernel applies
-    bool split;        // bound by the fp32 matrix cores: the bf16 kernel applies (cgemm_split.hip)
-    bool thin;         // a side of at most four: the vector-unit kernels apply (cgemm_thin.hip)
-};
-
-static hipError_t prepare(const GemmOperand &A, const GemmOperand &B, float *C, FreqLayout layC, long C_rs,
-                          long C_cs, int M, int N, int K, int bins, const GemmSwitches &sw, Prepared *out) {
-    if (bins % kXcds != 0) return hipErrorInvalidValue;   // N*(N/2+1) with N >= 8 always is
-    GemmParams &prm = out->prm;
-    prm.A = A.ptr; prm.B = B.ptr; prm.C = C;
-    prm.layA = A.lay; prm.layB = B.lay; prm.layC = layC;
-    prm.a_rs = A.rs; prm.a_cs = A.cs; prm.b_rs = B.rs; prm.b_cs = B.cs;
-    prm.c_rs = C_rs; prm.c_cs = C_cs;
-    prm.M = M; prm.N = N; prm.K = K; prm.bins = bins;
-    prm.tiles_m = prm.tiles_n = 0;
-    prm.split_from = 0xffffffffu;
-    prm.a_sign = A.conj ? 0x80000000u : 0u;
-    prm.b_sign = B.conj ? 0x80000000u : 0u;
-    const bool akf = (A.cs == 1), bkf = (B.rs == 1);
-    // 16-byte gathers need: runs of >= 4 planes, the contiguous index a multiple of 4 at every
-    // vector start (tile origins are), its extent a multiple of 4, and the other stride too.
-    auto vec_ok = [](const FreqLayout &l, long contiguous_extent, long other_stride, const float *p) {
-        return l.tsh >= 2 && contiguous_extent % 4 == 0 && other_stride % 4 == 0 && ((size_t)p & 15) == 0;
-    };
-    const bool va = akf ? vec_ok(A.lay, K, A.rs, A.ptr) : (A.rs == 1 && vec_ok(A.lay, M, A.cs, A.ptr));
-    const bool vb = bkf ? vec_ok(B.lay, K, B.cs, B.ptr) : (B.cs == 1 && vec_ok(B.lay, N, B.rs, B.ptr));
-    out->akf = akf; out->bkf = bkf; out->vec = va && vb;
-    prm.fast = (out->vec && fast_addressing(A.lay, akf ? A.rs : A.cs, bins) &&
-                fast_addressing(B.lay, bkf ? B.cs : B.rs, bins) && C_cs == 1 && fast_addressing(layC, C_rs, bins) &&
-                !sw.no_fast) ? 1 : 0;
-    // Layouts with runs of 4 planes (basis 64) put four bins in every 128-byte line: the
-    // bin-group kernel loads whole lines and multiplies the four bins side by side.
-    out->bingroup = out->vec && !sw.no_bingroup && A.lay.tsh == 2 && B.lay.tsh == 2 && layC.tsh == 2 &&
-                    bins % (4 * kXcds) == 0 && (akf || A.rs == 1) && (bkf || B.cs == 1) && C_cs == 1 &&
-                    C_rs % 4 == 0 && N % 4 == 0 && ((size_t)C & 15) == 0;
-    out->thin = !sw.no_thin && thin_supported(prm);
-    out->split = !out->bingroup && (akf || !bkf) && !sw.no_split && sw.tile < 0 && split_pays(prm, out->vec) && !narrow_tile(prm, out->vec);
-    return hipSuccess;
-}
-
 // Workgroups of the 64x64 kernel that are resident at once (four per compute unit: LDS).
 static long resident_workgroups() {
     static long slots = 0;
@@ -681,7 +599,7 @@ static hipError_t run_tail(GemmParams prm, long full, long rem, LaunchCtx st) {
 static hipError_t launch_prepared(const Prepared &q, LaunchCtx st) {
     const GemmParams &prm = q.prm;
     const GemmSwitches &sw = switches_of(st.sw);
-    if (q.thin) return launch_cgemm_thin(prm, st);
+    if (q.thin != Thin::none) return launch_cgemm_thin(prm, q.thin, st);
     if (q.bingroup) return launch_cgemm_bingroup(prm, q.akf, q.bkf, st);
     if (q.split) return launch_cgemm_split(prm, q.akf, q.bkf, q.vec, st);
     const int shape = pick_tile(sw, prm, q.vec);
@@ -752,12 +670,10 @@ static hipError_t pair_second(const Prepared &q2, GemmPairParams &pp, LaunchCtx 
 
 bool cgemm_pair_supported(const GemmProblem &g1, const GemmProblem &g2, const GemmSwitches *swp) {
     const GemmSwitches &sw = switches_of(swp);
-    if (sw.tile >= 0) return false;       // A/B runs of single-kernel shapes
-    if (sw.no_pair) return false;
     Prepared q1, q2;
     if (prepare(g1.A, g1.B, g1.C, g1.layC, g1.C_rs, g1.C_cs, g1.M, g1.N, g1.K, g1.bins, sw, &q1) != hipSuccess) return false;
     if (prepare(g2.A, g2.B, g2.C, g2.layC, g2.C_rs, g2.C_cs, g2.M, g2.N, g2.K, g2.bins, sw, &q2) != hipSuccess) return false;
-    return q1.vec && q2.vec && !q1.bingroup && !q2.bingroup && !q1.thin && !q2.thin;
+    return pair_form(q1, q2, sw) != Pair::none;
 }
 
 hipError_t launch_cgemm_pair(const GemmProblem &g1, const GemmProblem &g2, LaunchCtx st) {
@@ -765,9 +681,9 @@ hipError_t launch_cgemm_pair(const GemmProblem &g1, const GemmProblem &g2, Launc
     const GemmSwitches &sw = switches_of(st.sw);
     if (hipError_t e = prepare(g1.A, g1.B, g1.C, g1.layC, g1.C_rs, g1.C_cs, g1.M, g1.N, g1.K, g1.bins, sw, &q1); e != hipSuccess) return e;
     if (hipError_t e = prepare(g2.A, g2.B, g2.C, g2.layC, g2.C_rs, g2.C_cs, g2.M, g2.N, g2.K, g2.bins, sw, &q2); e != hipSuccess) return e;
-    if (!(q1.vec && q2.vec) || q1.bingroup || q2.bingroup || q1.thin || q2.thin) return hipErrorInvalidValue;
-    if (q1.split && q2.split && !q1.bkf && !q2.bkf && q1.akf != q2.akf)
-        return launch_cgemm_split_pair(q1.prm, q1.akf, q2.prm, true, st);
+    const Pair form = pair_form(q1, q2, sw);
+    if (form == Pair::none) return hipErrorInvalidValue;
+    if (form == Pair::split) return launch_cgemm_split_pair(q1.prm, q1.akf, q2.prm, true, st);
     GemmPairParams pp;
     pp.p1 = q1.prm; pp.p2 = q2.prm; pp.n1 = 0;
     if (q1.akf && q1.bkf) return pair_second<true, true>(q2, pp, st);

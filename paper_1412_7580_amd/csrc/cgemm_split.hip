@@ -285,21 +285,6 @@ static long tile_grid(GemmParams &p) {
     return (long)p.bins * p.tiles_m * p.tiles_n;
 }
 
-// A bin's M N K products against its M K + K N + M N elements, by the layout's runs.  With runs of 32
-// or 64 planes (bases up to 16) gathers are whole lines and the products bound a layer early (fp32
-// form -> this, training step, us): 15 products an element (16 samples, 512 -> 512 channels, 8x8) 168 ->
-// 147, 16 (32 x 64 -> 64, 13x13) 46 -> 42, 43 (128 x 128 -> 128) 95 -> 86, 55 163 -> 144.  With runs of 8 or
-// 16 the gathers do, and the bf16 form's power costs the transforms behind it clock: 26 (128 x 64 ->
-// 64, 27x27) 120 -> 114 on one card and 124 on another, 32 (56x56, padded) 305 -> 310; 43 (64 x 256 ->
-// 256, 28x28 / 32x32) 545 -> 504 / 717 -> 679, 45 (128 x 96 -> 256, 27x27) 456 -> 407.  Runs of four and
-// single planes are the gathers' alone (64 x 63 -> 129, 45x45: 491 -> 513), and
-// 4-byte gathers count as short runs (128 x 37 -> 65, 13x13: 80 either way).
-bool split_pays(const GemmParams &p, bool vec) {
-    if (p.layA.tsh < 3) return false;
-    const double m = p.M, n = p.N, k = p.K;
-    return m * n * k >= (p.layA.tsh >= 5 && vec ? 12.0 : 40.0) * (m * k + k * n + m * n);
-}
-
 // go(integral_constant mode)
 template <class F>
 static hipError_t with_mode(int mode, F &&go) {

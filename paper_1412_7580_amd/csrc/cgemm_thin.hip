@@ -204,30 +204,6 @@ __global__ void __launch_bounds__(64 * kThinWaves) cgemm_thin_acc_kernel(GemmPar
     }
 }
 
-// The three forms, with A, B and C as the passes lay them out: rows of W planes side by side, the
-// wide index in whole quads.
-enum class Thin { none, k, n, acc };
-static Thin thin_form(const GemmParams &p) {
-    const bool akf = p.a_rs != 1, bkf = p.b_cs != 1;      // reduction index contiguous (row index, if both are)
-    auto whole = [](const FreqLayout &l, const float *ptr) { return l.tsh >= 2 && ((size_t)ptr & 15) == 0; };
-    if (!whole(p.layA, p.A) || !whole(p.layB, p.B) || !whole(p.layC, p.C) || p.layA.tsh != p.layC.tsh) return Thin::none;
-    if (akf || p.K == 1) {
-        if (p.K <= 4 && p.a_rs == p.K && p.N % 4 == 0 && p.c_rs % 4 == 0 &&
-            (p.K == 1 || bkf ? p.b_cs == p.K || (p.K == 1 && p.b_cs == 1) : p.b_rs % 4 == 0 && p.b_cs == 1))
-            return Thin::k;
-    }
-    // (n only where runs are four planes: with longer ones a lane's 16 bytes are a part of each line and
-    // the matrix-core kernel is ahead, e.g. 128 samples, 64 -> 3 channels, 28x28 57 us a pass against 49;
-    // with runs of four 64x64 images 251 -> 181 us)
-    if (akf && !bkf && p.layA.tsh == 2 && p.N <= 4 && p.K % 4 == 0 && p.a_rs % 4 == 0 && p.b_rs == p.N && p.b_cs == 1) return Thin::n;
-    if (!akf && !bkf && p.N <= 4 && p.M % 4 == 0 && p.a_cs % 4 == 0 && p.b_rs == p.N && p.b_cs == 1) return Thin::acc;
-    return Thin::none;
-}
-
-bool thin_supported(const GemmParams &prm) {
-    return thin_form(prm) != Thin::none;
-}
-
 template <class... P, class... Q>
 static hipError_t launch_thin(void (*k)(P...), long grid, int block, LaunchCtx st, Q... q) {
     if (grid > 0x7fffffffL) return hipErrorInvalidValue;
@@ -258,8 +234,7 @@ static hipError_t run_thin(Thin form, const GemmParams &p, LaunchCtx st) {
     return launch_thin(cgemm_thin_acc_kernel<W>, (long)bin_blocks * ((p.M / 4 + per_run - 1) / per_run), 64 * kThinWaves, st, p, bin_blocks);
 }
 
-hipError_t launch_cgemm_thin(const GemmParams &p, LaunchCtx st) {
-    const Thin form = thin_form(p);
+hipError_t launch_cgemm_thin(const GemmParams &p, Thin form, LaunchCtx st) {
     switch (form == Thin::none ? 0 : form == Thin::k ? p.K : p.N) {
         case 1: return run_thin<1>(form, p, st);
         case 2: return run_thin<2>(form, p, st);

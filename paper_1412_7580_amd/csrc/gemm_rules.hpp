@@ -1,0 +1,136 @@
+// Which kernel runs a contraction: the rules, by sizes, layout and alignment, on the host alone (no
+// launch, no device call), so that a CPU program can ask them.
+#pragma once
+#include "gemm_params.hpp"
+
+#include <initializer_list>
+
+namespace fc {
+
+// Fast addressing of an operand (see TileLoader::prepare_fast): one index of the matrix is the
+// contiguous plane index, the other moves `stride` planes per step.  When that stride is a
+// whole number of plane tiles, a step of the strided index adds a constant to the element index,
+// whatever the contiguous index is, so addresses split into a uniform part and a per-lane
+// part.  The per-lane part must fit an unsigned 32-bit byte offset: 64 steps of the strided index.
+inline bool fast_addressing(const FreqLayout &lay, long stride, int bins) {
+    const long T = 1L << lay.tsh;
+    if (stride <= 0 || stride % T != 0) return false;
+    return (double)stride * bins * 2 * 4 * 65 < 2147483648.0;
+}
+
+// A side of at most 32 against one of at least 128 (a few images served through a wide layer, a
+// layer of few channels): 32x128 or 128x32 tiles, as half of every 64x64 tile and of its products
+// would be padding: 8 images, 256 -> 256 channels, 27x27, weights ahead 117 -> 91 us a pass, bprop 155 ->
+// 125; 128 images, 32 -> 32 channels 40 -> 36.  Not where that leaves compute units without a workgroup
+// (112 workgroups: 33 -> 35), nor with
+// gathers of 4 bytes or runs of four planes, where the gathers are the bound, nor
+// for two K tiles or fewer (16 images 160x160, 16 -> 48 channels: 129 -> 131).  Under fast addressing the longer tile's per-lane offsets must fit, too.
+inline bool narrow_tile(const GemmParams &prm, bool vec) {
+    if (!vec || prm.layA.tsh < 3 || prm.K < 32) return false;
+    if (!((prm.M <= 32 && prm.N >= 128) || (prm.N <= 32 && prm.M >= 128))) return false;
+    const int longer = prm.M > prm.N ? prm.M : prm.N;
+    if ((long)prm.bins * ((longer + 127) / 128) < 256) return false;
+    if (!prm.fast) return true;
+    long stride = prm.a_rs > prm.a_cs ? prm.a_rs : prm.a_cs;
+    for (long s : {prm.b_rs, prm.b_cs, prm.c_rs}) stride = s > stride ? s : stride;
+    return (double)stride * prm.bins * 2 * 4 * 129 < 2147483648.0;
+}
+
+// A bin's M N K products against its M K + K N + M N elements, by the layout's runs.  With runs of 32
+// or 64 planes (bases up to 16) gathers are whole lines and the products bound a layer early (fp32
+// form -> this, training step, us): 15 products an element (16 samples, 512 -> 512 channels, 8x8) 168 ->
+// 147, 16 (32 x 64 -> 64, 13x13) 46 -> 42, 43 (128 x 128 -> 128) 95 -> 86, 55 163 -> 144.  With runs of 8 or
+// 16 the gathers do, and the bf16 form's power costs the transforms behind it clock: 26 (128 x 64 ->
+// 64, 27x27) 120 -> 114 on one card and 124 on another, 32 (56x56, padded) 305 -> 310; 43 (64 x 256 ->
+// 256, 28x28 / 32x32) 545 -> 504 / 717 -> 679, 45 (128 x 96 -> 256, 27x27) 456 -> 407.  Runs of four and
+// single planes are the gathers' alone (64 x 63 -> 129, 45x45: 491 -> 513), and
+// 4-byte gathers count as short runs (128 x 37 -> 65, 13x13: 80 either way).
+inline bool split_pays(const GemmParams &p, bool vec) {
+    if (p.layA.tsh < 3) return false;
+    const double m = p.M, n = p.N, k = p.K;
+    return m * n * k >= (p.layA.tsh >= 5 && vec ? 12.0 : 40.0) * (m * k + k * n + m * n);
+}
+
+// The three forms, with A, B and C as the passes lay them out: rows of W planes side by side, the
+// wide index in whole quads.
+inline Thin thin_form(const GemmParams &p) {
+    const bool akf = p.a_rs != 1, bkf = p.b_cs != 1;      // reduction index contiguous (row index, if both are)
+    auto whole = [](const FreqLayout &l, const float *ptr) { return l.tsh >= 2 && ((size_t)ptr & 15) == 0; };
+    if (!whole(p.layA, p.A) || !whole(p.layB, p.B) || !whole(p.layC, p.C) || p.layA.tsh != p.layC.tsh ||
+        p.c_cs != 1) return Thin::none;
+    if (akf || p.K == 1) {
+        if (p.K <= 4 && p.a_rs == p.K && p.N % 4 == 0 && p.c_rs % 4 == 0 &&
+            (p.K == 1 || bkf ? p.b_cs == p.K || (p.K == 1 && p.b_cs == 1) : p.b_rs % 4 == 0 && p.b_cs == 1))
+            return Thin::k;
+    }
+    // (n only where runs are four planes: with longer ones a lane's 16 bytes are a part of each line and
+    // the matrix-core kernel is ahead, e.g. 128 samples, 64 -> 3 channels, 28x28 57 us a pass against 49;
+    // with runs of four 64x64 images 251 -> 181 us)
+    if (akf && !bkf && p.layA.tsh == 2 && p.N <= 4 && p.K % 4 == 0 && p.a_rs % 4 == 0 && p.b_rs == p.N && p.b_cs == 1) return Thin::n;
+    if (!akf && !bkf && p.N <= 4 && p.M % 4 == 0 && p.a_cs % 4 == 0 && p.b_rs == p.N && p.b_cs == 1) return Thin::acc;
+    return Thin::none;
+}
+
+// Kernel parameters of one contraction and the kernel variant it can use.
+struct Prepared {
+    GemmParams prm;
+    bool akf, bkf;     // the reduction index is the contiguous plane index of A / B
+    bool vec;          // 16-byte gathers are possible
+    bool bingroup;     // the four-bins-per-line kernel applies
+    bool split;        // bound by the fp32 matrix cores: the bf16 kernel applies (cgemm_split.hip)
+    Thin thin;         // a side of at most four: the vector-unit kernels apply (cgemm_thin.hip)
+};
+
+inline hipError_t prepare(const GemmOperand &A, const GemmOperand &B, float *C, FreqLayout layC, long C_rs,
+                          long C_cs, int M, int N, int K, int bins, const GemmSwitches &sw, Prepared *out) {
+    if (bins % kXcds != 0) return hipErrorInvalidValue;   // N*(N/2+1) with N >= 8 always is
+    GemmParams &prm = out->prm;
+    prm.A = A.ptr; prm.B = B.ptr; prm.C = C;
+    prm.layA = A.lay; prm.layB = B.lay; prm.layC = layC;
+    prm.a_rs = A.rs; prm.a_cs = A.cs; prm.b_rs = B.rs; prm.b_cs = B.cs;
+    prm.c_rs = C_rs; prm.c_cs = C_cs;
+    prm.M = M; prm.N = N; prm.K = K; prm.bins = bins;
+    prm.tiles_m = prm.tiles_n = 0;
+    prm.split_from = 0xffffffffu;
+    prm.a_sign = A.conj ? 0x80000000u : 0u;
+    prm.b_sign = B.conj ? 0x80000000u : 0u;
+    const bool akf = (A.cs == 1), bkf = (B.rs == 1);
+    // 16-byte gathers need: runs of >= 4 planes, the contiguous index a multiple of 4 at every
+    // vector start (tile origins are), its extent a multiple of 4, and the other stride too.
+    auto vec_ok = [](const FreqLayout &l, long contiguous_extent, long other_stride, const float *p) {
+        return l.tsh >= 2 && contiguous_extent % 4 == 0 && other_stride % 4 == 0 && ((size_t)p & 15) == 0;
+    };
+    const bool va = akf ? vec_ok(A.lay, K, A.rs, A.ptr) : (A.rs == 1 && vec_ok(A.lay, M, A.cs, A.ptr));
+    const bool vb = bkf ? vec_ok(B.lay, K, B.cs, B.ptr) : (B.cs == 1 && vec_ok(B.lay, N, B.rs, B.ptr));
+    out->akf = akf; out->bkf = bkf; out->vec = va && vb;
+    prm.fast = (out->vec && fast_addressing(A.lay, akf ? A.rs : A.cs, bins) &&
+                fast_addressing(B.lay, bkf ? B.cs : B.rs, bins) && C_cs == 1 && fast_addressing(layC, C_rs, bins) &&
+                !sw.no_fast) ? 1 : 0;
+    // Layouts with runs of 4 planes (basis 64) put four bins in every 128-byte line: the
+    // bin-group kernel loads whole lines and multiplies the four bins side by side.
+    out->bingroup = out->vec && !sw.no_bingroup && A.lay.tsh == 2 && B.lay.tsh == 2 && layC.tsh == 2 &&
+                    bins % (4 * kXcds) == 0 && (akf || A.rs == 1) && (bkf || B.cs == 1) && C_cs == 1 &&
+                    C_rs % 4 == 0 && N % 4 == 0 && ((size_t)C & 15) == 0;
+    out->thin = sw.no_thin ? Thin::none : thin_form(prm);
+    out->split = !out->bingroup && (akf || !bkf) && !sw.no_split && sw.tile < 0 && split_pays(prm, out->vec) && !narrow_tile(prm, out->vec);
+    return hipSuccess;
+}
+
+// 64x64 tiles on four waves with one tile of register staging ahead (shape 3) measured fastest
+// for every layer shape tried (more workgroups in flight beat the larger tiles' operand reuse
+// and the deeper staging's registers).
+inline int pick_tile(const GemmSwitches &sw, const GemmParams &prm, bool vec) {
+    if (sw.tile >= 0) return sw.tile;
+    return narrow_tile(prm, vec) ? (prm.M <= 32 ? 6 : 7) : 3;
+}
+
+// Two contractions in one launch: bprop and accGrad of a layer, which share operand A and neither of
+// which waits for the other.
+enum class Pair { none, tiles, split };
+inline Pair pair_form(const Prepared &q1, const Prepared &q2, const GemmSwitches &sw) {
+    if (sw.tile >= 0 || sw.no_pair) return Pair::none;       // A/B runs of single-kernel shapes
+    if (!q1.vec || !q2.vec || q1.bingroup || q2.bingroup || q1.thin != Thin::none || q2.thin != Thin::none) return Pair::none;
+    return q1.split && q2.split && !q1.bkf && !q2.bkf && q1.akf != q2.akf ? Pair::split : Pair::tiles;
+}
+
+}  // namespace fc

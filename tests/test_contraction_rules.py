@@ -1,0 +1,67 @@
+"""Which kernel runs a contraction, asked of the library's own rules on the CPU (a small program around
+the header that holds them), for the matrices that the planner gives each pass of a layer."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+import paper_1412_7580_amd as pkg
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+PASSES = {"fprop": pkg.FPROP, "bprop": pkg.BPROP, "accgrad": pkg.ACCGRAD}
+
+
+class Rules:
+    def __init__(self, path):
+        self._lib = ctypes.CDLL(path)
+
+    @staticmethod
+    def _matrix(pass_, S, f, fo, h, w, kh, kw):
+        d = pkg.describe_plan(PASSES[pass_], S, f, fo, h, w, kh, kw)
+        return (ctypes.c_long * 11)(d["M"], d["N"], d["K"], d["bins"], d["tile_log2"], d["a_rs"], d["a_cs"], d["b_rs"],
+                                    d["b_cs"], d["c_rs"], d["c_cs"])
+
+    def single(self, pass_, *layer, tile=-1):
+        """(kernel, gathers): kernel one of thin_k, thin_n, thin_acc, bin4, bf16, tile<shape>; gathers one of
+        fast, vec, scalar."""
+        out = (ctypes.c_int * 8)()
+        assert self._lib.rules_single(self._matrix(pass_, *layer), (ctypes.c_long * 2)(tile, 0), out) == 0
+        _, _, vec, fast, thin, bin4, bf16, shape = out
+        gathers = "fast" if fast else "vec" if vec else "scalar"
+        if thin:
+            return ("thin_k", "thin_n", "thin_acc")[thin - 1], gathers
+        return ("bin4" if bin4 else "bf16" if bf16 else f"tile{shape}"), gathers
+
+    def pair(self, *layer, no_pair=False):
+        got = self._lib.rules_pair(self._matrix("bprop", *layer), self._matrix("accgrad", *layer),
+                                   (ctypes.c_long * 2)(-1, no_pair))
+        return ("two launches", "tiles", "bf16")[got]
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    path = str(tmp_path_factory.mktemp("rules") / "rules.so")
+    subprocess.check_call([os.path.join(ROCM, "llvm", "bin", "clang++"), "-std=c++17", "-O1", "-fPIC", "-shared", "-x", "c++",
+                           "-D__HIP_PLATFORM_AMD__", "-I" + os.path.join(ROCM, "include"), "-Wno-unused-function",
+                           os.path.join(HERE, "contraction_rules", "rules.cpp"), "-o", path])
+    return Rules(path)
+
+
+def _layer(S, f, fo, h, k):
+    return S, f, fo, h, h, k, k
+
+
+def test_ordinary_layers(rules):
+    assert rules.single("fprop", *_layer(128, 64, 64, 27, 5)) == ("tile3", "fast")
+    assert rules.single("fprop", *_layer(128, 384, 384, 13, 3)) == ("bf16", "fast")
+    assert rules.single("fprop", *_layer(32, 128, 128, 64, 31)) == ("bin4", "fast")
+    assert rules.single("fprop", *_layer(128, 3, 96, 128, 11)) == ("thin_k", "scalar")
+    assert rules.single("accgrad", *_layer(128, 3, 96, 128, 11)) == ("thin_acc", "scalar")
+    assert rules.single("fprop", *_layer(8, 256, 256, 27, 5)) == ("tile6", "fast")
+    assert rules.single("bprop", *_layer(50, 37, 75, 30, 7)) == ("tile3", "scalar")
+    assert rules.pair(*_layer(128, 64, 64, 27, 5)) == "tiles"
+    assert rules.pair(*_layer(128, 384, 384, 13, 3)) == "bf16"
+    assert rules.pair(*_layer(128, 64, 64, 27, 5), no_pair=True) == "two launches"
+    assert rules.pair(*_layer(32, 128, 128, 64, 31)) == "two launches"
