@@ -683,7 +683,7 @@ hipError_t launch_cgemm_pair(const GemmProblem &g1, const GemmProblem &g2, Launc
     if (hipError_t e = prepare(g2.A, g2.B, g2.C, g2.layC, g2.C_rs, g2.C_cs, g2.M, g2.N, g2.K, g2.bins, sw, &q2); e != hipSuccess) return e;
     const Pair form = pair_form(q1, q2, sw);
     if (form == Pair::none) return hipErrorInvalidValue;
-    if (form == Pair::split) return launch_cgemm_split_pair(q1.prm, q1.akf, q2.prm, true, st);
+    if (form == Pair::split) return launch_cgemm_split_pair(q1.prm, q1.akf, q2.prm, st);
     GemmPairParams pp;
     pp.p1 = q1.prm; pp.p2 = q2.prm; pp.n1 = 0;
     if (q1.akf && q1.bkf) return pair_second<true, true>(q2, pp, st);

@@ -23,17 +23,15 @@
 #include "gemm_params.hpp"
 #include "bf16_split.hpp"
 
-#include <type_traits>
-
 namespace fc {
 
 constexpr unsigned kOutside = 0x80000000u;       // byte offset past every buffer range
 
 constexpr int ROWS = 64, TK = 16, KQ = TK / 4;
 
-// How an operand's tile is read.  Fast: see prepare().  Vec: 16-byte gathers along k with general
-// index arithmetic.  Scalar: 4-byte gathers, any strides and extents.
-enum : int { kFast = 0, kVec = 1, kScalar = 2 };
+// How an operand's tile is addressed.  Fast: see prepare().  General: any strides, and along the rows
+// any extents, by index arithmetic for each gather.
+enum : int { kFast = 0, kGeneral = 1 };
 
 // Loader of one operand tile (ROWS x TK) with the "row" index being m (or n) and the
 // reduction index k.  KF: k is the contiguous plane index, and a unit of work is four
@@ -94,7 +92,7 @@ struct SplitLoader {
 #pragma unroll
         for (int j = 0; j < 4; ++j) { re[j] = 0.f; im[j] = 0.f; }
         if (r >= R) return;
-        if constexpr (KF && MODE == kVec) {
+        if constexpr (KF) {
             if (kk < K) {                                 // K is a multiple of 4
                 const float *q = base + lay.index(r * rs + kk * cs, bin, 0);
                 const float4 a = *reinterpret_cast<const float4 *>(q), b = *reinterpret_cast<const float4 *>(q + im_off);
@@ -285,37 +283,27 @@ static long tile_grid(GemmParams &p) {
     return (long)p.bins * p.tiles_m * p.tiles_n;
 }
 
-// go(integral_constant mode)
-template <class F>
-static hipError_t with_mode(int mode, F &&go) {
-    if (mode == kFast) return go(std::integral_constant<int, kFast>{});
-    if (mode == kVec) return go(std::integral_constant<int, kVec>{});
-    return go(std::integral_constant<int, kScalar>{});
-}
-
 hipError_t launch_cgemm_split(GemmParams p, bool akf, bool bkf, bool vec, LaunchCtx st) {
     const long grid = tile_grid(p);
-    if (grid > 0x7fffffffL || (!akf && bkf)) return hipErrorInvalidValue;
-    return with_mode(p.fast ? kFast : vec ? kVec : kScalar, [&](auto md) {
-        constexpr int MODE = decltype(md)::value;
-        auto k = akf ? (bkf ? cgemm_split_kernel<true, true, MODE> : cgemm_split_kernel<true, false, MODE>)
-                     : cgemm_split_kernel<false, false, MODE>;
-        launch_kernel(k, dim3((unsigned)grid), dim3(256), 0, st, p);
-        return hipGetLastError();
-    });
+    // (4-byte gathers: along the rows of both operands only, see split_pays())
+    if (grid > 0x7fffffffL || (!akf && bkf) || (akf && !p.fast && !vec)) return hipErrorInvalidValue;
+    auto k = !akf ? (p.fast ? cgemm_split_kernel<false, false, kFast> : cgemm_split_kernel<false, false, kGeneral>)
+             : bkf ? (p.fast ? cgemm_split_kernel<true, true, kFast> : cgemm_split_kernel<true, true, kGeneral>)
+                   : (p.fast ? cgemm_split_kernel<true, false, kFast> : cgemm_split_kernel<true, false, kGeneral>);
+    launch_kernel(k, dim3((unsigned)grid), dim3(256), 0, st, p);
+    return hipGetLastError();
 }
 
-hipError_t launch_cgemm_split_pair(const GemmParams &p1, bool akf1, const GemmParams &p2, bool vec, LaunchCtx st) {
+// Both with 16-byte gathers (pair_form()).
+hipError_t launch_cgemm_split_pair(const GemmParams &p1, bool akf1, const GemmParams &p2, LaunchCtx st) {
     SplitPairParams pp{p1, p2, 0};
     const long n1 = tile_grid(pp.p1), n2 = tile_grid(pp.p2);
     if (n1 + n2 > 0x7fffffffL) return hipErrorInvalidValue;
     pp.n1 = (unsigned)n1;     // a multiple of the XCD count, as bins is
-    return with_mode(p1.fast && p2.fast ? kFast : vec ? kVec : kScalar, [&](auto md) {
-        constexpr int MODE = decltype(md)::value;
-        auto k = akf1 ? cgemm_split_pair_kernel<true, false, MODE> : cgemm_split_pair_kernel<false, true, MODE>;
-        launch_kernel(k, dim3((unsigned)(n1 + n2)), dim3(256), 0, st, pp);
-        return hipGetLastError();
-    });
+    auto k = p1.fast && p2.fast ? (akf1 ? cgemm_split_pair_kernel<true, false, kFast> : cgemm_split_pair_kernel<false, true, kFast>)
+                                : (akf1 ? cgemm_split_pair_kernel<true, false, kGeneral> : cgemm_split_pair_kernel<false, true, kGeneral>);
+    launch_kernel(k, dim3((unsigned)(n1 + n2)), dim3(256), 0, st, pp);
+    return hipGetLastError();
 }
 
 }  // namespace fc

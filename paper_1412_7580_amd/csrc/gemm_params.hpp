@@ -25,7 +25,7 @@ __device__ __forceinline__ float flip(float v, unsigned sign) {
 // Contractions on the bf16 matrix cores (cgemm_split.hip).  vec: 16-byte gathers are possible.  A pair is
 // bprop (A along the reduction) and accGrad (A along the rows), akf1 saying which comes first.
 hipError_t launch_cgemm_split(GemmParams prm, bool akf, bool bkf, bool vec, LaunchCtx st);
-hipError_t launch_cgemm_split_pair(const GemmParams &p1, bool akf1, const GemmParams &p2, bool vec, LaunchCtx st);
+hipError_t launch_cgemm_split_pair(const GemmParams &p1, bool akf1, const GemmParams &p2, LaunchCtx st);
 
 // Contractions with a side of at most four (cgemm_thin.hip), in one of three forms (thin_form()).
 enum class Thin { none, k, n, acc };

@@ -43,10 +43,13 @@ inline bool narrow_tile(const GemmParams &prm, bool vec) {
 // 16 the gathers do, and the bf16 form's power costs the transforms behind it clock: 26 (128 x 64 ->
 // 64, 27x27) 120 -> 114 on one card and 124 on another, 32 (56x56, padded) 305 -> 310; 43 (64 x 256 ->
 // 256, 28x28 / 32x32) 545 -> 504 / 717 -> 679, 45 (128 x 96 -> 256, 27x27) 456 -> 407.  Runs of four and
-// single planes are the gathers' alone (64 x 63 -> 129, 45x45: 491 -> 513), and
-// 4-byte gathers count as short runs (128 x 37 -> 65, 13x13: 80 either way).
-inline bool split_pays(const GemmParams &p, bool vec) {
-    if (p.layA.tsh < 3) return false;
+// single planes are the gathers' alone (64 x 63 -> 129, 45x45: 491 -> 513).
+// 4-byte gathers: where they run along the rows of both operands (accGrad) this loader is as good as the
+// fp32 kernel's and the products count (128 x 255 -> 255, 13x13 / 27x27: 103 -> 95, 430 -> 397; 130 x 123 ->
+// 127: 45 -> 41); along the reduction its four values a lane take four times the lines (fprop of the
+// same layers 111 -> 133, 412 -> 504, 53 -> 56, bprop 109 -> 113, 407 -> 429, 52 -> 52).
+inline bool split_pays(const GemmParams &p, bool akf, bool bkf, bool vec) {
+    if (p.layA.tsh < 3 || (!vec && (akf || bkf))) return false;
     const double m = p.M, n = p.N, k = p.K;
     return m * n * k >= (p.layA.tsh >= 5 && vec ? 12.0 : 40.0) * (m * k + k * n + m * n);
 }
@@ -112,7 +115,7 @@ inline hipError_t prepare(const GemmOperand &A, const GemmOperand &B, float *C, 
                     bins % (4 * kXcds) == 0 && (akf || A.rs == 1) && (bkf || B.cs == 1) && C_cs == 1 &&
                     C_rs % 4 == 0 && N % 4 == 0 && ((size_t)C & 15) == 0;
     out->thin = sw.no_thin ? Thin::none : thin_form(prm);
-    out->split = !out->bingroup && (akf || !bkf) && !sw.no_split && sw.tile < 0 && split_pays(prm, out->vec) && !narrow_tile(prm, out->vec);
+    out->split = !out->bingroup && (akf || !bkf) && !sw.no_split && sw.tile < 0 && split_pays(prm, akf, bkf, out->vec) && !narrow_tile(prm, out->vec);
     return hipSuccess;
 }
 
