@@ -48,10 +48,19 @@ inline bool narrow_tile(const GemmParams &prm, bool vec) {
 // fp32 kernel's and the products count (128 x 255 -> 255, 13x13 / 27x27: 103 -> 95, 430 -> 397; 130 x 123 ->
 // 127: 45 -> 41); along the reduction its four values a lane take four times the lines (fprop of the
 // same layers 111 -> 133, 412 -> 504, 53 -> 56, bprop 109 -> 113, 407 -> 429, 52 -> 52).
-inline bool split_pays(const GemmParams &p, bool akf, bool bkf, bool vec) {
-    if (p.layA.tsh < 3 || (!vec && (akf || bkf))) return false;
+// 16-byte gathers with general addressing (strides that are no multiple of a run): each gather's index
+// arithmetic adds to the cut's, so it takes more products: 17 .. 27 an element lose 2 .. 5 % (128 x 48 ->
+// 48, 10x10 .. 16x16), 36 win on runs of 32 (128 x 100 -> 100, 13x13: fprop 39.6 -> 37.4, bprop 41.2 -> 39.6) and
+// are even on 64, 56 win (128 x 196 -> 204, 27x27: 287 -> 249, 280 -> 269).  Not accGrad, whose
+// four gathers a lane all need it (325 -> 331; 64 x 300 -> 516, 20x20 278 -> 287).
+inline double products_per_element(const GemmParams &p) {
     const double m = p.M, n = p.N, k = p.K;
-    return m * n * k >= (p.layA.tsh >= 5 && vec ? 12.0 : 40.0) * (m * k + k * n + m * n);
+    return m * n * k / (m * k + k * n + m * n);
+}
+inline bool split_pays(const GemmParams &p, bool akf, bool bkf, bool vec) {
+    const int tsh = p.layA.tsh;
+    if (tsh < 3 || (vec ? !akf && !p.fast : akf || bkf)) return false;
+    return products_per_element(p) >= (p.fast && tsh >= 5 ? 12 : vec && tsh == 5 ? 30 : 40);
 }
 
 // The three forms, with A, B and C as the passes lay them out: rows of W planes side by side, the
@@ -133,7 +142,14 @@ enum class Pair { none, tiles, split };
 inline Pair pair_form(const Prepared &q1, const Prepared &q2, const GemmSwitches &sw) {
     if (sw.tile >= 0 || sw.no_pair) return Pair::none;       // A/B runs of single-kernel shapes
     if (!q1.vec || !q2.vec || q1.bingroup || q2.bingroup || q1.thin != Thin::none || q2.thin != Thin::none) return Pair::none;
-    return q1.split && q2.split && !q1.bkf && !q2.bkf && q1.akf != q2.akf ? Pair::split : Pair::tiles;
+    if (q1.bkf || q2.bkf || q1.akf == q2.akf) return Pair::tiles;
+    // Under general addressing the shared launch of the bf16 kernel wins on runs of 8 and 16 in spite of
+    // its accGrad (128 x 196 -> 204, 20x20 262 -> 256 us a backward pass, 32x32 621 -> 613), not on longer ones
+    // (8x8 61 -> 65, 13x13 even).
+    const Prepared &b = q1.akf ? q1 : q2, &a = q1.akf ? q2 : q1;
+    const bool accgrad = a.prm.fast ? a.split
+                                    : a.prm.layA.tsh < 5 && products_per_element(a.prm) >= 40 && !narrow_tile(a.prm, a.vec);
+    return b.split && accgrad ? Pair::split : Pair::tiles;
 }
 
 }  // namespace fc

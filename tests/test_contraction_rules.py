@@ -75,3 +75,18 @@ def test_4_byte_gathers_along_the_reduction_stay_in_fp32(rules, layer):
     assert rules.single("bprop", *_layer(*layer)) == ("tile3", "scalar")
     assert rules.single("accgrad", *_layer(*layer)) == ("bf16", "scalar")
     assert rules.pair(*_layer(*layer)) == "two launches"
+
+
+def test_general_addressing_takes_more_products(rules):
+    """Channel counts that are a multiple of 4 and not of a run: accGrad always, and layers of few
+    products an element, were slower in the bf16 kernel."""
+    for layer in ((128, 48, 48, 10, 3), (128, 40, 40, 13, 3), (256, 36, 36, 7, 3), (128, 32, 96, 7, 3), (64, 160, 160, 7, 3)):
+        for p in PASSES:
+            assert rules.single(p, *_layer(*layer)) == ("tile3", "vec"), (p, layer)
+        assert rules.pair(*_layer(*layer)) == "tiles"
+    for layer, pair in (((128, 100, 100, 13, 3), "tiles"), ((128, 196, 204, 7, 3), "tiles"), ((128, 196, 204, 27, 5), "bf16")):
+        assert rules.single("fprop", *_layer(*layer)) == ("bf16", "vec")
+        assert rules.single("bprop", *_layer(*layer)) == ("bf16", "vec")
+        assert rules.single("accgrad", *_layer(*layer)) == ("tile3", "vec")
+        assert rules.pair(*_layer(*layer)) == pair
+    assert rules.single("accgrad", *_layer(128, 32, 96, 10, 3)) == ("bf16", "fast")
