@@ -136,17 +136,43 @@ inline int pick_tile(const GemmSwitches &sw, const GemmParams &prm, bool vec) {
     return narrow_tile(prm, vec) ? (prm.M <= 32 ? 6 : 7) : 3;
 }
 
+// What a contraction loses, in us, as a part of the shared launch's 64x64 tiles against the kernel that
+// it has by itself: fits of the differences measured over 60 layers of 1, 4, 16 .. 384 channels.
+inline double lost_in_shared_tiles(const Prepared &q) {
+    const GemmParams &p = q.prm;
+    const double steps = (double)p.bins * p.K * ((p.M + 63) / 64) * ((p.N + 63) / 64);
+    if (q.thin == Thin::acc) return 0.041 * p.K > 1.9e-4 * steps ? 0.041 * p.K : 1.9e-4 * steps;
+    if (q.thin != Thin::none) return 3 + 5e-4 * steps;
+    return narrow_tile(p, q.vec) ? 1e-4 * steps : 0;
+}
+
+// bprop and accGrad of a layer with four or fewer channels on a side, or of one sample: two launches
+// for the products mean two for the inverse transforms, too (bases up to 32 have a shared one), and
+// neither product runs beside the other.  That costs 12 us and more with bprop's reduction: 16 samples,
+// 4 -> 16 channels, 13x13 15 us a backward pass in the shared launch against 30; 128 x 4 -> 384, 20x20 119 / 114, 128 x
+// 4 -> 128, 28x28 92 / 78.  With the thin side in bprop alone accGrad decides (256 x 64 -> 4, 32x32 91 /
+// 109; 256 x 384 -> 4, 20x20 194 / 172).  One sample: by the size of the gradient's spectrum (64 -> 128 channels,
+// 20x20, 58 MB 33 / 44; 256 -> 256, 115 MB 110 / 100).
+inline bool shared_launch_pays(const Prepared &b, const Prepared &a) {
+    if (b.thin == Thin::none && a.thin == Thin::none) return true;
+    if (a.prm.K == 1) return (double)a.prm.bins * a.prm.M * a.prm.N < 1.4e7;
+    const double lost = lost_in_shared_tiles(a);
+    return lost == 0 || lost + lost_in_shared_tiles(b) < 12 + 0.03 * b.prm.K;
+}
+
 // Two contractions in one launch: bprop and accGrad of a layer, which share operand A and neither of
 // which waits for the other.
 enum class Pair { none, tiles, split };
 inline Pair pair_form(const Prepared &q1, const Prepared &q2, const GemmSwitches &sw) {
     if (sw.tile >= 0 || sw.no_pair) return Pair::none;       // A/B runs of single-kernel shapes
-    if (!q1.vec || !q2.vec || q1.bingroup || q2.bingroup || q1.thin != Thin::none || q2.thin != Thin::none) return Pair::none;
+    if (!q1.vec || !q2.vec || q1.bingroup || q2.bingroup) return Pair::none;
+    const Prepared &b = q1.akf ? q1 : q2, &a = q1.akf ? q2 : q1;
+    if (!shared_launch_pays(b, a)) return Pair::none;
+    if (b.thin != Thin::none || a.thin != Thin::none) return Pair::tiles;
     if (q1.bkf || q2.bkf || q1.akf == q2.akf) return Pair::tiles;
     // Under general addressing the shared launch of the bf16 kernel wins on runs of 8 and 16 in spite of
     // its accGrad (128 x 196 -> 204, 20x20 262 -> 256 us a backward pass, 32x32 621 -> 613), not on longer ones
     // (8x8 61 -> 65, 13x13 even).
-    const Prepared &b = q1.akf ? q1 : q2, &a = q1.akf ? q2 : q1;
     const bool accgrad = a.prm.fast ? a.split
                                     : a.prm.layA.tsh < 5 && products_per_element(a.prm) >= 40 && !narrow_tile(a.prm, a.vec);
     return b.split && accgrad ? Pair::split : Pair::tiles;

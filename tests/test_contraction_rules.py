@@ -90,3 +90,19 @@ def test_general_addressing_takes_more_products(rules):
         assert rules.single("accgrad", *_layer(*layer)) == ("tile3", "vec")
         assert rules.pair(*_layer(*layer)) == pair
     assert rules.single("accgrad", *_layer(128, 32, 96, 10, 3)) == ("bf16", "fast")
+
+
+SHARED = {   # backward passes with a thin side: where the shared launch measured faster, and where two did
+    "tiles": [(16, 4, 16, 13, 3), (16, 4, 384, 28, 5), (128, 4, 64, 20, 3), (128, 4, 16, 28, 5), (64, 4, 128, 28, 5),
+              (128, 4, 384, 13, 3), (64, 4, 384, 20, 3), (256, 4, 384, 8, 3), (128, 4, 4, 13, 3), (64, 16, 4, 32, 5),
+              (256, 64, 4, 32, 5), (128, 64, 4, 112, 5), (16, 384, 4, 28, 5), (1, 64, 64, 13, 3), (1, 64, 128, 32, 5),
+              (1, 512, 512, 8, 3), (1, 256, 256, 13, 3), (1, 128, 256, 20, 3)],
+    "two launches": [(128, 4, 64, 28, 5), (128, 4, 128, 28, 5), (128, 4, 384, 20, 5), (256, 4, 128, 20, 5),
+                     (1024, 4, 16, 32, 5), (32, 4, 16, 224, 5), (128, 4, 4, 32, 5), (256, 384, 4, 20, 5),
+                     (1, 256, 256, 20, 3), (1, 512, 512, 13, 3), (1, 128, 256, 32, 5)],
+}
+
+
+@pytest.mark.parametrize("form,layer", [(f, l) for f, ls in SHARED.items() for l in ls], ids=lambda v: str(v).replace(" ", ""))
+def test_shared_launch_of_a_backward_pass_with_a_thin_side(rules, form, layer):
+    assert rules.pair(*_layer(*layer)) == form
