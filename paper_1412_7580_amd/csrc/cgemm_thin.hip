@@ -7,7 +7,7 @@
 // frequency tensors' contiguous direction), a lane works on four consecutive planes as one
 // 16-byte access a component, and the products are fp32 on the vector units.  Runs of the layout
 // longer than four put neighbouring quads of a run on neighbouring lanes.
-#include "gemm_params.hpp"
+#include "gemm_rules.hpp"
 
 namespace fc {
 
@@ -216,15 +216,12 @@ template <int W>
 static hipError_t run_thin(Thin form, const GemmParams &p, LaunchCtx st) {
     const int per_run = 1 << (p.layC.tsh - 2);                             // quads of a run
     if (form == Thin::k) {
-        // rows a lane walks over: up to 8 quads, fewer where that leaves fewer than 8192 waves
         const int groups = (p.N / 4 + per_run - 1) / per_run, bin_blocks = (p.bins * per_run + 255) / 256;
-        const int mquads = (p.M + 3) / 4;
-        long chunk = (long)mquads * groups * bin_blocks * 4 / 8192;
-        chunk = chunk < 1 ? 1 : chunk > 8 ? 8 : chunk;
+        const int mquads = (p.M + 3) / 4, chunk = thin_k_rows(p);
         const long regions = (long)bin_blocks * ((mquads + chunk - 1) / chunk);
         const long grid = (regions + kXcds - 1) / kXcds * kXcds * groups;
-        if (p.b_cs != 1 || W == 1) return launch_thin(cgemm_thin_k_kernel<W, true>, grid, 256, st, p, groups, bin_blocks, (int)chunk);
-        return launch_thin(cgemm_thin_k_kernel<W, false>, grid, 256, st, p, groups, bin_blocks, (int)chunk);
+        if (p.b_cs != 1 || W == 1) return launch_thin(cgemm_thin_k_kernel<W, true>, grid, 256, st, p, groups, bin_blocks, chunk);
+        return launch_thin(cgemm_thin_k_kernel<W, false>, grid, 256, st, p, groups, bin_blocks, chunk);
     }
     if (form == Thin::n) {
         const int bin_blocks = (p.bins + 63) / 64;

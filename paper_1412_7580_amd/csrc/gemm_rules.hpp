@@ -83,6 +83,16 @@ inline Thin thin_form(const GemmParams &p) {
     return Thin::none;
 }
 
+// Quads of rows that a lane of the k form walks over with its columns of B: the fewest, up to 8, that
+// leave 8192 waves or fewer (one a lane beyond that reads B anew for every quad it writes: 64 x 4 -> 384
+// channels, 28x28, 10752 waves 76.7 us a pass, with two 70.0; 128 x 4 -> 64, 56x56 86.5 -> 80.6).
+inline int thin_k_rows(const GemmParams &p) {
+    const int per_run = 1 << (p.layC.tsh - 2);                             // quads of a run
+    const long groups = (p.N / 4 + per_run - 1) / per_run, bin_blocks = (p.bins * per_run + 255) / 256;
+    const long rows = ((p.M + 3) / 4 * groups * bin_blocks * 4 + 8191) / 8192;
+    return rows < 1 ? 1 : rows > 8 ? 8 : (int)rows;
+}
+
 // Kernel parameters of one contraction and the kernel variant it can use.
 struct Prepared {
     GemmParams prm;

@@ -19,13 +19,15 @@ static GemmSwitches switches(const long *sw) {
 }
 
 extern "C" {
-// out: k contiguous in A, in B, 16-byte gathers, fast addressing, thin form, four-bin kernel, bf16 kernel, tile shape
+// out: k contiguous in A, in B, 16-byte gathers, fast addressing, thin form, four-bin kernel, bf16 kernel, tile shape,
+// quads of rows a lane of the thin k form walks over
 int rules_single(const long *v, const long *sw, int *out) {
     Prepared q;
     const GemmSwitches s = switches(sw);
     if (!problem(v, s, &q)) return -1;
     out[0] = q.akf; out[1] = q.bkf; out[2] = q.vec; out[3] = q.prm.fast;
     out[4] = (int)q.thin; out[5] = q.bingroup; out[6] = q.split; out[7] = pick_tile(s, q.prm, q.vec);
+    out[8] = q.thin == Thin::k ? thin_k_rows(q.prm) : 0;
     return 0;
 }
 // 0: two launches, 1: one launch of 64x64 tiles, 2: one launch of the bf16 kernel

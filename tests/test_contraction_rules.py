@@ -23,12 +23,18 @@ class Rules:
         return (ctypes.c_long * 11)(d["M"], d["N"], d["K"], d["bins"], d["tile_log2"], d["a_rs"], d["a_cs"], d["b_rs"],
                                     d["b_cs"], d["c_rs"], d["c_cs"])
 
+    def _ask(self, pass_, layer, tile):
+        out = (ctypes.c_int * 9)()
+        assert self._lib.rules_single(self._matrix(pass_, *layer), (ctypes.c_long * 2)(tile, 0), out) == 0
+        return list(out)
+
+    def rows(self, pass_, *layer):
+        return self._ask(pass_, layer, -1)[8]
+
     def single(self, pass_, *layer, tile=-1):
         """(kernel, gathers): kernel one of thin_k, thin_n, thin_acc, bin4, bf16, tile<shape>; gathers one of
         fast, vec, scalar."""
-        out = (ctypes.c_int * 8)()
-        assert self._lib.rules_single(self._matrix(pass_, *layer), (ctypes.c_long * 2)(tile, 0), out) == 0
-        _, _, vec, fast, thin, bin4, bf16, shape = out
+        _, _, vec, fast, thin, bin4, bf16, shape, _ = self._ask(pass_, layer, tile)
         gathers = "fast" if fast else "vec" if vec else "scalar"
         if thin:
             return ("thin_k", "thin_n", "thin_acc")[thin - 1], gathers
@@ -106,3 +112,12 @@ SHARED = {   # backward passes with a thin side: where the shared launch measure
 @pytest.mark.parametrize("form,layer", [(f, l) for f, ls in SHARED.items() for l in ls], ids=lambda v: str(v).replace(" ", ""))
 def test_shared_launch_of_a_backward_pass_with_a_thin_side(rules, form, layer):
     assert rules.pair(*_layer(*layer)) == form
+
+
+def test_rows_a_lane_of_a_thin_product(rules):
+    """As few as leave 8192 waves or fewer, 1 .. 8."""
+    assert rules.rows("fprop", *_layer(64, 4, 384, 28, 5)) == 2          # 10752 waves at one
+    assert rules.rows("fprop", *_layer(128, 4, 64, 56, 3)) == 2
+    assert rules.rows("fprop", *_layer(16, 4, 64, 28, 5)) == 1
+    assert rules.rows("fprop", *_layer(128, 3, 96, 128, 11)) == 8
+    assert rules.rows("bprop", *_layer(64, 384, 4, 32, 5)) == 2
