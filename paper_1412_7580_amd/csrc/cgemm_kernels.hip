@@ -601,7 +601,7 @@ static hipError_t launch_prepared(const Prepared &q, LaunchCtx st) {
     const GemmSwitches &sw = switches_of(st.sw);
     if (q.thin != Thin::none) return launch_cgemm_thin(prm, q.thin, st);
     if (q.bingroup) return launch_cgemm_bingroup(prm, q.akf, q.bkf, st);
-    if (q.split) return launch_cgemm_split(prm, q.akf, q.bkf, q.vec, st);
+    if (q.split_alone) return launch_cgemm_split(prm, q.akf, q.bkf, q.vec, st);
     const int shape = pick_tile(sw, prm, q.vec);
     if (q.vec && shape == 3 && sw.tile < 0 && !sw.no_tail) {
         // a short last round (at most a quarter of the resident workgroups): split its tiles

@@ -48,19 +48,22 @@ inline bool narrow_tile(const GemmParams &prm, bool vec) {
 // fp32 kernel's and the products count (128 x 255 -> 255, 13x13 / 27x27: 103 -> 95, 430 -> 397; 130 x 123 ->
 // 127: 45 -> 41); along the reduction its four values a lane take four times the lines (fprop of the
 // same layers 111 -> 133, 412 -> 504, 53 -> 56, bprop 109 -> 113, 407 -> 429, 52 -> 52).
-// 16-byte gathers with general addressing (strides that are no multiple of a run): each gather's index
-// arithmetic adds to the cut's, so it takes more products: 17 .. 27 an element lose 2 .. 5 % (128 x 48 ->
-// 48, 10x10 .. 16x16), 36 win on runs of 32 (128 x 100 -> 100, 13x13: fprop 39.6 -> 37.4, bprop 41.2 -> 39.6) and
-// are even on 64, 56 win (128 x 196 -> 204, 27x27: 287 -> 249, 280 -> 269).  Not accGrad, whose
-// four gathers a lane all need it (325 -> 331; 64 x 300 -> 516, 20x20 278 -> 287).
+// General addressing (16-byte gathers whose strides are no multiple of a run) follows the same rule: 128 x 100 ->
+// 100, 13x13 fprop 40.2 -> 35.9, bprop 41.0 -> 37.9, 128 x 196 -> 204, 27x27 277 -> 244, 277 -> 259 and accGrad 323 -> 313.
+inline long tiles_64(const GemmParams &p) { return (long)p.bins * ((p.M + 63) / 64) * ((p.N + 63) / 64); }
 inline double products_per_element(const GemmParams &p) {
     const double m = p.M, n = p.N, k = p.K;
     return m * n * k / (m * k + k * n + m * n);
 }
+// General addressing of accGrad leaves three workgroups a compute unit, not four: by itself it does not take grids
+// that the fp32 kernel holds in one round and this one would not (128 x 196 -> 204, 10x10 52 / 56).
+inline bool split_alone_pays(const GemmParams &p, bool akf, bool vec) {
+    return akf || p.fast || !vec || tiles_64(p) <= 3 * 256 || tiles_64(p) > 4 * 256;
+}
 inline bool split_pays(const GemmParams &p, bool akf, bool bkf, bool vec) {
     const int tsh = p.layA.tsh;
-    if (tsh < 3 || (vec ? !akf && !p.fast : akf || bkf)) return false;
-    return products_per_element(p) >= (p.fast && tsh >= 5 ? 12 : vec && tsh == 5 ? 30 : 40);
+    if (tsh < 3 || (!vec && (akf || bkf || p.a_rs != 1 || p.b_cs != 1))) return false;
+    return products_per_element(p) >= (tsh >= 5 && vec ? 12 : 40);
 }
 
 // The three forms, with A, B and C as the passes lay them out: rows of W planes side by side, the
@@ -83,6 +86,32 @@ inline Thin thin_form(const GemmParams &p) {
     return Thin::none;
 }
 
+// Whether a thin product is the faster one, where another kernel takes the same matrices.  fourbin: the
+// four-bins-per-line kernel would (16-byte gathers, runs of four planes); else it is 64x64 tiles.
+//   n: a workgroup walks over K for 64 bins and 16 rows, so few rows leave the chip idle: 16 samples, 4 -> 256
+//      channels, 40x40 51 us a pass in the four-bin kernel and 107 here, 128 x 4 -> 64, 56x56 101 and 92.  Against 64x64
+//      tiles with 4-byte gathers only long reductions in a single round of workgroups lose: 64 x 3 ->
+//      384, 40x40 191 and 204, 128 x 3 -> 384 328 and 267.
+//   k: four wide rows of B are as much to read as to write (64 x 4 -> 256, 56x56 82.6 / 88.4 at 32 samples,
+//      fewer rows or columns win: 16 samples, 64x64 91 / 82, 128 x 4 -> 64 equal).  Four columns on runs of 32
+//      or 64 planes leave most of each line unused (128 x 4 -> 4, 8x8 13.9 / 14.5, 13x13 16.0 / 16.6; 512 samples
+//      16.7 / 15.3, 20.2 / 17.5).
+//      One sample's gradient, K = 1: equal or ahead, but for results somewhat larger than the 256 MB
+//      last-level cache (256 -> 256, 40x40, 453 MB 216 / 233; 28 MB 39 / 37, 855 MB 428 / 401).
+//   acc: behind only for wide layers of the largest such basis (256 x 4 -> 256, 64x64 829 / 860).
+inline bool thin_pays(const GemmParams &p, Thin form, bool bkf, bool vec, bool fourbin) {
+    const double result = (double)p.bins * p.M * p.N;
+    if (form == Thin::n) {
+        const long workgroups = (p.bins + 63) / 64 * (((p.M + 3) / 4 + 3) / 4);
+        if (fourbin) return workgroups >= 128 && p.K <= 64;
+        return p.K <= 256 || (long)p.bins * ((p.M + 63) / 64) > 1024;
+    }
+    if (!fourbin) return form != Thin::k || !vec || p.layC.tsh < 5 || p.N > 4 || p.M >= 256;
+    if (form == Thin::k && p.K == 1) return result < 3.4e7 || result > 8e7;
+    if (form == Thin::k) return p.K < 4 || !bkf || p.M < 32 || p.N < 128 || result < 7e6;
+    return p.bins <= 2048 || p.M < 256 || p.K < 128;
+}
+
 // Quads of rows that a lane of the k form walks over with its columns of B: the fewest, up to 8, that
 // leave 8192 waves or fewer (one a lane beyond that reads B anew for every quad it writes: 64 x 4 -> 384
 // channels, 28x28, 10752 waves 76.7 us a pass, with two 70.0; 128 x 4 -> 64, 56x56 86.5 -> 80.6).
@@ -99,7 +128,8 @@ struct Prepared {
     bool akf, bkf;     // the reduction index is the contiguous plane index of A / B
     bool vec;          // 16-byte gathers are possible
     bool bingroup;     // the four-bins-per-line kernel applies
-    bool split;        // bound by the fp32 matrix cores: the bf16 kernel applies (cgemm_split.hip)
+    bool split;        // bound by the fp32 matrix cores: the bf16 kernel applies (cgemm_split.hip) ...
+    bool split_alone;  // ... and in a launch of its own, too
     Thin thin;         // a side of at most four: the vector-unit kernels apply (cgemm_thin.hip)
 };
 
@@ -133,8 +163,10 @@ inline hipError_t prepare(const GemmOperand &A, const GemmOperand &B, float *C, 
     out->bingroup = out->vec && !sw.no_bingroup && A.lay.tsh == 2 && B.lay.tsh == 2 && layC.tsh == 2 &&
                     bins % (4 * kXcds) == 0 && (akf || A.rs == 1) && (bkf || B.cs == 1) && C_cs == 1 &&
                     C_rs % 4 == 0 && N % 4 == 0 && ((size_t)C & 15) == 0;
-    out->thin = sw.no_thin ? Thin::none : thin_form(prm);
+    const Thin form = thin_form(prm);
+    out->thin = sw.no_thin || !thin_pays(prm, form, bkf, out->vec, out->bingroup) ? Thin::none : form;
     out->split = !out->bingroup && (akf || !bkf) && !sw.no_split && sw.tile < 0 && split_pays(prm, akf, bkf, out->vec) && !narrow_tile(prm, out->vec);
+    out->split_alone = out->split && split_alone_pays(prm, akf, out->vec);
     return hipSuccess;
 }
 
@@ -151,7 +183,10 @@ inline int pick_tile(const GemmSwitches &sw, const GemmParams &prm, bool vec) {
 inline double lost_in_shared_tiles(const Prepared &q) {
     const GemmParams &p = q.prm;
     const double steps = (double)p.bins * p.K * ((p.M + 63) / 64) * ((p.N + 63) / 64);
-    if (q.thin == Thin::acc) return 0.041 * p.K > 1.9e-4 * steps ? 0.041 * p.K : 1.9e-4 * steps;
+    if (q.thin == Thin::acc) {
+        const double chain = 0.041 * p.K, lost = chain > 1.9e-4 * steps ? chain : 1.9e-4 * steps;
+        return 4 * p.M < 1 << p.layA.tsh ? 0.3 * lost : lost;     // (few rows on a long run: a few lanes work)
+    }
     if (q.thin != Thin::none) return 3 + 5e-4 * steps;
     return narrow_tile(p, q.vec) ? 1e-4 * steps : 0;
 }
@@ -180,12 +215,10 @@ inline Pair pair_form(const Prepared &q1, const Prepared &q2, const GemmSwitches
     if (!shared_launch_pays(b, a)) return Pair::none;
     if (b.thin != Thin::none || a.thin != Thin::none) return Pair::tiles;
     if (q1.bkf || q2.bkf || q1.akf == q2.akf) return Pair::tiles;
-    // Under general addressing the shared launch of the bf16 kernel wins on runs of 8 and 16 in spite of
-    // its accGrad (128 x 196 -> 204, 20x20 262 -> 256 us a backward pass, 32x32 621 -> 613), not on longer ones
-    // (8x8 61 -> 65, 13x13 even).
-    const bool accgrad = a.prm.fast ? a.split
-                                    : a.prm.layA.tsh < 5 && products_per_element(a.prm) >= 40 && !narrow_tile(a.prm, a.vec);
-    return b.split && accgrad ? Pair::split : Pair::tiles;
+    if (!b.split || !a.split) return Pair::tiles;
+    // Under general addressing small grids are behind (128 x 48 -> 48, 7x7, 40 tiles 27.6 / 29.0; 128 x 32 -> 96, 80 28.5 /
+    // 29.6; 64 x 96 -> 96, 160 26.3 / 26.3; 64 x 32 -> 384, 240 53.0 / 51.3).
+    return a.prm.fast || tiles_64(a.prm) >= 100 ? Pair::split : Pair::tiles;
 }
 
 }  // namespace fc

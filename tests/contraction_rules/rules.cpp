@@ -26,7 +26,7 @@ int rules_single(const long *v, const long *sw, int *out) {
     const GemmSwitches s = switches(sw);
     if (!problem(v, s, &q)) return -1;
     out[0] = q.akf; out[1] = q.bkf; out[2] = q.vec; out[3] = q.prm.fast;
-    out[4] = (int)q.thin; out[5] = q.bingroup; out[6] = q.split; out[7] = pick_tile(s, q.prm, q.vec);
+    out[4] = (int)q.thin; out[5] = q.bingroup; out[6] = q.split_alone; out[7] = pick_tile(s, q.prm, q.vec);
     out[8] = q.thin == Thin::k ? thin_k_rows(q.prm) : 0;
     return 0;
 }

@@ -83,26 +83,27 @@ def test_4_byte_gathers_along_the_reduction_stay_in_fp32(rules, layer):
     assert rules.pair(*_layer(*layer)) == "two launches"
 
 
-def test_general_addressing_takes_more_products(rules):
-    """Channel counts that are a multiple of 4 and not of a run: accGrad always, and layers of few
-    products an element, were slower in the bf16 kernel."""
-    for layer in ((128, 48, 48, 10, 3), (128, 40, 40, 13, 3), (256, 36, 36, 7, 3), (128, 32, 96, 7, 3), (64, 160, 160, 7, 3)):
+def test_general_addressing(rules):
+    """Channel counts that are a multiple of 4 and not of a run: the bf16 kernel as under fast addressing,
+    but for accGrad's grids that only the fp32 kernel holds in one round and shared launches of few tiles."""
+    for layer, pair in (((128, 48, 48, 7, 3), "tiles"), ((128, 32, 96, 7, 3), "tiles"), ((64, 32, 384, 7, 3), "bf16"),
+                        ((128, 100, 100, 13, 3), "bf16"), ((128, 196, 204, 27, 5), "bf16")):
         for p in PASSES:
-            assert rules.single(p, *_layer(*layer)) == ("tile3", "vec"), (p, layer)
-        assert rules.pair(*_layer(*layer)) == "tiles"
-    for layer, pair in (((128, 100, 100, 13, 3), "tiles"), ((128, 196, 204, 7, 3), "tiles"), ((128, 196, 204, 27, 5), "bf16")):
-        assert rules.single("fprop", *_layer(*layer)) == ("bf16", "vec")
+            assert rules.single(p, *_layer(*layer)) == ("bf16", "vec"), (p, layer)
+        assert rules.pair(*_layer(*layer)) == pair
+    for layer in ((128, 196, 204, 10, 3), (16, 144, 144, 13, 3)):
         assert rules.single("bprop", *_layer(*layer)) == ("bf16", "vec")
         assert rules.single("accgrad", *_layer(*layer)) == ("tile3", "vec")
-        assert rules.pair(*_layer(*layer)) == pair
+        assert rules.pair(*_layer(*layer)) == "bf16"
     assert rules.single("accgrad", *_layer(128, 32, 96, 10, 3)) == ("bf16", "fast")
+    assert rules.single("fprop", *_layer(128, 100, 100, 27, 5)) == ("tile3", "vec")          # 36 products an element
 
 
 SHARED = {   # backward passes with a thin side: where the shared launch measured faster, and where two did
     "tiles": [(16, 4, 16, 13, 3), (16, 4, 384, 28, 5), (128, 4, 64, 20, 3), (128, 4, 16, 28, 5), (64, 4, 128, 28, 5),
               (128, 4, 384, 13, 3), (64, 4, 384, 20, 3), (256, 4, 384, 8, 3), (128, 4, 4, 13, 3), (64, 16, 4, 32, 5),
               (256, 64, 4, 32, 5), (128, 64, 4, 112, 5), (16, 384, 4, 28, 5), (1, 64, 64, 13, 3), (1, 64, 128, 32, 5),
-              (1, 512, 512, 8, 3), (1, 256, 256, 13, 3), (1, 128, 256, 20, 3)],
+              (1, 512, 512, 8, 3), (1, 256, 256, 13, 3), (1, 128, 256, 20, 3), (512, 4, 4, 8, 3), (512, 4, 4, 13, 3)],
     "two launches": [(128, 4, 64, 28, 5), (128, 4, 128, 28, 5), (128, 4, 384, 20, 5), (256, 4, 128, 20, 5),
                      (1024, 4, 16, 32, 5), (32, 4, 16, 224, 5), (128, 4, 4, 32, 5), (256, 384, 4, 20, 5),
                      (1, 256, 256, 20, 3), (1, 512, 512, 13, 3), (1, 128, 256, 32, 5)],
@@ -121,3 +122,25 @@ def test_rows_a_lane_of_a_thin_product(rules):
     assert rules.rows("fprop", *_layer(16, 4, 64, 28, 5)) == 1
     assert rules.rows("fprop", *_layer(128, 3, 96, 128, 11)) == 8
     assert rules.rows("bprop", *_layer(64, 384, 4, 32, 5)) == 2
+
+
+def test_thin_products_that_another_kernel_does_faster(rules):
+    """Few rows for the n form, wide layers of four channels for the k form, one sample's gradient about
+    the last-level cache's size, the widest layers at basis 64 for the acc form."""
+    for layer in ((4, 4, 8, 40, 5), (16, 4, 256, 40, 5), (32, 4, 16, 56, 7), (64, 4, 64, 40, 5), (128, 4, 256, 64, 5)):
+        assert rules.single("bprop", *_layer(*layer))[0] == "bin4", layer
+    for layer in ((128, 4, 64, 56, 5), (256, 4, 16, 64, 5), (8, 3, 64, 40, 5), (64, 3, 384, 56, 5), (128, 3, 384, 40, 5)):
+        assert rules.single("bprop", *_layer(*layer))[0] == "thin_n", layer
+    assert rules.single("bprop", *_layer(64, 3, 384, 40, 5)) == ("tile3", "scalar")
+    for layer in ((32, 4, 256, 56, 5), (64, 4, 256, 48, 5), (256, 4, 256, 40, 5)):
+        assert rules.single("fprop", *_layer(*layer))[0] == "bin4", layer
+    for layer in ((16, 4, 256, 64, 5), (128, 4, 64, 56, 5), (128, 4, 16, 40, 5), (128, 3, 384, 56, 5)):
+        assert rules.single("fprop", *_layer(*layer))[0] == "thin_k", layer
+    assert rules.single("bprop", *_layer(128, 256, 4, 56, 5))[0] == "thin_k"
+    assert rules.single("fprop", *_layer(128, 4, 4, 8, 3))[0] == "tile3"
+    assert rules.single("fprop", *_layer(128, 4, 4, 20, 3))[0] == "thin_k"
+    assert rules.single("fprop", *_layer(512, 4, 4, 8, 3))[0] == "thin_k"
+    for layer, kernel in (((1, 64, 64, 56, 3), "thin_k"), ((1, 128, 256, 56, 3), "bin4"), ((1, 256, 256, 40, 5), "bin4"),
+                          ((1, 256, 256, 56, 5), "thin_k"), ((1, 128, 129, 48, 5), "thin_k"), ((256, 4, 256, 64, 5), "bin4"),
+                          ((256, 4, 64, 64, 5), "thin_acc"), ((256, 4, 256, 56, 5), "thin_acc")):
+        assert rules.single("accgrad", *_layer(*layer))[0] == kernel, layer
