@@ -164,7 +164,7 @@ inline hipError_t prepare(const GemmOperand &A, const GemmOperand &B, float *C, 
                     bins % (4 * kXcds) == 0 && (akf || A.rs == 1) && (bkf || B.cs == 1) && C_cs == 1 &&
                     C_rs % 4 == 0 && N % 4 == 0 && ((size_t)C & 15) == 0;
     const Thin form = thin_form(prm);
-    out->thin = sw.no_thin || !thin_pays(prm, form, bkf, out->vec, out->bingroup) ? Thin::none : form;
+    out->thin = sw.no_thin || sw.tile >= 0 || !thin_pays(prm, form, bkf, out->vec, out->bingroup) ? Thin::none : form;
     out->split = !out->bingroup && (akf || !bkf) && !sw.no_split && sw.tile < 0 && split_pays(prm, akf, bkf, out->vec) && !narrow_tile(prm, out->vec);
     out->split_alone = out->split && split_alone_pays(prm, akf, out->vec);
     return hipSuccess;

@@ -10,10 +10,11 @@ namespace fc {
 // that one dispatch (their elapsed time is the kernel's own execution time, without the gaps
 // that events recorded between launches would include).
 // Switches of the contraction for A/B runs (environment variables FFTCONV_GEMM_TILE, _NO_TAIL,
-// _NO_PAIR, _NO_BINGROUP, _NO_FAST, _NO_THIN, _NO_SPLIT and FFTCONV_BG_TILE), read once when a handle is created; none
-// changes a result beyond rounding.  All off by default.
+// _NO_PAIR, _NO_BINGROUP, _NO_FAST, _NO_THIN, _NO_SPLIT and FFTCONV_BG_TILE), read once when a handle is
+// created; none changes a result beyond rounding.  All off by default.
 struct GemmSwitches {
-    int tile = -1;          // 0..5: another tile shape, single kernels only; -1: the default
+    int tile = -1;          // 0..7: this tile shape of the fp32 kernel, in launches of their own, for all
+                            // layers but those of the four-bins-per-line kernel; -1: the library's choice
     bool no_tail = false, no_pair = false, no_bingroup = false, no_fast = false, no_thin = false, no_split = false;
     int bg_tile = 0;        // per-wave tile of the four-bins-per-line kernel
 };

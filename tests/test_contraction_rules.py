@@ -144,3 +144,10 @@ def test_thin_products_that_another_kernel_does_faster(rules):
                           ((1, 256, 256, 56, 5), "thin_k"), ((1, 128, 129, 48, 5), "thin_k"), ((256, 4, 256, 64, 5), "bin4"),
                           ((256, 4, 64, 64, 5), "thin_acc"), ((256, 4, 256, 56, 5), "thin_acc")):
         assert rules.single("accgrad", *_layer(*layer))[0] == kernel, layer
+
+
+def test_a_named_tile_shape_takes_every_layer_of_the_fp32_kernel(rules):
+    for layer in ((128, 3, 96, 128, 11), (128, 384, 384, 13, 3), (8, 256, 256, 27, 5), (128, 64, 64, 27, 5)):
+        for p in PASSES:
+            for tile in (0, 3, 7):
+                assert rules.single(p, *_layer(*layer), tile=tile)[0] == f"tile{tile}", (p, layer)
