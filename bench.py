@@ -26,7 +26,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
-MFMA_FP32_PEAK_TFLOPS = 157.3  # MI355X dense fp32 matrix, published
+MFMA_PEAK_TFLOPS = {"fp32": 157.3, "bf16": 2500.0}   # MI355X dense matrix, published
 
 STAGES = ("fft", "contraction", "ifft")   # kernels of one pass, in launch order
 
@@ -74,12 +74,25 @@ def stage_model(cfg, pass_name):
         "fft": {"bytes": fwd(A) + fwd(B)},
         "fft_a": {"bytes": fwd(A)},
         "fft_b": {"bytes": fwd(B)},
-        # executed real flops: three real multiply-adds per complex one (Gauss's 3-multiplication
-        # product), i.e. 6 M N K per bin; a plain 4-multiplication product would execute 8 M N K
-        "contraction": {"flops": 6 * M * Nn * K * bins,
-                        "bytes": 8 * bins * (A[0] + B[0] + C[0])},
+        "contraction": contraction_model(M, Nn, K, N, bins, A[0] + B[0] + C[0]),
         "ifft": {"bytes": C[0] * (8 * bins + 4 * C[1] * C[2])},
     }
+
+
+def on_bf16_cores(M, Nn, K, N):
+    """Whether the contraction of a layer whose channel counts are multiples of 64 runs on the bf16 matrix
+    cores (the library's rule for such layers: products per operand element, by the layout's runs)."""
+    if N > 32 or min(M, Nn) <= 32 <= K and max(M, Nn) >= 128:
+        return False
+    return M * Nn * K >= (12 if N <= 16 else 40) * (M * K + K * Nn + M * Nn)
+
+
+def contraction_model(M, Nn, K, N, bins, planes):
+    """Executed real flops per bin and the unit they run on: on the fp32 matrix cores three real
+    multiply-adds per complex one (Gauss's 3-multiplication product), 6 M N K; on the bf16 ones
+    four, each of six bf16 products, 48 M N K."""
+    unit = "bf16" if on_bf16_cores(M, Nn, K, N) else "fp32"
+    return {"flops": (48 if unit == "bf16" else 6) * M * Nn * K * bins, "unit": unit, "bytes": 8 * bins * planes}
 
 
 def direct_flops(cfg):
@@ -584,8 +597,10 @@ def kernel_model(cfg, name):
         if st == "contraction":
             # GYF is an operand of both problems: counted once (the launch can read it once)
             gyf = 8 * cfg["N"] * (cfg["N"] // 2 + 1) * cfg["S"] * cfg["fo"]
-            return {"bytes": mb["contraction"]["bytes"] + ma["contraction"]["bytes"] - gyf,
-                    "flops": mb["contraction"]["flops"] + ma["contraction"]["flops"]}
+            cb, ca = mb["contraction"], ma["contraction"]
+            if cb["unit"] != ca["unit"]:            # the shared launch takes one kernel for both: fp32
+                cb, ca = ({**m, "unit": "fp32", "flops": m["flops"] // (8 if m["unit"] == "bf16" else 1)} for m in (cb, ca))
+            return {"bytes": cb["bytes"] + ca["bytes"] - gyf, "flops": cb["flops"] + ca["flops"], "unit": cb["unit"]}
         if st == "ifft":
             return {"bytes": mb["ifft"]["bytes"] + ma["ifft"]["bytes"]}
         return mb["fft_a"]                          # tiled layers: gy cut a second time
@@ -594,16 +609,18 @@ def kernel_model(cfg, name):
 
 def roofline_entry(ms, model):
     """Roofline of one kernel: the bound is the roofline that allows the least (HBM for the
-    transforms; for a contraction whichever of executed flops / 157.3 TFLOP/s and algorithmic
-    bytes / 8 TB/s takes longer); frac = that least time over the measured time."""
+    transforms; for a contraction whichever of executed flops / the peak of the matrix cores
+    they run on and algorithmic bytes / 8 TB/s takes longer); frac = that least time over the measured time."""
     ent = {"ms": round(ms, 5), "GBps": round(model["bytes"] / ms / 1e6, 1),
            "frac_hbm": round(model["bytes"] / ms / 1e6 / HBM_PEAK_GBS, 4)}
     t_hbm = model["bytes"] / (HBM_PEAK_GBS * 1e9)
     bound = "hbm"
     if "flops" in model:
+        peak = MFMA_PEAK_TFLOPS[model["unit"]]
         ent["TFLOPs"] = round(model["flops"] / ms / 1e9, 2)
-        ent["frac_mfma"] = round(model["flops"] / ms / 1e9 / MFMA_FP32_PEAK_TFLOPS, 4)
-        if model["flops"] / (MFMA_FP32_PEAK_TFLOPS * 1e12) > t_hbm:
+        ent["mfma"] = model["unit"]
+        ent["frac_mfma"] = round(model["flops"] / ms / 1e9 / peak, 4)
+        if model["flops"] / (peak * 1e12) > t_hbm:
             bound = "mfma"
     ent["bound"] = bound
     ent["frac"] = ent["frac_mfma"] if bound == "mfma" else ent["frac_hbm"]
@@ -787,7 +804,7 @@ def main():
         "kernel": f"{dom} ({KERNEL_FUNCTIONS.get(dom.split('.')[1], 'fft2d_r2c_multi_kernel')})",
         "bound": d["bound"],
         "achieved": d["TFLOPs"] if d["bound"] == "mfma" else d["GBps"],
-        "peak": MFMA_FP32_PEAK_TFLOPS if d["bound"] == "mfma" else HBM_PEAK_GBS,
+        "peak": MFMA_PEAK_TFLOPS[d["mfma"]] if d["bound"] == "mfma" else HBM_PEAK_GBS,
         "unit": "TFLOP/s" if d["bound"] == "mfma" else "GB/s",
         "frac": d["frac"],
         "traffic": None if traffic is None else round(traffic),
@@ -796,7 +813,8 @@ def main():
         "algorithmic_bytes": model["bytes"],
         "avg_launch_ms": d["ms"], "launches_averaged": prof_steps,
         "note": "per-kernel times: HIP event pair attached to each dispatch on the library's stream; "
-                "contraction flops are the executed ones, 6 M N K per bin (3-multiplication complex product)",
+                "contraction flops are the executed ones: 6 M N K per bin on the fp32 matrix cores (3-multiplication "
+                "complex product), 48 M N K on the bf16 ones (four real products of six bf16 products each)",
         "stages": stages,
     }
     if "flops" in model:

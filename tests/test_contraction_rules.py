@@ -1,6 +1,7 @@
 """Which kernel runs a contraction, asked of the library's own rules on the CPU (a small program around
 the header that holds them), for the matrices that the planner gives each pass of a layer."""
 import ctypes
+import importlib.util
 import os
 import subprocess
 
@@ -18,8 +19,8 @@ class Rules:
         self._lib = ctypes.CDLL(path)
 
     @staticmethod
-    def _matrix(pass_, S, f, fo, h, w, kh, kw):
-        d = pkg.describe_plan(PASSES[pass_], S, f, fo, h, w, kh, kw)
+    def _matrix(pass_, S, f, fo, h, w, kh, kw, basis=-1):
+        d = pkg.describe_plan(PASSES[pass_], S, f, fo, h, w, kh, kw, basis)
         return (ctypes.c_long * 11)(d["M"], d["N"], d["K"], d["bins"], d["tile_log2"], d["a_rs"], d["a_cs"], d["b_rs"],
                                     d["b_cs"], d["c_rs"], d["c_cs"])
 
@@ -151,3 +152,31 @@ def test_a_named_tile_shape_takes_every_layer_of_the_fp32_kernel(rules):
         for p in PASSES:
             for tile in (0, 3, 7):
                 assert rules.single(p, *_layer(*layer), tile=tile)[0] == f"tile{tile}", (p, layer)
+
+
+def test_the_benchmark_counts_the_products_of_the_kernel_that_runs(rules):
+    spec = importlib.util.spec_from_file_location("bench", os.path.join(os.path.dirname(HERE), "bench.py"))
+    bench = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(bench)
+    from paper_1412_7580_amd import synth
+    units = {}
+    for name in ("C2", "C3", "C4"):
+        cfg = synth.CONV_CONFIGS[name]
+        layer = tuple(cfg[k] for k in ("S", "f", "fo", "h", "w", "kh", "kw"))
+        for basis in (cfg["N"], -1):
+            used = dict(cfg, N=cfg["N"] if basis > 0 else bench.library_basis(cfg))
+            for p in PASSES:
+                model = bench.stage_model(used, p)["contraction"]
+                bf16 = rules.single(p, *layer, basis)[0] == "bf16"
+                assert model["unit"] == ("bf16" if bf16 else "fp32"), (name, p, basis)
+                units.setdefault(name, set()).add(model["unit"])
+                M, Nn, K = {"fprop": (cfg["S"], cfg["fo"], cfg["f"]), "bprop": (cfg["S"], cfg["f"], cfg["fo"]),
+                            "accgrad": (cfg["fo"], cfg["f"], cfg["S"])}[p]
+                bins = used["N"] * (used["N"] // 2 + 1)
+                assert model["flops"] == (48 if bf16 else 6) * M * Nn * K * bins
+            if name != "C4":
+                shared = bench.kernel_model(used, "backward.contraction")
+                assert rules.pair(*layer, basis) == {"bf16": "bf16", "fp32": "tiles"}[shared["unit"]]
+                ent = bench.roofline_entry(0.2, shared)
+                assert ent["frac_mfma"] == round(shared["flops"] / 0.2e-3 / 1e12 / bench.MFMA_PEAK_TFLOPS[shared["unit"]], 4)
+    assert units == {"C2": {"fp32"}, "C3": {"bf16"}, "C4": {"fp32"}}
