@@ -47,6 +47,13 @@ class Rules:
         return ("two launches", "tiles", "bf16")[got]
 
 
+def _module(path):
+    spec = importlib.util.spec_from_file_location(os.path.basename(path)[:-3], path)
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    return mod
+
+
 @pytest.fixture(scope="module")
 def rules(tmp_path_factory):
     path = str(tmp_path_factory.mktemp("rules") / "rules.so")
@@ -155,9 +162,7 @@ def test_a_named_tile_shape_takes_every_layer_of_the_fp32_kernel(rules):
 
 
 def test_the_benchmark_counts_the_products_of_the_kernel_that_runs(rules):
-    spec = importlib.util.spec_from_file_location("bench", os.path.join(os.path.dirname(HERE), "bench.py"))
-    bench = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(bench)
+    bench = _module(os.path.join(os.path.dirname(HERE), "bench.py"))
     from paper_1412_7580_amd import synth
     units = {}
     for name in ("C2", "C3", "C4"):
@@ -180,3 +185,46 @@ def test_the_benchmark_counts_the_products_of_the_kernel_that_runs(rules):
                 ent = bench.roofline_entry(0.2, shared)
                 assert ent["frac_mfma"] == round(shared["flops"] / 0.2e-3 / 1e12 / bench.MFMA_PEAK_TFLOPS[shared["unit"]], 4)
     assert units == {"C2": {"fp32"}, "C3": {"bf16"}, "C4": {"fp32"}}
+
+
+def test_the_gpu_test_reaches_every_kernel(rules):
+    """Every kernel that a contraction can take, with every kind of gather and operand order it is built
+    for, with rows, columns and reduction that leave a remainder, on short and on long runs."""
+    gpu = _module(os.path.join(HERE, "test_gpu_contraction.py"))
+    params = lambda test: next(m.args[1] for m in test.pytestmark if m.name == "parametrize" and m.args[0] == "S,f,fo")
+    layers = [(S, f, fo, h, h, 3, 2) for S, f, fo, h in gpu.EDGES]
+    layers += [(*c, h, h, 3, 3) for c in params(gpu.test_thin_sides) for h in gpu.SIDES.values()]
+    layers += [(*c, h, h, 3, 2) for c in params(gpu.test_tile_edges) for h in (8, 13, 20, 32)]
+    got, ragged, pairs, walks = set(), set(), set(), set()
+    for layer in layers:
+        for p in PASSES:
+            d = pkg.describe_plan(PASSES[p], *layer)
+            kernel, gathers = rules.single(p, *layer)
+            runs = "long" if d["tile_log2"] >= 5 else "short"
+            got.add((kernel, gathers, p, runs))
+            tm, tn = {"tile6": (32, 128), "tile7": (128, 32)}.get(kernel, (64, 64))
+            for side, v in (("M", d["M"] % tm), ("N", d["N"] % tn), ("K", d["K"] % 16)):
+                if v:
+                    ragged.add((kernel, side))
+            if kernel == "thin_k":
+                walks.add((p, rules.rows(p, *layer) > 1, min(d["K"], 4)))
+        pairs.add((rules.pair(*layer), rules.single("bprop", *layer)[1],
+                   rules.single("accgrad", *layer)[0].startswith("thin") or rules.single("bprop", *layer)[0].startswith("thin")))
+    missing = []
+    for p in PASSES:
+        for runs in ("long", "short"):
+            missing += [k for k in (("bf16", "fast", p, runs), ("tile3", "fast", p, runs), ("tile3", "vec", p, runs),
+                                    ("tile3", "scalar", p, runs)) if k not in got]
+        for g in ("fast", "vec"):
+            missing += [("narrow", g, p)] * (not any((t, g, p, r) in got for t in ("tile6", "tile7") for r in ("long", "short")))
+        missing += [("bin4", p)] * (("bin4", "fast", p, "short") not in got)
+        missing += [("bf16", "vec", p)] * (("bf16", "vec", p, "long") not in got or ("bf16", "vec", p, "short") not in got)
+    missing += [("bf16", "scalar", r) for r in ("long", "short") if ("bf16", "scalar", "accgrad", r) not in got]
+    missing += [(t, g) for t in ("tile6", "tile7") for g in ("fast", "vec") if not any(k[:2] == (t, g) for k in got)]
+    missing += [(k, s) for k in ("tile3", "tile6", "tile7", "bf16") for s in "MNK" if (k, s) not in ragged]
+    missing += [t for t in ("thin_n", "thin_acc") if not any(k[0] == t for k in got)]
+    missing += [w for w in (("fprop", True, 3), ("bprop", True, 3), ("fprop", False, 4), ("bprop", False, 4), ("bprop", False, 1),
+                            ("accgrad", False, 1)) if w not in walks]
+    missing += [q for q in (("bf16", "fast", False), ("bf16", "vec", False), ("tiles", "fast", False), ("tiles", "vec", False),
+                            ("tiles", "vec", True), ("two launches", "scalar", True)) if q not in pairs]
+    assert not missing, missing

@@ -1,10 +1,12 @@
 """The per-bin contraction at the edges of its kernels (GPU, C ABI): sides around the matrix-core
 tiles (32, 64, 128) and K tile (16), and the vector-unit kernels for sides of 1 .. 4, on layouts with
-runs of 4, 8, 16, 32 and 64 planes.
+runs of 4, 8, 16, 32 and 64 planes.  tests/test_contraction_rules.py checks on the CPU that these layers reach
+every kernel, kind of gather and remainder.
 
 Reference: the convolution in fp64 (torch, CPU).  Bound on max|err| / max|ref|: the transforms
-make about 12 roundings of 2^-24 a value and the sum one per 16 terms, at most 64 here, each against
-the largest partial sum; 4e-6 is 67 such roundings, all in one direction."""
+make about 12 roundings of 2^-24 a value and the sum one per 2 terms (fp32) or 5 (bf16, three per 16),
+80 at most here, each against the largest partial sum and of either sign; 4e-6 is 67 roundings in one
+direction, seven times the root of 92."""
 import numpy as np
 import pytest
 
@@ -70,6 +72,24 @@ def test_thin_sides_tiled(hd, S, f, fo, side, gx):
 @pytest.mark.parametrize("S,f,fo", [(8, 64, 128), (31, 16, 64), (32, 32, 32), (33, 48, 160), (64, 64, 64), (65, 17, 33),
                                     (129, 5, 31), (16, 63, 129), (7, 20, 68)])
 def test_tile_edges(hd, S, f, fo, side):
+    _check(hd, S, f, fo, side, side, 3, 2)
+
+
+# Layers that reach what the ones above do not.  (S, f, fo, image side)
+EDGES = [
+    (257, 48, 32, 13), (129, 48, 32, 20), (129, 36, 20, 20), (130, 20, 36, 20), (33, 20, 132, 20),      # 128x32
+    (31, 48, 144, 20), (31, 144, 48, 20), (40, 144, 32, 20), (5, 36, 132, 20), (7, 132, 36, 20), (33, 132, 20, 20),  # 32x128
+    (33, 64, 128, 8), (65, 64, 64, 8), (70, 96, 160, 13), (33, 32, 64, 13),                             # bf16, fast addressing
+    (130, 128, 144, 20), (130, 120, 136, 32), (100, 120, 136, 32),
+    (65, 36, 44, 13), (70, 100, 68, 8), (130, 124, 132, 20), (129, 124, 132, 32), (20, 68, 132, 13),    # bf16, general
+    (130, 123, 127, 13), (130, 123, 127, 20), (131, 125, 129, 8),                                       # bf16, 4-byte gathers
+    (160, 4, 8, 40), (90, 3, 96, 40), (90, 96, 3, 40), (260, 4, 4, 8), (20, 4, 12, 20), (12, 40, 4, 13),  # thin sides
+    (1, 36, 44, 20), (1, 64, 64, 40), (33, 64, 64, 40),
+]
+
+
+@pytest.mark.parametrize("S,f,fo,side", EDGES)
+def test_edges_of_every_kernel(hd, S, f, fo, side):
     _check(hd, S, f, fo, side, side, 3, 2)
 
 
