@@ -44,11 +44,12 @@ __device__ __forceinline__ size_t element(const FreqLayout &lay, unsigned plane,
 // consecutive k of one row, as one 16-byte gather; else the row index is contiguous, lanes run
 // along the rows and a unit is four 4-byte gathers (as many cache lines a byte as wider loads
 // would touch, and the four k that one LDS word pair holds meet in one lane).
-// LDS image: [6 = (re, im) x (h, m, l)][k / 4][row] of four bf16; RP rows a plane, so that both
-// kinds of unit store, and the fragments load, without bank conflicts.
+// LDS image: [6 = (re, im) x (h, m, l)][k / 8][row][k % 8] of bf16: a fragment is one 16-byte load at a
+// constant offset from the lane's address (8-byte pieces by k / 4 cost an address each, 11 of 159 vector
+// instructions a K tile), and both kinds of unit store 8 bytes of it without bank conflicts.
 template <bool KF, int MODE>
 struct SplitLoader {
-    static constexpr int RP = ROWS + 8, PLANE = KQ * RP * 8, BYTES = 6 * PLANE;
+    static constexpr int OCTET = ROWS * 16, PLANE = TK / 8 * OCTET, BYTES = 6 * PLANE;
     float re[4], im[4];
     unsigned off;        // byte offset of this lane's unit from the tile's base, which is uniform
 
@@ -118,7 +119,8 @@ struct SplitLoader {
 
     // Terms of the staged values, times `scale`, into the LDS image; `sign` conjugates.
     __device__ __forceinline__ void store(char *img, float scale, unsigned sign, int tid) const {
-        char *q = img + (kq_of(tid) * RP + row_of(tid)) * 8;
+        const int kq = kq_of(tid);
+        char *q = img + (kq >> 1) * OCTET + row_of(tid) * 16 + (kq & 1) * 8;
         uint2 h, m, l;
         split4(scale * re[0], scale * re[1], scale * re[2], scale * re[3], h, m, l);
         *reinterpret_cast<uint2 *>(q) = h;
@@ -133,9 +135,7 @@ struct SplitLoader {
 
     // MFMA fragment of plane c: lane half lk holds k 8 lk .. 8 lk + 7.
     static __device__ __forceinline__ bf16x8 fragment(const char *img, int c, int row, int lk) {
-        const char *q = img + c * PLANE + (2 * lk * RP + row) * 8;
-        const uint2 a = *reinterpret_cast<const uint2 *>(q), b = *reinterpret_cast<const uint2 *>(q + RP * 8);
-        return __builtin_bit_cast(bf16x8, make_uint4(a.x, a.y, b.x, b.y));
+        return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(img + c * PLANE + lk * OCTET + row * 16));
     }
 };
 
