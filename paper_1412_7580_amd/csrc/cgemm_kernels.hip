@@ -31,9 +31,6 @@ __device__ __forceinline__ void static_for_gemm(F &&f) {
     }
 }
 
-
-
-
 // Loader of one operand tile (ROWS x TK) with the "row" index being m (or n) and the
 // reduction index k.  KF: k is the contiguous plane index (else the row index is).
 // VEC: 16-byte gathers (needs plane runs of >= 4, aligned starts and extents).
@@ -538,8 +535,9 @@ static hipError_t run_gemm(GemmParams prm, LaunchCtx st) {
 }
 
 // Tile shapes (M x N on four waves): 0 128x128, 1 64x128, 2 128x64, 3 64x64; 4 and 5 are 64x64
-// with 2 and 4 tiles of register staging ahead.  6 and 7 are 32x128 and 128x32.  3 is the
-// default, 6 and 7 serve narrow sides (narrow_tile), the others are kept for A/B runs.  1-, 2- and 8-wave workgroups and TK = 8 / 32 were also measured; none beat 3.
+// with 2 and 4 tiles of register staging ahead, 6 and 7 are 32x128 and 128x32.  3 is the default,
+// 6 and 7 serve narrow sides (narrow_tile), the others are kept for A/B runs.  1-, 2- and 8-wave
+// workgroups and TK = 8 / 32 were also measured; none beat 3.
 template <bool AKF, bool BKF, bool VEC>
 static hipError_t dispatch_tile(int shape, GemmParams prm, LaunchCtx st) {
     switch (shape) {

@@ -4,11 +4,11 @@
 // Same operation as cgemm_kernels.hip (the Cgemm row of Table 1 of the fbfft paper), same layout,
 // same order of workgroups.  Every fp32 operand value is cut, without loss, into three bf16 terms
 // (x = h + m + l: each is the rounded value of what the ones before it leave, and 8 + 8 + 8 bits
-// hold the whole significand; bf16_split.hpp has the range and what widens it to all of fp32), and a
-// real product is the six bf16 products hh, hm, mh, mm, hl,
-// lh, which are exact and are summed in fp32 by v_mfma_f32_32x32x16_bf16.  What is left out (ml,
-// lm, ll) is at most 2^-23 of |a b| and of either sign, 2^-26 on average: below the rounding of the
-// fp32 sum itself.  The fp32 MFMA does 2 of K in 64 cycles, the six products do 16 of K in 192.
+// hold the whole significand; bf16_split.hpp has the range and what widens it to all of fp32), and
+// a real product is the six bf16 products hh, hm, mh, mm, hl, lh, which are exact and are summed in
+// fp32 by v_mfma_f32_32x32x16_bf16.  What is left out (ml, lm, ll) is at most 2^-23 of |a b| and of
+// either sign, 2^-26 on average: below the rounding of the fp32 sum itself.  The fp32 MFMA does 2 of
+// K in 64 cycles, the six products do 16 of K in 192.
 //     Cr += Ar Br - Ai Bi,   Ci += Ar Bi + Ai Br      (four real products, no cancellation)
 // Relative 2-norm error of the passes against 64 bits, three-product fp32 form -> this: 128 samples,
 // 384 -> 384 channels, 13x13: 4.5e-7 / 4.9e-7 / 2.9e-7 -> 2.1e-7 / 2.3e-7 / 1.8e-7.
@@ -16,10 +16,12 @@
 // Workgroup = 4 waves, a 64x64 tile, each wave one MFMA tile of 32x32 (re and im accumulators).  K is
 // walked in tiles of 16 through one LDS image of both operands, cut on the way from the staging
 // registers; the next tile's global loads are in flight while the current one is multiplied, and
-// the barriers around the image are covered by the compute unit's other workgroups (four, at 128
-// registers: a build that spilled to stay there was 10 % slower on the backward pair).  128x64
-// tiles and two tiles of staging measured no faster, K tiles of 32 slower.  That layer's training
-// step 485 -> 433 us; 128 x 256 -> 256 240 -> 219, 128 x 192 -> 192 163 -> 144, 8x8 images, 256 x 128 -> 128 88 -> 74.
+// the barriers around the image are covered by the compute unit's other workgroups: four at 128
+// registers under fast addressing (a build that spilled to stay there was 10 % slower on the
+// backward pair), three or four under general.  The matrix cores are 55 .. 62 % busy, and the vector
+// units with the cuts beside them about half the cycles.  128x64 tiles and two tiles of staging
+// measured no faster, K tiles of 32 slower.  That layer's training step 485 -> 422 .. 440 us by the card;
+// 128 x 256 -> 256 240 -> 219, 128 x 192 -> 192 163 -> 144, 8x8 images, 256 x 128 -> 128 88 -> 74.
 #include "gemm_params.hpp"
 #include "bf16_split.hpp"
 
@@ -46,7 +48,8 @@ __device__ __forceinline__ size_t element(const FreqLayout &lay, unsigned plane,
 // would touch, and the four k that one LDS word pair holds meet in one lane).
 // LDS image: [6 = (re, im) x (h, m, l)][k / 8][row][k % 8] of bf16: a fragment is one 16-byte load at a
 // constant offset from the lane's address (8-byte pieces by k / 4 cost an address each, 11 of 159 vector
-// instructions a K tile), and both kinds of unit store 8 bytes of it without bank conflicts.
+// instructions a K tile), and both kinds of unit store 8 bytes of it.  Octets padded so that the stores
+// along k do not meet in the banks (48 cycles a wave and K tile) measured no different.
 template <bool KF, int MODE>
 struct SplitLoader {
     static constexpr int OCTET = ROWS * 16, PLANE = TK / 8 * OCTET, BYTES = 6 * PLANE;

@@ -66,10 +66,10 @@ __device__ __forceinline__ Lane lane_of(unsigned u, int tsh) {
 
 // K of at most four (fprop of a layer with few input channels, bprop of one with few output
 // channels): C(m, n) = sum_k A(m, k) B(k, n).  A lane holds four columns of B and walks over
-// `chunk` quads of rows, writing one quad of C a row.  Bound by the writes of C: 1632 bins of 1152 x
-// 96 x 3 (first layer, 128x128 images on basis 56, 1.44 GB of C) 980 -> 325 us against the matrix-core
-// kernel, whose 4-byte gathers and stores of runs of four fill a quarter of their lines.  Workgroups of one (bins, rows) region, which share A, are numbered so
-// that they run on one XCD.
+// `chunk` quads of rows, writing one quad of C a row.  Bound by the writes of C: 1632 bins of
+// 1152 x 96 x 3 (first layer, 128x128 images on basis 56, 1.44 GB of C) 980 -> 325 us against the
+// matrix-core kernel, whose 4-byte gathers and stores of runs of four fill a quarter of their lines.
+// Workgroups of one (bins, rows) region, which share A, are numbered so that they run on one XCD.
 template <int K, bool BKF>
 __global__ void __launch_bounds__(256) cgemm_thin_k_kernel(GemmParams prm, int groups, int bin_blocks, int chunk) {
     const unsigned x = blockIdx.x % kXcds, s = blockIdx.x / kXcds;

@@ -20,11 +20,12 @@ inline bool fast_addressing(const FreqLayout &lay, long stride, int bins) {
 
 // A side of at most 32 against one of at least 128 (a few images served through a wide layer, a
 // layer of few channels): 32x128 or 128x32 tiles, as half of every 64x64 tile and of its products
-// would be padding: 8 images, 256 -> 256 channels, 27x27, weights ahead 117 -> 91 us a pass, bprop 155 ->
-// 125; 128 images, 32 -> 32 channels 40 -> 36.  Not where that leaves compute units without a workgroup
-// (112 workgroups: 33 -> 35), nor with
-// gathers of 4 bytes or runs of four planes, where the gathers are the bound, nor
-// for two K tiles or fewer (16 images 160x160, 16 -> 48 channels: 129 -> 131).  Under fast addressing the longer tile's per-lane offsets must fit, too.
+// would be padding: 8 images, 256 -> 256 channels, 27x27, weights ahead 120 -> 100 us a pass (118 -> 91 on
+// the same inputs again and again), bprop 155 -> 123; 128 images, 32 -> 32 channels bprop 40 -> 36.
+// Not where that leaves compute units without a workgroup (112 workgroups: 33 -> 35), nor with gathers
+// of 4 bytes or runs of four planes, where the gathers are the bound, nor for less than two whole K
+// tiles (16 images 160x160, 16 -> 48 channels: 129 -> 131).  Under fast addressing the longer tile's
+// per-lane offsets must fit, too.
 inline bool narrow_tile(const GemmParams &prm, bool vec) {
     if (!vec || prm.layA.tsh < 3 || prm.K < 32) return false;
     if (!((prm.M <= 32 && prm.N >= 128) || (prm.N <= 32 && prm.M >= 128))) return false;
@@ -170,9 +171,9 @@ inline hipError_t prepare(const GemmOperand &A, const GemmOperand &B, float *C, 
     return hipSuccess;
 }
 
-// 64x64 tiles on four waves with one tile of register staging ahead (shape 3) measured fastest
-// for every layer shape tried (more workgroups in flight beat the larger tiles' operand reuse
-// and the deeper staging's registers).
+// But for narrow sides, 64x64 tiles on four waves with one tile of register staging ahead (shape 3)
+// measured fastest of the fp32 kernel's shapes for every layer tried (more workgroups in flight beat
+// the larger tiles' operand reuse and the deeper staging's registers).
 inline int pick_tile(const GemmSwitches &sw, const GemmParams &prm, bool vec) {
     if (sw.tile >= 0) return sw.tile;
     return narrow_tile(prm, vec) ? (prm.M <= 32 ? 6 : 7) : 3;
