@@ -383,7 +383,7 @@ static GemmProblem gemm_problem(const PassPlan &p, const float *AF, const float 
     g.A = GemmOperand{AF, p.lay, p.a_rs, p.a_cs, p.conjA};
     g.B = GemmOperand{BF, p.lay, p.b_rs, p.b_cs, p.conjB};
     g.C = CF; g.layC = p.lay; g.C_rs = p.c_rs; g.C_cs = p.c_cs;
-    g.M = p.M; g.N = p.Nn; g.K = p.K; g.bins = p.bins;
+    g.M = p.M; g.N = p.Nn; g.K = p.K; g.bins = p.bins; g.live = p.Nr * (p.Nc / 2 + 1);
     return g;
 }
 
@@ -425,7 +425,7 @@ static hipError_t invert_pair(fftconv_ctx *c, const PassPlan &pb, const float *G
 static hipError_t contract_and_invert(fftconv_ctx *c, const PassPlan &p, const float *AF, const float *BF,
                                       float *CF, float *out, float scale, int accumulate) {
     const GemmProblem g = gemm_problem(p, AF, BF, CF);
-    if (hipError_t e = launch_cgemm_bins(g.A, g.B, g.C, g.layC, g.C_rs, g.C_cs, g.M, g.N, g.K, g.bins, next_ctx(c, "contraction")); e != hipSuccess) return e;
+    if (hipError_t e = launch_cgemm_bins(g, next_ctx(c, "contraction")); e != hipSuccess) return e;
     return invert(c, p, CF, out, scale, accumulate);
 }
 

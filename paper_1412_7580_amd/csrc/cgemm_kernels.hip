@@ -626,10 +626,9 @@ static hipError_t launch_prepared(const Prepared &q, LaunchCtx st) {
     return dispatch_tile<false, true, false>(shape, prm, st);
 }
 
-hipError_t launch_cgemm_bins(GemmOperand A, GemmOperand B, float *C, FreqLayout layC, long C_rs,
-                             long C_cs, int M, int N, int K, int bins, LaunchCtx st) {
+hipError_t launch_cgemm_bins(const GemmProblem &g, LaunchCtx st) {
     Prepared q;
-    if (hipError_t e = prepare(A, B, C, layC, C_rs, C_cs, M, N, K, bins, switches_of(st.sw), &q); e != hipSuccess) return e;
+    if (hipError_t e = prepare(g, switches_of(st.sw), &q); e != hipSuccess) return e;
     return launch_prepared(q, st);
 }
 
@@ -669,16 +668,16 @@ static hipError_t pair_second(const Prepared &q2, GemmPairParams &pp, LaunchCtx 
 bool cgemm_pair_supported(const GemmProblem &g1, const GemmProblem &g2, const GemmSwitches *swp) {
     const GemmSwitches &sw = switches_of(swp);
     Prepared q1, q2;
-    if (prepare(g1.A, g1.B, g1.C, g1.layC, g1.C_rs, g1.C_cs, g1.M, g1.N, g1.K, g1.bins, sw, &q1) != hipSuccess) return false;
-    if (prepare(g2.A, g2.B, g2.C, g2.layC, g2.C_rs, g2.C_cs, g2.M, g2.N, g2.K, g2.bins, sw, &q2) != hipSuccess) return false;
+    if (prepare(g1, sw, &q1) != hipSuccess) return false;
+    if (prepare(g2, sw, &q2) != hipSuccess) return false;
     return pair_form(q1, q2, sw) != Pair::none;
 }
 
 hipError_t launch_cgemm_pair(const GemmProblem &g1, const GemmProblem &g2, LaunchCtx st) {
     Prepared q1, q2;
     const GemmSwitches &sw = switches_of(st.sw);
-    if (hipError_t e = prepare(g1.A, g1.B, g1.C, g1.layC, g1.C_rs, g1.C_cs, g1.M, g1.N, g1.K, g1.bins, sw, &q1); e != hipSuccess) return e;
-    if (hipError_t e = prepare(g2.A, g2.B, g2.C, g2.layC, g2.C_rs, g2.C_cs, g2.M, g2.N, g2.K, g2.bins, sw, &q2); e != hipSuccess) return e;
+    if (hipError_t e = prepare(g1, sw, &q1); e != hipSuccess) return e;
+    if (hipError_t e = prepare(g2, sw, &q2); e != hipSuccess) return e;
     const Pair form = pair_form(q1, q2, sw);
     if (form == Pair::none) return hipErrorInvalidValue;
     if (form == Pair::split) return launch_cgemm_split_pair(q1.prm, q1.akf, q2.prm, st);

@@ -59,7 +59,7 @@ struct SplitLoader {
     static __device__ __forceinline__ int row_of(int tid) { return KF ? tid / KQ : tid % ROWS; }
     static __device__ __forceinline__ int kq_of(int tid) { return KF ? tid % KQ : tid / ROWS; }
 
-    // The strided index moves in whole plane tiles (fast_addressing() in cgemm_kernels.hip), so an
+    // The strided index moves in whole plane tiles (fast_addressing() in gemm_rules.hpp), so an
     // address is a uniform base that changes with the K tile and an offset that never does.
     __device__ __forceinline__ void prepare(const FreqLayout &lay, long rs, long cs, int r0, int R, int tid) {
         if constexpr (MODE != kFast) return;
@@ -164,7 +164,7 @@ __device__ __forceinline__ bool cgemm_split_attempt(const GemmParams &prm, const
     const int lane = lane_number(), tid = wave * 64 + lane;
     const int wm = wave >> 1, wn = wave & 1;
 
-    // XCD-aware decomposition of the flat workgroup index (see file header).
+    // XCD-aware decomposition of the flat workgroup index (see the head of cgemm_kernels.hip).
     const int tiles = prm.tiles_m * prm.tiles_n;
     const int xcd = wg % kXcds, slot = wg / kXcds;
     const int bins_per_xcd = prm.bins / kXcds;
@@ -257,10 +257,13 @@ __device__ __forceinline__ bool cgemm_split_attempt(const GemmParams &prm, const
     return true;
 }
 
-// The attempts, of which all but the rarest data take one.  The empty asm keeps the compiler from
+// The attempts, of which all but the rarest data take one: not the layout's padding bins, which hold what
+// the memory held.  The empty asm keeps the compiler from
 // holding what the attempts have in common in registers through the K loop.
 template <bool AKF, bool BKF, int MODE>
 __device__ __forceinline__ void cgemm_split_body(const GemmParams &prm, const unsigned wg, char *smem) {
+    const unsigned bins_per_xcd = prm.bins / kXcds, tiles = prm.tiles_m * prm.tiles_n;
+    if (wg % kXcds * bins_per_xcd + wg / kXcds / tiles >= (unsigned)prm.live) return;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 #pragma unroll 1
     for (int i = 0; i < kScalings; ++i) {

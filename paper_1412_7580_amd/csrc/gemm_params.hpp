@@ -11,7 +11,7 @@ struct GemmParams {
     float *C;
     FreqLayout layA, layB, layC;
     long a_rs, a_cs, b_rs, b_cs, c_rs, c_cs;
-    int M, N, K, bins;
+    int M, N, K, bins, live;   // bins from `live` on are padding
     int tiles_m, tiles_n;
     unsigned a_sign, b_sign;   // 0x80000000 to conjugate the operand (flips Im on the way to the MFMA)
     unsigned split_from;       // cgemm_tail_kernel: first workgroup index of the quadrant workgroups

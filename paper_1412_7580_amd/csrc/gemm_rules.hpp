@@ -134,15 +134,16 @@ struct Prepared {
     Thin thin;         // a side of at most four: the vector-unit kernels apply (cgemm_thin.hip)
 };
 
-inline hipError_t prepare(const GemmOperand &A, const GemmOperand &B, float *C, FreqLayout layC, long C_rs,
-                          long C_cs, int M, int N, int K, int bins, const GemmSwitches &sw, Prepared *out) {
+inline hipError_t prepare(const GemmProblem &g, const GemmSwitches &sw, Prepared *out) {
+    const GemmOperand &A = g.A, &B = g.B;
+    const int M = g.M, N = g.N, K = g.K, bins = g.bins;
     if (bins % kXcds != 0) return hipErrorInvalidValue;   // N*(N/2+1) with N >= 8 always is
     GemmParams &prm = out->prm;
-    prm.A = A.ptr; prm.B = B.ptr; prm.C = C;
-    prm.layA = A.lay; prm.layB = B.lay; prm.layC = layC;
+    prm.A = A.ptr; prm.B = B.ptr; prm.C = g.C;
+    prm.layA = A.lay; prm.layB = B.lay; prm.layC = g.layC;
     prm.a_rs = A.rs; prm.a_cs = A.cs; prm.b_rs = B.rs; prm.b_cs = B.cs;
-    prm.c_rs = C_rs; prm.c_cs = C_cs;
-    prm.M = M; prm.N = N; prm.K = K; prm.bins = bins;
+    prm.c_rs = g.C_rs; prm.c_cs = g.C_cs;
+    prm.M = M; prm.N = N; prm.K = K; prm.bins = bins; prm.live = g.live;
     prm.tiles_m = prm.tiles_n = 0;
     prm.split_from = 0xffffffffu;
     prm.a_sign = A.conj ? 0x80000000u : 0u;
@@ -157,13 +158,13 @@ inline hipError_t prepare(const GemmOperand &A, const GemmOperand &B, float *C, 
     const bool vb = bkf ? vec_ok(B.lay, K, B.cs, B.ptr) : (B.cs == 1 && vec_ok(B.lay, N, B.rs, B.ptr));
     out->akf = akf; out->bkf = bkf; out->vec = va && vb;
     prm.fast = (out->vec && fast_addressing(A.lay, akf ? A.rs : A.cs, bins) &&
-                fast_addressing(B.lay, bkf ? B.cs : B.rs, bins) && C_cs == 1 && fast_addressing(layC, C_rs, bins) &&
+                fast_addressing(B.lay, bkf ? B.cs : B.rs, bins) && g.C_cs == 1 && fast_addressing(g.layC, g.C_rs, bins) &&
                 !sw.no_fast) ? 1 : 0;
     // Layouts with runs of 4 planes (basis 64) put four bins in every 128-byte line: the
     // bin-group kernel loads whole lines and multiplies the four bins side by side.
-    out->bingroup = out->vec && !sw.no_bingroup && A.lay.tsh == 2 && B.lay.tsh == 2 && layC.tsh == 2 &&
-                    bins % (4 * kXcds) == 0 && (akf || A.rs == 1) && (bkf || B.cs == 1) && C_cs == 1 &&
-                    C_rs % 4 == 0 && N % 4 == 0 && ((size_t)C & 15) == 0;
+    out->bingroup = out->vec && !sw.no_bingroup && A.lay.tsh == 2 && B.lay.tsh == 2 && g.layC.tsh == 2 &&
+                    bins % (4 * kXcds) == 0 && (akf || A.rs == 1) && (bkf || B.cs == 1) && g.C_cs == 1 &&
+                    g.C_rs % 4 == 0 && N % 4 == 0 && ((size_t)g.C & 15) == 0;
     const Thin form = thin_form(prm);
     out->thin = sw.no_thin || sw.tile >= 0 || !thin_pays(prm, form, bkf, out->vec, out->bingroup) ? Thin::none : form;
     out->split = !out->bingroup && (akf || !bkf) && !sw.no_split && sw.tile < 0 && split_pays(prm, akf, bkf, out->vec) && !narrow_tile(prm, out->vec);

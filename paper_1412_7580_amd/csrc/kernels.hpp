@@ -86,7 +86,8 @@ int fft2d_tile_log2(int N);
 // 32 for the bases with runs of 4 planes), so that the contraction can always cut the bins into
 // equal chunks per XCD (and whole 128-byte lines).  The padding bins, which only bases with an
 // odd factor have, are never written by the transforms nor read by the inverse; the
-// contraction multiplies whatever they hold into the padding bins of its output.
+// contraction multiplies whatever they hold into the padding bins of its output (the bf16 kernel,
+// which looks at its sums, leaves them out).
 int fft2d_layout_bins(int N);
 
 // 2-D R2C of `planes` planes [h_in x w_in] zero-padded to N x N.
@@ -171,18 +172,19 @@ struct GemmOperand {
     long rs, cs;       // plane strides of the (row, col) indices
     bool conj;         // use the complex conjugate of the stored values
 };
-hipError_t launch_cgemm_bins(GemmOperand A, GemmOperand B, float *C, FreqLayout layC, long C_rs,
-                             long C_cs, int M, int N, int K, int bins, LaunchCtx st);
-
-// Two independent contractions in one launch (see cgemm_pair_kernel).  Possible when both
-// can use 16-byte gathers and neither is a case for the four-bins-per-line kernel.
+// `bins` of the layout, of which the first `live` hold data: the rest is its padding (see
+// fft2d_layout_bins()), whose products nothing reads.
 struct GemmProblem {
     GemmOperand A, B;
     float *C;
     FreqLayout layC;
     long C_rs, C_cs;
-    int M, N, K, bins;
+    int M, N, K, bins, live;
 };
+hipError_t launch_cgemm_bins(const GemmProblem &g, LaunchCtx st);
+
+// Two independent contractions in one launch (see cgemm_pair_kernel).  Possible when both
+// can use 16-byte gathers and neither is a case for the four-bins-per-line kernel.
 bool cgemm_pair_supported(const GemmProblem &g1, const GemmProblem &g2, const GemmSwitches *sw = nullptr);
 hipError_t launch_cgemm_pair(const GemmProblem &g1, const GemmProblem &g2, LaunchCtx st);
 

@@ -7,8 +7,9 @@ using namespace fc;
 static bool problem(const long *v, const GemmSwitches &sw, Prepared *q) {
     const FreqLayout lay{(int)v[4], (int)v[3]};
     float *at = reinterpret_cast<float *>((size_t)1 << 20);
-    return prepare(GemmOperand{at, lay, v[5], v[6], false}, GemmOperand{at, lay, v[7], v[8], false}, at, lay, v[9], v[10],
-                   (int)v[0], (int)v[1], (int)v[2], (int)v[3], sw, q) == hipSuccess;
+    const GemmProblem g{GemmOperand{at, lay, v[5], v[6], false}, GemmOperand{at, lay, v[7], v[8], false}, at, lay, v[9], v[10],
+                        (int)v[0], (int)v[1], (int)v[2], (int)v[3], (int)v[3]};
+    return prepare(g, sw, q) == hipSuccess;
 }
 // sw: tile shape (-1: none), then no_pair
 static GemmSwitches switches(const long *sw) {

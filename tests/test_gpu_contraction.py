@@ -153,3 +153,24 @@ def test_values_that_are_not_finite_stay_in_their_sample(hd):
     other = [s for s in range(64) if s not in (5, 9)]
     assert not torch.isfinite(got[5]).any() and not torch.isfinite(got[9]).any()
     assert float((got[other].double() - ref[other]).abs().max() / ref.abs().max()) <= TOL
+
+
+@pytest.mark.parametrize("side", [10, 12, 20], ids=["bins60of64", "bins84of88", "bins220of224"])
+def test_bf16_kernel_leaves_the_padding_bins_alone(hd, lib, side):
+    """They hold whatever the memory held: NaN there would have the kernel repeat their tiles for nothing."""
+    import torch
+    import torch.nn.functional as F
+    S, f, fo = 136, 128, 128
+    d = lib.describe_plan(lib.FPROP, S, f, fo, side, side, 3, 3)
+    live, bins, T = d["Nr"] * (d["Nr"] // 2 + 1), d["bins"], 1 << d["tile_log2"]
+    assert live < bins
+    g = torch.Generator().manual_seed(6)
+    x, w = torch.randn(S, f, side, side, generator=g), torch.randn(fo, f, 3, 3, generator=g)
+    ws = torch.full((d["total"] // 4,), float("nan"), device="cuda")
+    got = hd.fft_conv_fprop(x.cuda(), w.cuda(), ws=ws)
+    assert _relerr(got, F.conv2d(x.double(), w.double())) <= TOL
+    product = ws[d["offC"] // 4:][:-(-d["planesC"] // T) * T * bins * 2].view(-1, bins, 2, T)
+    assert torch.isfinite(product[:, :live]).all()
+    ws.fill_(7.0)
+    hd.fft_conv_fprop(x.cuda(), w.cuda(), ws=ws)
+    assert (product[:, live:] == 7.0).all()
