@@ -166,100 +166,144 @@ __device__ __forceinline__ void stage_padded(float *dst, const float *src, unsig
 }
 
 // ------------------------------------------------------------------ tiled operands
+// Quotient of x < 2^31 by an invariant d < 2^31: with l = ceil(log2 d) and m = floor(2^(31+l) / d) + 1,
+// (x m) >> (31 + l) is exact (Granlund and Montgomery, "Division by invariant integers using
+// multiplication", 1994): m d exceeds 2^(31+l) by at most 2^l, which a factor below 2^31 cannot turn into one.
+struct Div31 {
+    unsigned m;
+    int shift;
+};
+static inline Div31 make_div31(unsigned d) {
+    int l = 0;
+    while ((1u << l) < d) ++l;
+    return Div31{(unsigned)((1ull << (31 + l)) / d + 1), 31 + l};
+}
+__device__ __forceinline__ unsigned div31(unsigned x, Div31 d) { return (unsigned)(((unsigned long long)x * d.m) >> d.shift); }
+
+// A view and its dividers.
+struct WindowMap {
+    PlaneView v;
+    Div31 c, ntx, nty;
+};
+static inline WindowMap make_window_map(const PlaneView &v) {
+    return WindowMap{v, make_div31((unsigned)v.C), make_div31((unsigned)v.ntx), make_div31((unsigned)v.nty)};
+}
+
 // Image offset and window origin (before the view's oy / ox) of plane p of a tiled operand.
 struct PlaneOrigin {
     long long base;
     int y0, x0;
 };
-__device__ __forceinline__ PlaneOrigin plane_origin(const PlaneView &v, long p) {
-    const long m = p / v.C;
-    const int ch = (int)(p - m * v.C);
-    const long q = m / v.ntx;
-    const int tx = (int)(m - q * v.ntx);
-    const long s = q / v.nty;
-    const int ty = (int)(q - s * v.nty);
+__device__ __forceinline__ PlaneOrigin plane_origin(const WindowMap &wm, unsigned p) {
+    const PlaneView &v = wm.v;
+    const unsigned m = div31(p, wm.c), ch = p - m * v.C;
+    const unsigned q = div31(m, wm.ntx), tx = m - q * v.ntx;
+    const unsigned s = div31(q, wm.nty), ty = q - s * v.nty;
     const int cimg = v.Cimg ? v.Cimg : v.C;
-    return PlaneOrigin{((s * cimg + ch) * (long long)v.H) * v.W, ty * v.dy, tx * v.dx};
+    return PlaneOrigin{((long long)s * cimg + ch) * v.H * v.W, (int)ty * v.dy, (int)tx * v.dx};
 }
 
-// Per-workgroup table of the origins of its np planes, kept in LDS at `info`
-// (T x 16 bytes: bases, then y0, then x0).
-template <int T>
-struct OriginTable {
-    long long *base;
-    int *y0, *x0;
-    __device__ __forceinline__ explicit OriginTable(float *info)
-        : base(reinterpret_cast<long long *>(info)), y0(reinterpret_cast<int *>(info + 2 * T)), x0(y0 + T) {}
-    __device__ __forceinline__ void fill(const PlaneView &v, long p0, int np, int tid) {
-        if (tid < np) {
-            const PlaneOrigin o = plane_origin(v, p0 + tid);
-            base[tid] = o.base; y0[tid] = o.y0; x0[tid] = o.x0;
-        }
-        __syncthreads();
+// How the threads of a workgroup share the rows of T windows: a thread keeps V columns (of N) and
+// the rows r0, r0 + step, ... of one plane (or of `passes` planes, T / passes apart, one after the
+// other), so that window origin, column and column check are worked out once a plane and an
+// access costs a row check and an add.  With every lane dividing its way from a flat element
+// number to row, column and plane, and the origins from a table in LDS behind a barrier, the forward
+// transforms of windows were bound by that arithmetic: a fifth of the vector instructions of the
+// 32-basis kernel, and its time 71 -> 61 us for the 16384 + 16384 windows of gy of a 56x56 layer (32 images,
+// 128 channels, 3x3, padded), 711 -> 625 us for 110592 windows of basis 56 (first layer, 118x118 outputs).
+// V = 4 where every window starts on 16 bytes (window_vec()), else 1.
+template <int L, int G, int T, int V>
+struct WindowRows {
+    static constexpr int N = L * G, LANES = N / V, SLOTS = T * (N / 2) * G / LANES;   // rows side by side
+    static_assert(N % V == 0 && SLOTS * LANES == T * (N / 2) * G, "whole rows");
+    static constexpr int step = SLOTS >= T ? SLOTS / T : 1;
+    static constexpr int passes = SLOTS >= T ? 1 : T / SLOTS;
+    static constexpr int rounds = (N + step - 1) / step;        // rows of a plane that a thread takes, at most
+    static constexpr int most = V == 1 ? 16 : 8;                // ... in equal batches of up to so many
+    static constexpr int U = (rounds + (rounds + most - 1) / most - 1) / ((rounds + most - 1) / most);
+    int col, plane, r0;
+    __device__ __forceinline__ explicit WindowRows(int tid) {
+        const int slot = tid / LANES;
+        col = (tid - slot * LANES) * V;
+        plane = slot / step;
+        r0 = slot - plane * step;
     }
 };
 
-// Gather the h x w windows of np planes into an LDS image with row stride rs and plane
-// stride ps; elements outside the H x W image become 0.  V floats per load: V = 4 needs every
-// window column origin, W, w and the image base to be multiples of 4 floats, so that a
-// group of 4 lies wholly inside or outside the image and is 16-byte aligned; div_w divides
-// by w / V.
-template <int BT, int T, int V>
-__device__ __forceinline__ void stage_windows(float *dst, const float *img, const PlaneView &v,
-                                              const OriginTable<T> &tab, int np, unsigned h, unsigned w,
-                                              unsigned rs, unsigned ps, MagicDiv div_w, MagicDiv div_h, int tid) {
-    constexpr int U = (V == 1) ? 8 : 4;
+// Gather the h x w windows of np planes from p0 on into an LDS image with row stride rs and plane
+// stride ps; elements outside the H x W image become 0.
+template <int L, int G, int T, int V>
+__device__ __forceinline__ void stage_windows(float *dst, const float *img, const WindowMap &wm, long p0, int np, int h, int w,
+                                              int rs, int ps, int tid) {
+    typedef WindowRows<L, G, T, V> WR;
     typedef float vec_t __attribute__((ext_vector_type(V)));
-    const unsigned wv = w / V, total = (unsigned)np * h * wv;
-    for (unsigned b = tid; b < total; b += BT * U) {
-        vec_t val[U];
-        unsigned off[U];
+    const WR wr(tid);
+    const PlaneView &v = wm.v;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const unsigned e = b + u * BT;
-            val[u] = vec_t(0.f); off[u] = 0;
-            if (e < total) {
-                const unsigned row = mdiv(e, div_w);
-                const unsigned c = (e - row * wv) * V;
-                const unsigned pl = mdiv(row, div_h);
-                const unsigned r = row - pl * h;
-                off[u] = pl * ps + r * rs + c;
-                const int gy = tab.y0[pl] + v.oy + (int)r, gx = tab.x0[pl] + v.ox + (int)c;
-                if ((unsigned)gy < (unsigned)v.H && (unsigned)gx < (unsigned)v.W)
-                    val[u] = *reinterpret_cast<const vec_t *>(img + tab.base[pl] + (long long)gy * v.W + gx);
+    for (int pass = 0; pass < WR::passes; ++pass) {
+        const int pl = wr.plane + pass * (T / WR::passes);
+        if (pl >= np || wr.col >= w) continue;
+        const PlaneOrigin o = plane_origin(wm, (unsigned)(p0 + pl));
+        const int gx = o.x0 + v.ox + wr.col, gy = o.y0 + v.oy + wr.r0;
+        const bool in_cols = (unsigned)gx < (unsigned)v.W;
+        const float *src = img + o.base + (long long)gy * v.W + gx;
+        float *d = dst + pl * ps + wr.r0 * rs + wr.col;
+        for (int i = 0; i * WR::step < h; i += WR::U) {
+            vec_t val[WR::U];
+#pragma unroll
+            for (int u = 0; u < WR::U; ++u) {
+                const int r = (i + u) * WR::step;
+                val[u] = vec_t(0.f);
+                if (in_cols && wr.r0 + r < h && (unsigned)(gy + r) < (unsigned)v.H)
+                    val[u] = *reinterpret_cast<const vec_t *>(src + (long long)r * v.W);
+            }
+#pragma unroll
+            for (int u = 0; u < WR::U; ++u) {
+                const int r = (i + u) * WR::step;
+                if (wr.r0 + r < h) {
+#pragma unroll
+                    for (int q = 0; q < V; ++q) d[r * rs + q] = val[u][q];
+                }
             }
         }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (b + u * BT < total) {
-#pragma unroll
-                for (int q = 0; q < V; ++q) dst[off[u] + q] = val[u][q];
-            }
     }
 }
 
 // Scatter the h x w windows at offset (oy, ox) of an LDS image of np planes of sh x sw floats
-// to their places in the H x W images; elements outside the image are dropped.  V = 4 under the
-// same alignment conditions as for the gather, plus sw and ox multiples of 4.
-template <int BT, int T, int V>
-__device__ __forceinline__ void unstage_windows(float *img, const float *src, const PlaneView &v,
-                                                const OriginTable<T> &tab, int np, unsigned h, unsigned w,
-                                                unsigned sh, unsigned sw, MagicDiv div_w, MagicDiv div_h,
-                                                int tid, bool accumulate) {
+// to their places in the H x W images; elements outside the image are dropped.
+template <int L, int G, int T, int V>
+__device__ __forceinline__ void unstage_windows(float *img, const float *src, const WindowMap &wm, long p0, int np, int h, int w,
+                                                int sh, int sw, int tid, bool accumulate) {
+    typedef WindowRows<L, G, T, V> WR;
     typedef float vec_t __attribute__((ext_vector_type(V)));
-    const unsigned wv = w / V, total = (unsigned)np * h * wv;
-    for (unsigned e = tid; e < total; e += BT) {
-        const unsigned row = mdiv(e, div_w);
-        const unsigned c = (e - row * wv) * V;
-        const unsigned pl = mdiv(row, div_h);
-        const unsigned r = row - pl * h;
-        const int gy = tab.y0[pl] + (int)r, gx = tab.x0[pl] + (int)c;
-        if (gy < v.H && gx < v.W) {
-            vec_t *d = reinterpret_cast<vec_t *>(img + tab.base[pl] + (long long)gy * v.W + gx);
-            const vec_t val = *reinterpret_cast<const vec_t *>(src + (pl * sh + r + v.oy) * sw + c + v.ox);
-            if (accumulate) *d += val; else *d = val;
+    const WR wr(tid);
+    const PlaneView &v = wm.v;
+#pragma unroll
+    for (int pass = 0; pass < WR::passes; ++pass) {
+        const int pl = wr.plane + pass * (T / WR::passes);
+        if (pl >= np || wr.col >= w) continue;
+        const PlaneOrigin o = plane_origin(wm, (unsigned)(p0 + pl));
+        const int gx = o.x0 + wr.col;
+        const int end = h < v.H - o.y0 ? h : v.H - o.y0;        // rows of the window inside the image
+        if (gx >= v.W) continue;
+        float *d = img + o.base + (long long)o.y0 * v.W + gx;
+        const float *s = src + (pl * sh + v.oy) * sw + v.ox + wr.col;
+        if (accumulate) {
+            for (int r = wr.r0; r < end; r += WR::step)
+                *reinterpret_cast<vec_t *>(d + (long long)r * v.W) += *reinterpret_cast<const vec_t *>(s + r * sw);
+        } else {
+#pragma unroll 4
+            for (int r = wr.r0; r < end; r += WR::step)
+                *reinterpret_cast<vec_t *>(d + (long long)r * v.W) = *reinterpret_cast<const vec_t *>(s + r * sw);
         }
     }
+}
+
+// Whether windows of w columns can move as groups of four: then a group lies wholly inside or outside
+// the image and starts on 16 bytes, in memory and (with rows of ox + w floats) in the LDS image.
+template <int L, int G>
+static inline bool window_vec(const void *img, const PlaneView &v, int w) {
+    return (L * G) % 4 == 0 && ((size_t)img & 15) == 0 && v.W % 4 == 0 && v.dx % 4 == 0 && v.ox % 4 == 0 && w % 4 == 0;
 }
 
 // ------------------------------------------------------------------ 2-D forward
@@ -276,10 +320,9 @@ struct Fwd2dParams {
     int linear;       // staged planes need no padding: LDS image == global image
     int vec_ok;       // (unused by the linear staging, which adapts to the block's alignment)
     int out_vec_ok;   // output base and every block start are 16-byte aligned
-    int tiled;        // planes are windows of images (view); origin table at LDS float info_off
-    int info_off;
+    int tiled;        // planes are windows of images (win)
     int tw_off;       // lines of four or eight lanes: twiddle table at LDS float tw_off
-    PlaneView view;
+    WindowMap win;
 };
 
 // How the forward kernels write the plane-tiled layout.  With runs of 16 planes or more a lane's
@@ -341,14 +384,9 @@ __device__ __forceinline__ void fft2d_r2c_body(const Fwd2dParams &prm, unsigned 
     bool windows = false;
     if constexpr (CONV) windows = prm.tiled != 0;   // only the plane-tiled layout is used with views
     if (windows) {
-        OriginTable<T> tab(smem + prm.info_off);
-        tab.fill(prm.view, p0, np, tid);
-        if (prm.vecw == 4)
-            stage_windows<BT, T, 4>(sin, prm.in, prm.view, tab, np, h_in, w_in, prm.RS, prm.IPS, prm.div_wv,
-                                    prm.div_h, tid);
-        else
-            stage_windows<BT, T, 1>(sin, prm.in, prm.view, tab, np, h_in, w_in, prm.RS, prm.IPS, prm.div_wv,
-                                    prm.div_h, tid);
+        constexpr int V = N % 4 ? 1 : 4;
+        if (prm.vecw == 4) stage_windows<L, G, T, V>(sin, prm.in, prm.win, p0, np, h_in, w_in, prm.RS, prm.IPS, tid);
+        else stage_windows<L, G, T, 1>(sin, prm.in, prm.win, p0, np, h_in, w_in, prm.RS, prm.IPS, tid);
     } else {
         const float *src = prm.in + p0 * hw;
         if (prm.linear) {
@@ -538,14 +576,12 @@ struct Inv2dParams {
     FreqLayout lay;
     float scale;
     int accumulate;
-    int vec_ok;       // tiled outputs: the windows can be scattered with 16-byte stores
-    int in_vec_ok;    // natural layout only: input base is 16-byte aligned
-    int tiled;        // outputs are windows of images (view); origin table at LDS float info_off
-    int info_off;
-    int win_h, win_w; // tiled: size of the window taken at (view.oy, view.ox) of the h_out x w_out block
+    int in_vec_ok;    // input base and every block start are 16-byte aligned
+    int tiled;        // outputs are windows of images (win)
+    int vec_ok;       // tiled: the windows can be scattered with 16-byte stores
+    int win_h, win_w; // tiled: size of the window taken at (oy, ox) of the h_out x w_out block
     int tw_off;       // lines of four or eight lanes: twiddle table at LDS float tw_off
-    MagicDiv div_w, div_h;
-    PlaneView view;
+    WindowMap win;
 };
 
 // PRE (plane-tiled layout only): the block's input already stands in LDS at pre_img, laid out
@@ -679,14 +715,13 @@ __device__ __forceinline__ void fft2d_c2r_body(const Inv2dParams &prm, unsigned 
     __syncthreads();
     if constexpr (CONV) {
         if (prm.tiled) {
-            OriginTable<T> tab(smem + prm.info_off);
-            tab.fill(prm.view, p0, np, tid);
+            constexpr int V = N % 4 ? 1 : 4;
             if (prm.vec_ok)
-                unstage_windows<BT, T, 4>(prm.out, sout, prm.view, tab, np, prm.win_h, prm.win_w, h_out, w_out,
-                                          prm.div_w, prm.div_h, tid, prm.accumulate != 0);
+                unstage_windows<L, G, T, V>(prm.out, sout, prm.win, p0, np, prm.win_h, prm.win_w, h_out, w_out, tid,
+                                            prm.accumulate != 0);
             else
-                unstage_windows<BT, T, 1>(prm.out, sout, prm.view, tab, np, prm.win_h, prm.win_w, h_out, w_out,
-                                          prm.div_w, prm.div_h, tid, prm.accumulate != 0);
+                unstage_windows<L, G, T, 1>(prm.out, sout, prm.win, p0, np, prm.win_h, prm.win_w, h_out, w_out, tid,
+                                            prm.accumulate != 0);
             return;
         }
     }
@@ -923,14 +958,11 @@ static Fwd2dParams make_fwd2d(const float *in, float *out, long planes, int h_in
     prm.out_vec_ok = (((size_t)out & 15) == 0 && ((size_t)T * N * (NH + 1) * 2) % 4 == 0) ? 1 : 0;
     const size_t a = ((size_t)T * prm.IPS + N) * sizeof(float), b = (size_t)T * prm.MPS * sizeof(float2);
     *lds = a > b ? a : b;
-    prm.tiled = 0; prm.info_off = 0; prm.tw_off = 0; prm.view = PlaneView{};
-    if (view) {   // gathered windows: scalar loads, padded image, origin table behind everything else
-        prm.tiled = 1; prm.view = *view;
+    prm.tiled = 0; prm.tw_off = 0; prm.win = WindowMap{};
+    if (view) {   // gathered windows: padded image
+        prm.tiled = 1; prm.win = make_window_map(*view);
         prm.linear = 0;
-        const bool v4 = ((size_t)in & 15) == 0 && view->W % 4 == 0 && view->dx % 4 == 0 && view->ox % 4 == 0 &&
-                        w_in % 4 == 0;
-        prm.vecw = v4 ? 4 : 1;
-        prm.div_wv = make_magic((unsigned)(w_in / prm.vecw));
+        prm.vecw = window_vec<L, G>(in, *view, w_in) ? 4 : 1;
     }
     return prm;
 }
@@ -944,14 +976,6 @@ static inline size_t with_twiddle_table(size_t lds, int *tw_off) {
     const size_t at = (lds + 7) / 8 * 8;
     *tw_off = (int)(at / sizeof(float));
     return at + kGroupTwiddleFloats<L, G> * sizeof(float);
-}
-
-// LDS bytes of a launch whose blocks keep an origin table of T planes behind `lds` bytes of
-// other data; *info_off receives the table's offset in floats.
-static inline size_t with_origin_table(size_t lds, int T, int *info_off) {
-    const size_t at = (lds + 7) / 8 * 8;
-    *info_off = (int)(at / sizeof(float));
-    return at + (size_t)T * 16;
 }
 
 // CONV_TOO = false: only the natural-layout kernel is instantiated (conv must be false).
@@ -970,7 +994,6 @@ static hipError_t run_fwd2d(const float *in, float *out, long planes, int h_in, 
         if (c > lds) lds = c;
     }
     lds = with_twiddle_table<L, G>(lds, &prm.tw_off);
-    if (prm.tiled) lds = with_origin_table(lds, T, &prm.info_off);
     const unsigned grid = (unsigned)((planes + T - 1) / T);
     hipError_t e;
     auto go = [&](auto k) -> hipError_t {
@@ -1011,15 +1034,6 @@ static hipError_t run_fwd2d_multi(const FwdOperand *ops, int nops, LaunchCtx st)
         lds = with_twiddle_table<L, G>(lds, &tw_off);
         for (int o = 0; o < 3; ++o) m.op[o].tw_off = tw_off;
     }
-    {   // one origin table position for all operands, behind everything else
-        int info_off = 0;
-        bool any = false;
-        for (int o = 0; o < nops; ++o) any = any || m.op[o].tiled;
-        if (any) {
-            lds = with_origin_table(lds, T, &info_off);
-            for (int o = 0; o < 3; ++o) m.op[o].info_off = info_off;
-        }
-    }
     auto k = fft2d_r2c_multi_kernel<L, G, T>;
     hipError_t e;
     if ((e = allow_big_lds((const void *)k, lds)) != hipSuccess) return e;
@@ -1035,16 +1049,12 @@ static Inv2dParams make_inv2d(const float *in, float *out, long planes, int h_ou
                               bool force_stage = false) {
     constexpr int N = L * G, NH = N / 2;
     Inv2dParams prm;
-    prm.tiled = 0; prm.info_off = 0; prm.win_h = prm.win_w = 0; prm.view = PlaneView{};
-    prm.div_w = prm.div_h = MagicDiv{0};
-    bool tiled_vec = false;
+    prm.tiled = 0; prm.win_h = prm.win_w = 0; prm.vec_ok = 0; prm.win = WindowMap{};
     if (view) {
         // the block assembled in LDS spans the transform's rows / columns up to the window's end
-        prm.tiled = 1; prm.view = *view;
+        prm.tiled = 1; prm.win = make_window_map(*view);
         prm.win_h = h_out; prm.win_w = w_out;
-        tiled_vec = ((size_t)out & 15) == 0 && view->W % 4 == 0 && view->dx % 4 == 0 && view->ox % 4 == 0 &&
-                    w_out % 4 == 0;    // then the LDS block's row length ox + w_out is a multiple of 4 too
-        prm.div_w = make_magic((unsigned)(tiled_vec ? w_out / 4 : w_out)); prm.div_h = make_magic((unsigned)h_out);
+        prm.vec_ok = window_vec<L, G>(out, *view, w_out) ? 1 : 0;
         h_out += view->oy; w_out += view->ox;
     }
     prm.in = in; prm.out = out; prm.planes = planes; prm.h_out = h_out; prm.w_out = w_out;
@@ -1052,8 +1062,6 @@ static Inv2dParams make_inv2d(const float *in, float *out, long planes, int h_ou
     prm.lay.tsh = fft2d_tile_log2(N);
     prm.lay.bins = fft2d_layout_bins(N);
     prm.scale = scale; prm.accumulate = accumulate ? 1 : 0;
-    prm.vec_ok = (((size_t)out & 15) == 0 && ((size_t)T * h_out * w_out) % 4 == 0) ? 1 : 0;
-    if (view) prm.vec_ok = tiled_vec ? 1 : 0;   // tiled: 16-byte scatter of the windows
     prm.in_vec_ok = (((size_t)in & 15) == 0 && ((size_t)T * N * (NH + 1) * 2) % 4 == 0) ? 1 : 0;
     const size_t a = (size_t)T * prm.MPS * sizeof(float2), b = ((size_t)T * h_out * w_out + 3) * sizeof(float);
     size_t lds = a > b ? a : b;
@@ -1078,7 +1086,6 @@ static hipError_t run_inv2d(const float *in, float *out, long planes, int h_out,
     bool istage;
     Inv2dParams prm = make_inv2d<L, G, T>(in, out, planes, h_out, w_out, conv, scale, accumulate, view, &lds, &istage);
     lds = with_twiddle_table<L, G>(lds, &prm.tw_off);
-    if (prm.tiled) lds = with_origin_table(lds, T, &prm.info_off);
     const unsigned grid = (unsigned)((planes + T - 1) / T);
     hipError_t e;
     auto go = [&](auto k) -> hipError_t {
@@ -1102,7 +1109,6 @@ static hipError_t run_inv2d_pair(const InvOperand *ops, LaunchCtx st) {
     InvPairParams m;
     size_t lds = 0;
     unsigned blocks = 0;
-    bool any_tiled = false;
     for (int o = 0; o < 2; ++o) {
         size_t l;
         bool istage;
@@ -1110,14 +1116,12 @@ static hipError_t run_inv2d_pair(const InvOperand *ops, LaunchCtx st) {
         m.op[o] = make_inv2d<L, G, T>(ops[o].in, ops[o].out, ops[o].planes, ops[o].h_out, ops[o].w_out, true,
                                       ops[o].scale, ops[o].accumulate, ops[o].view, &l, &istage, true);
         if (l > lds) lds = l;
-        any_tiled = any_tiled || m.op[o].tiled;
         blocks += (unsigned)((ops[o].planes + T - 1) / T);
     }
     m.first[2] = blocks;
-    int tw_off = 0, info_off = 0;
+    int tw_off = 0;
     lds = with_twiddle_table<L, G>(lds, &tw_off);
-    if (any_tiled) lds = with_origin_table(lds, T, &info_off);
-    for (int o = 0; o < 2; ++o) { m.op[o].tw_off = tw_off; m.op[o].info_off = info_off; }
+    for (int o = 0; o < 2; ++o) m.op[o].tw_off = tw_off;
     if (blocks == 0) return hipSuccess;
     auto k = fft2d_c2r_pair_kernel<L, G, T>;
     if (hipError_t e = allow_big_lds((const void *)k, lds); e != hipSuccess) return e;

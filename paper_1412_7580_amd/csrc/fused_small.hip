@@ -122,8 +122,8 @@ static hipError_t run_fused(const float *x, const float *wf, float *y, int S, in
     iv.MPS = MidLayout<L, G>::inv_plane(oh) | 1;
     iv.lay = fp.fwd.lay;
     iv.scale = 1.0f / ((float)N * (float)N); iv.accumulate = 0;
-    iv.vec_ok = 0; iv.in_vec_ok = 0; iv.tiled = 0; iv.info_off = 0; iv.tw_off = 0; iv.win_h = iv.win_w = 0;
-    iv.div_w = iv.div_h = MagicDiv{0}; iv.view = PlaneView{};
+    iv.in_vec_ok = 0; iv.vec_ok = 0; iv.tiled = 0; iv.tw_off = 0; iv.win_h = iv.win_w = 0;
+    iv.win = WindowMap{};
     fp.wf = wf; fp.f = f; fp.fo = fo;
     fp.x_stride = (long)in_planes * in_h * in_w; fp.y_stride = (long)out_planes * oh * ow;
     const size_t img = (size_t)T * N * NB * 2;           // floats of one LDS image
@@ -347,7 +347,7 @@ static hipError_t run_fused_accgrad(const float *gy, const float *x, float *gw, 
     const size_t img = (size_t)T * N * NB * 2 * sizeof(float);      // bytes of one LDS image
     // Two regions of equal size, one per thread set, each holding its forward transform's staging
     // and transposed data and then its spectra (the first later also the inverse's transposed data
-    // and output block); the products' image behind them, the two origin tables last.
+    // and output block); the products' image behind them.
     size_t first = img;
     if (lds_g > first) first = lds_g;
     if (lds_x > first) first = lds_x;
@@ -357,11 +357,7 @@ static hipError_t run_fused_accgrad(const float *gy, const float *x, float *gw, 
     first = (first + 15) / 16 * 16;
     ap.imgB = (int)(first / sizeof(float));
     ap.imgC = (int)(2 * first / sizeof(float));
-    int info0 = 0, info1 = 0;
-    size_t lds = with_origin_table(2 * first + img, T, &info0);
-    lds = with_origin_table(lds, T, &info1);
-    ap.fg.info_off = ap.inv.info_off = info0;
-    ap.fx.info_off = info1 - ap.imgB;          // relative to the second region
+    const size_t lds = 2 * first + img;
     if (lds > 160 * 1024) return hipErrorInvalidValue;
     auto k = fused_accgrad_kernel<L, G, T>;
     if (hipError_t e = allow_big_lds((const void *)k, lds); e != hipSuccess) return e;

@@ -276,3 +276,21 @@ def test_reuse_pair_on_a_named_basis(hd, cfg, n):
     assert torch.equal(y, hd.fft_conv_fprop_tiled(dx, dw, n))
     with pytest.raises(Exception, match="workspace too small"):
         hd.fft_conv_fprop_save_tiled(dx, dw, n, saved[:-64])
+
+
+@pytest.mark.parametrize("n", [8, 10, 12, 14, 16, 18, 20, 24, 28, 32, 36, 40, 48, 56, 64, 80, 96, 112, 128])
+@pytest.mark.parametrize("fours", [True, False], ids=["fours", "singles"])
+def test_windows_of_every_basis(hd, n, fours):
+    """Gathered and scattered windows on every basis (each with its own share of rows and planes a thread),
+    with image rows, tiles and origins that move in groups of four and ones that do not, ragged last
+    tiles and last planes, and gw added to."""
+    import torch
+    h, w, kh, kw = 2 * n + 3, 2 * n + (4 if fours else 3), 3, 5 if fours else 3
+    cfg = dict(S=1, f=2, fo=3, h=h, w=w, kh=kh, kw=kw)
+    x, wt, gy = synth.conv_inputs(seed=700 + n, **cfg)
+    dx, dw, dgy = _dev(x), _dev(wt), _dev(gy)
+    assert _relerr(_np(hd.fft_conv_fprop_tiled(dx, dw, n)), oracle.conv_fprop(x, wt)) <= TOL
+    assert _relerr(_np(hd.fft_conv_bprop_tiled(dgy, dw, h, w, n)), oracle.conv_bprop(gy, wt, h, w)) <= TOL
+    gw = torch.full((3, 2, kh, kw), 0.25, device="cuda")
+    hd.fft_conv_accgrad_tiled(dx, dgy, n, gw=gw, scale=-0.5, accumulate=True)
+    assert _relerr(_np(gw), 0.25 - 0.5 * oracle.conv_accgrad(x, gy)) <= TOL
