@@ -554,6 +554,7 @@ static hipError_t dispatch_tile(int shape, GemmParams prm, LaunchCtx st) {
 }
 
 hipError_t launch_cgemm_bingroup(const GemmParams &prm, bool akf, bool bkf, LaunchCtx st);
+hipError_t launch_cgemm_bingroup_shifted(GemmParams prm, bool akf, bool bkf, LaunchCtx st);
 
 GemmSwitches read_gemm_switches() {
     GemmSwitches s;
@@ -599,6 +600,7 @@ static hipError_t launch_prepared(const Prepared &q, LaunchCtx st) {
     const GemmSwitches &sw = switches_of(st.sw);
     if (q.thin != Thin::none) return launch_cgemm_thin(prm, q.thin, st);
     if (q.bingroup) return launch_cgemm_bingroup(prm, q.akf, q.bkf, st);
+    if (q.shifted) return launch_cgemm_bingroup_shifted(prm, q.akf, q.bkf, st);
     if (q.split_alone) return launch_cgemm_split(prm, q.akf, q.bkf, q.vec, st);
     const int shape = pick_tile(sw, prm, q.vec);
     if (q.vec && shape == 3 && sw.tile < 0 && !sw.no_tail) {

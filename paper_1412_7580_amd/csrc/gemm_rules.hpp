@@ -123,12 +123,29 @@ inline int thin_k_rows(const GemmParams &p) {
     return rows < 1 ? 1 : rows > 8 ? 8 : (int)rows;
 }
 
+// Whether the four-bins-per-line kernel's form for any channel counts (cgemm_bingroup.hip) can run: runs of four
+// planes, and 32-bit offsets that reach 32 rows or 16 reduction steps.
+inline bool shifted_lines(const GemmParams &p, bool akf, bool bkf) {
+    auto reach = [&](double planes) { return planes * p.bins * 2 * sizeof(float) < 4294967296.0; };
+    auto whole = [](const FreqLayout &l, const float *ptr) { return l.tsh == 2 && ((size_t)ptr & 15) == 0; };
+    return whole(p.layA, p.A) && whole(p.layB, p.B) && whole(p.layC, p.C) && p.bins % (4 * kXcds) == 0 && p.c_cs == 1 &&
+           (akf || p.a_rs == 1) && (bkf || p.b_cs == 1) && reach(akf ? 32.0 * p.a_rs + 20 : 16.0 * p.a_cs + 36) &&
+           reach(bkf ? 32.0 * p.b_cs + 20 : 16.0 * p.b_rs + 36);
+}
+
+// It is behind where its 32x32 tiles save no padding of 64x64 ones and there are few (40 x 51 x 16 on 1632 bins 21.6 / 27.8
+// us, 256 x 46 x 12 53.8 / 61.8; 97 x 112 x 123 129 / 128, 176 x 229 x 26 403 / 330).
+inline bool shifted_pays(const GemmParams &p) {
+    return ((p.M + 31) / 32) * ((p.N + 31) / 32) < 4 * ((p.M + 63) / 64) * ((p.N + 63) / 64) || (p.M > 64 && p.N > 64);
+}
+
 // Kernel parameters of one contraction and the kernel variant it can use.
 struct Prepared {
     GemmParams prm;
     bool akf, bkf;     // the reduction index is the contiguous plane index of A / B
     bool vec;          // 16-byte gathers are possible
     bool bingroup;     // the four-bins-per-line kernel applies
+    bool shifted;      // its form for any channel counts does
     bool split;        // bound by the fp32 matrix cores: the bf16 kernel applies (cgemm_split.hip) ...
     bool split_alone;  // ... and in a launch of its own, too
     Thin thin;         // a side of at most four: the vector-unit kernels apply (cgemm_thin.hip)
@@ -165,6 +182,7 @@ inline hipError_t prepare(const GemmProblem &g, const GemmSwitches &sw, Prepared
     out->bingroup = out->vec && !sw.no_bingroup && A.lay.tsh == 2 && B.lay.tsh == 2 && g.layC.tsh == 2 &&
                     bins % (4 * kXcds) == 0 && (akf || A.rs == 1) && (bkf || B.cs == 1) && g.C_cs == 1 &&
                     g.C_rs % 4 == 0 && N % 4 == 0 && ((size_t)g.C & 15) == 0;
+    out->shifted = !out->vec && !sw.no_bingroup && sw.tile < 0 && shifted_lines(prm, akf, bkf) && shifted_pays(prm);
     const Thin form = thin_form(prm);
     out->thin = sw.no_thin || sw.tile >= 0 || !thin_pays(prm, form, bkf, out->vec, out->bingroup) ? Thin::none : form;
     out->split = !out->bingroup && (akf || !bkf) && !sw.no_split && sw.tile < 0 && split_pays(prm, akf, bkf, out->vec) && !narrow_tile(prm, out->vec);

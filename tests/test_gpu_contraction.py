@@ -174,3 +174,11 @@ def test_bf16_kernel_leaves_the_padding_bins_alone(hd, lib, side):
     ws.fill_(7.0)
     hd.fft_conv_fprop(x.cuda(), w.cuda(), ws=ws)
     assert (product[:, live:] == 7.0).all()
+
+
+# Channel counts that are no multiple of four on runs of four planes (bases 36 .. 64): sides around the 32x32 tile and the
+# K tile of 16, rows that start on every place of a line.  (S, f, fo, image side)
+@pytest.mark.parametrize("S,f,fo,side", [(33, 5, 7, 40), (31, 17, 33, 40), (5, 33, 65, 40), (66, 37, 70, 40), (1, 6, 9, 40),
+                                         (17, 1, 5, 40), (9, 15, 31, 35), (34, 18, 47, 46), (3, 66, 130, 55), (6, 31, 14, 63)])
+def test_any_channel_counts_on_runs_of_four(hd, S, f, fo, side):
+    _check(hd, S, f, fo, side, side, 3, 2)
