@@ -423,9 +423,9 @@ static hipError_t invert_pair(fftconv_ctx *c, const PassPlan &pb, const float *G
 
 // Contraction + inverse transform of one pass, operands already in the frequency domain.
 static hipError_t contract_and_invert(fftconv_ctx *c, const PassPlan &p, const float *AF, const float *BF,
-                                      float *CF, float *out, float scale, int accumulate) {
+                                      float *CF, float *out, float scale, int accumulate, const GemmProblem *partner = nullptr) {
     const GemmProblem g = gemm_problem(p, AF, BF, CF);
-    if (hipError_t e = launch_cgemm_bins(g, next_ctx(c, "contraction")); e != hipSuccess) return e;
+    if (hipError_t e = launch_cgemm_bins(g, next_ctx(c, "contraction"), partner); e != hipSuccess) return e;
     return invert(c, p, CF, out, scale, accumulate);
 }
 
@@ -913,19 +913,17 @@ static int backward_impl(fftconv_handle hd, const float *gy, float *gx, float *g
         }
     }
     // bprop: GX = GY . W ; accGrad: GW = conj(GY) . X  (operand A of both plans is GYF)
-    if (gx && gw) {
-        const GemmProblem qb = gemm_problem(pb, GYF, WF, GXF), qa = gemm_problem(pa, GYFa, XF, GWF);
-        if (cgemm_pair_supported(qb, qa, &hd->sw)) {
-            // both contractions in one launch, then the two inverse transforms
-            // (the one with the longer reduction first: its workgroups run longest)
-            const bool a_first = pa.K >= pb.K;
-            if ((e = launch_cgemm_pair(a_first ? qa : qb, a_first ? qb : qa, next_ctx(hd, "contraction.pair"))) != hipSuccess) return hip_fail(hd, e);
-            if ((e = invert_pair(hd, pb, GXF, gx, pa, GWF, gw, scale, accumulate)) != hipSuccess) return hip_fail(hd, e);
-            return FFTCONV_OK;
-        }
+    const GemmProblem qb = gemm_problem(pb, GYF, WF, GXF), qa = gemm_problem(pa, GYFa, XF, GWF);
+    if (gx && gw && cgemm_pair_supported(qb, qa, &hd->sw)) {
+        // both contractions in one launch, then the two inverse transforms
+        // (the one with the longer reduction first: its workgroups run longest)
+        const bool a_first = pa.K >= pb.K;
+        if ((e = launch_cgemm_pair(a_first ? qa : qb, a_first ? qb : qa, next_ctx(hd, "contraction.pair"))) != hipSuccess) return hip_fail(hd, e);
+        if ((e = invert_pair(hd, pb, GXF, gx, pa, GWF, gw, scale, accumulate)) != hipSuccess) return hip_fail(hd, e);
+        return FFTCONV_OK;
     }
-    if (gx && (e = contract_and_invert(hd, pb, GYF, WF, GXF, gx, 1.0f, 0)) != hipSuccess) return hip_fail(hd, e);
-    if (gw && (e = contract_and_invert(hd, pa, GYFa, XF, GWF, gw, scale, accumulate)) != hipSuccess) return hip_fail(hd, e);
+    if (gx && (e = contract_and_invert(hd, pb, GYF, WF, GXF, gx, 1.0f, 0, gw ? nullptr : &qa)) != hipSuccess) return hip_fail(hd, e);
+    if (gw && (e = contract_and_invert(hd, pa, GYFa, XF, GWF, gw, scale, accumulate, gx ? nullptr : &qb)) != hipSuccess) return hip_fail(hd, e);
     return FFTCONV_OK;
 }
 

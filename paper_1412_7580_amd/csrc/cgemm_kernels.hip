@@ -505,6 +505,14 @@ struct GemmPairParams {
     unsigned split2;   // p2's workgroups from this number on are cut into quadrants (as in
                        // cgemm_tail_kernel); equal to p2's workgroup count when none are
 };
+// bprop and accGrad (p1 is bprop if B_FIRST) with 4-byte gathers: channel counts that are no multiple of four.
+template <bool B_FIRST>
+__global__ void __launch_bounds__(256, 3) cgemm_scalar_pair_kernel(GemmPairParams pp) {
+    if ((blockIdx.x < pp.n1) == B_FIRST)
+        cgemm_bins_body<2, 2, 1, 1, 16, true, false, false, 1>(B_FIRST ? pp.p1 : pp.p2, B_FIRST ? blockIdx.x : blockIdx.x - pp.n1);
+    else
+        cgemm_bins_body<2, 2, 1, 1, 16, false, false, false, 1>(B_FIRST ? pp.p2 : pp.p1, B_FIRST ? blockIdx.x - pp.n1 : blockIdx.x);
+}
 template <bool AKF1, bool BKF1, bool AKF2, bool BKF2>
 __global__ void __launch_bounds__(256, 3) cgemm_pair_kernel(GemmPairParams pp) {
     if (blockIdx.x < pp.n1) {
@@ -566,6 +574,7 @@ GemmSwitches read_gemm_switches() {
     s.no_fast = on("FFTCONV_GEMM_NO_FAST");
     s.no_thin = on("FFTCONV_GEMM_NO_THIN");
     s.no_split = on("FFTCONV_GEMM_NO_SPLIT");
+    s.no_direct = on("FFTCONV_GEMM_NO_DIRECT");
     if (const char *e = getenv("FFTCONV_BG_TILE")) s.bg_tile = atoi(e);
     return s;
 }
@@ -599,6 +608,7 @@ static hipError_t launch_prepared(const Prepared &q, LaunchCtx st) {
     const GemmParams &prm = q.prm;
     const GemmSwitches &sw = switches_of(st.sw);
     if (q.thin != Thin::none) return launch_cgemm_thin(prm, q.thin, st);
+    if (q.direct_alone) return launch_cgemm_direct(prm, q.akf, q.bkf, st);
     if (q.bingroup) return launch_cgemm_bingroup(prm, q.akf, q.bkf, st);
     if (q.shifted) return launch_cgemm_bingroup_shifted(prm, q.akf, q.bkf, st);
     if (q.split_alone) return launch_cgemm_split(prm, q.akf, q.bkf, q.vec, st);
@@ -628,11 +638,6 @@ static hipError_t launch_prepared(const Prepared &q, LaunchCtx st) {
     return dispatch_tile<false, true, false>(shape, prm, st);
 }
 
-hipError_t launch_cgemm_bins(const GemmProblem &g, LaunchCtx st) {
-    Prepared q;
-    if (hipError_t e = prepare(g, switches_of(st.sw), &q); e != hipSuccess) return e;
-    return launch_prepared(q, st);
-}
 
 template <bool AKF1, bool BKF1, bool AKF2, bool BKF2>
 static hipError_t run_pair(GemmPairParams &pp, LaunchCtx st) {
@@ -659,6 +664,17 @@ static hipError_t run_pair(GemmPairParams &pp, LaunchCtx st) {
     return hipGetLastError();
 }
 
+static hipError_t run_scalar_pair(GemmPairParams &pp, bool b_first, LaunchCtx st) {
+    for (GemmParams *g : {&pp.p1, &pp.p2}) { g->tiles_m = (g->M + 63) / 64; g->tiles_n = (g->N + 63) / 64; }
+    const long n1 = (long)pp.p1.bins * pp.p1.tiles_m * pp.p1.tiles_n, n2 = (long)pp.p2.bins * pp.p2.tiles_m * pp.p2.tiles_n;
+    pp.n1 = (unsigned)n1;
+    pp.split2 = (unsigned)n2;
+    const size_t lds = (size_t)(4 * 16 * 66 + 4 * 16 * 66) * sizeof(float);
+    if (b_first) launch_kernel(cgemm_scalar_pair_kernel<true>, dim3((unsigned)(n1 + n2)), dim3(256), lds, st, pp);
+    else launch_kernel(cgemm_scalar_pair_kernel<false>, dim3((unsigned)(n1 + n2)), dim3(256), lds, st, pp);
+    return hipGetLastError();
+}
+
 template <bool AKF1, bool BKF1>
 static hipError_t pair_second(const Prepared &q2, GemmPairParams &pp, LaunchCtx st) {
     if (q2.akf && q2.bkf) return run_pair<AKF1, BKF1, true, true>(pp, st);
@@ -667,12 +683,36 @@ static hipError_t pair_second(const Prepared &q2, GemmPairParams &pp, LaunchCtx 
     return run_pair<AKF1, BKF1, false, true>(pp, st);
 }
 
+// The shared launch of bprop and accGrad that a layer takes.
+enum class Shared { none, direct, form, scalar };
+static Shared shared_launch(const Prepared &q1, const Prepared &q2, const GemmSwitches &sw) {
+    if (sw.tile < 0 && !sw.no_pair) {
+        const Prepared &b = q1.akf ? q1 : q2, &a = q1.akf ? q2 : q1;
+        if (q1.akf != q2.akf && direct_pair_pays(b, a)) return Shared::direct;
+        if (pair_form(q1, q2, sw) != Pair::none) return Shared::form;
+        if (q1.akf != q2.akf && scalar_pair_pays(b, a)) return Shared::scalar;
+    }
+    return Shared::none;
+}
+
 bool cgemm_pair_supported(const GemmProblem &g1, const GemmProblem &g2, const GemmSwitches *swp) {
     const GemmSwitches &sw = switches_of(swp);
     Prepared q1, q2;
     if (prepare(g1, sw, &q1) != hipSuccess) return false;
     if (prepare(g2, sw, &q2) != hipSuccess) return false;
-    return pair_form(q1, q2, sw) != Pair::none;
+    return shared_launch(q1, q2, sw) != Shared::none;
+}
+
+hipError_t launch_cgemm_bins(const GemmProblem &g, LaunchCtx st, const GemmProblem *partner) {
+    const GemmSwitches &sw = switches_of(st.sw);
+    Prepared q, o;
+    if (hipError_t e = prepare(g, sw, &q); e != hipSuccess) return e;
+    if (partner && prepare(*partner, sw, &o) == hipSuccess) {
+        const Shared how = shared_launch(q, o, sw);
+        if (how == Shared::direct) return launch_cgemm_direct(q.prm, q.akf, q.bkf, st, &o.prm);
+        if (how != Shared::none) q.direct_alone = false;
+    }
+    return launch_prepared(q, st);
 }
 
 hipError_t launch_cgemm_pair(const GemmProblem &g1, const GemmProblem &g2, LaunchCtx st) {
@@ -680,11 +720,13 @@ hipError_t launch_cgemm_pair(const GemmProblem &g1, const GemmProblem &g2, Launc
     const GemmSwitches &sw = switches_of(st.sw);
     if (hipError_t e = prepare(g1, sw, &q1); e != hipSuccess) return e;
     if (hipError_t e = prepare(g2, sw, &q2); e != hipSuccess) return e;
-    const Pair form = pair_form(q1, q2, sw);
-    if (form == Pair::none) return hipErrorInvalidValue;
-    if (form == Pair::split) return launch_cgemm_split_pair(q1.prm, q1.akf, q2.prm, st);
+    const Shared how = shared_launch(q1, q2, sw);
+    if (how == Shared::none) return hipErrorInvalidValue;
+    if (how == Shared::direct) return launch_cgemm_direct_pair((q1.akf ? q1 : q2).prm, (q1.akf ? q2 : q1).prm, st);
     GemmPairParams pp;
     pp.p1 = q1.prm; pp.p2 = q2.prm; pp.n1 = 0;
+    if (how == Shared::scalar) return run_scalar_pair(pp, q1.akf, st);
+    if (pair_form(q1, q2, sw) == Pair::split) return launch_cgemm_split_pair(q1.prm, q1.akf, q2.prm, st);
     if (q1.akf && q1.bkf) return pair_second<true, true>(q2, pp, st);
     if (q1.akf && !q1.bkf) return pair_second<true, false>(q2, pp, st);
     if (!q1.akf && !q1.bkf) return pair_second<false, false>(q2, pp, st);

@@ -27,6 +27,11 @@ __device__ __forceinline__ float flip(float v, unsigned sign) {
 hipError_t launch_cgemm_split(GemmParams prm, bool akf, bool bkf, bool vec, LaunchCtx st);
 hipError_t launch_cgemm_split_pair(const GemmParams &p1, bool akf1, const GemmParams &p2, LaunchCtx st);
 
+// Contractions with a narrow side or few tiles (cgemm_direct.hip).  partner: the other product of the shared launch that
+// this one is to agree with bit for bit.
+hipError_t launch_cgemm_direct(GemmParams prm, bool akf, bool bkf, LaunchCtx st, const GemmParams *partner = nullptr);
+hipError_t launch_cgemm_direct_pair(const GemmParams &bprop, const GemmParams &accgrad, LaunchCtx st);
+
 // Contractions with a side of at most four (cgemm_thin.hip), in one of three forms (thin_form()).
 enum class Thin { none, k, n, acc };
 hipError_t launch_cgemm_thin(const GemmParams &prm, Thin form, LaunchCtx st);

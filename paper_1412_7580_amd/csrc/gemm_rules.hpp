@@ -139,6 +139,17 @@ inline bool shifted_pays(const GemmParams &p) {
     return ((p.M + 31) / 32) * ((p.N + 31) / 32) < 4 * ((p.M + 63) / 64) * ((p.N + 63) / 64) || (p.M > 64 && p.N > 64);
 }
 
+// Whether the kernel that splits the reduction over waves (cgemm_direct.hip) can run: runs of at least a quad, and
+// 32-bit offsets that reach 32 rows and the reduction of an operand whose reduction index is contiguous, 64 rows and
+// eight reduction steps of the others, 32 rows of the result.
+inline bool direct_fits(const GemmParams &p, bool akf, bool bkf) {
+    auto reach = [&](double planes) { return planes * p.bins * 2 * sizeof(float) < 4294967296.0; };
+    const long T = 1L << p.layA.tsh;
+    return p.layA.tsh >= 2 && p.layA.tsh == p.layB.tsh && p.layA.tsh == p.layC.tsh && p.c_cs == 1 && (akf || p.a_rs == 1) &&
+           (bkf || p.b_cs == 1) && reach(akf ? 32.0 * p.a_rs + p.K + T : 64 + 8.0 * p.a_cs + T) &&
+           reach(bkf ? 32.0 * p.b_cs + p.K + T : 64 + 8.0 * p.b_rs + T) && reach(32.0 * p.c_rs + 32 + T);
+}
+
 // Kernel parameters of one contraction and the kernel variant it can use.
 struct Prepared {
     GemmParams prm;
@@ -146,10 +157,28 @@ struct Prepared {
     bool vec;          // 16-byte gathers are possible
     bool bingroup;     // the four-bins-per-line kernel applies
     bool shifted;      // its form for any channel counts does
+    bool direct;       // the kernel that splits the reduction over waves can run ...
+    bool direct_alone; // ... and is the fastest in a launch of its own
     bool split;        // bound by the fp32 matrix cores: the bf16 kernel applies (cgemm_split.hip) ...
     bool split_alone;  // ... and in a launch of its own, too
     Thin thin;         // a side of at most four: the vector-unit kernels apply (cgemm_thin.hip)
 };
+
+// 32x32 tiles with the reduction split over waves (cgemm_direct.hip) in a launch of its own, over 1100 products of random layers
+// against 64x64 and narrow tiles, whose few workgroups each walk alone over a long reduction: 16 x 6 x 6832 on 544 bins 1486 -> ~130 us, 2 x 32 x
+// 277 on 40 bins 28.9 -> 9.2, 16 x 16 x 192 on 112 bins 18.5 -> 7.6.  Not for two chunks of reduction or less (5 x 32 x
+// 8: 4.0 / 9.5), nor with runs of four planes, where whole lines are worth more (5 x 248 x 176 on 864 bins 82 / 124), nor
+// what the bf16 cores do.  A tile of 32 reads its operands for half as many products, so a side above 32 (64 on runs of 32
+// and more, whose lines a strip uses whole) stays with 64x64 tiles (48 x 304 x 57 on 544 bins 50 / 68), and so do, unless the
+// tile of 64 would be half padding, grids of 32 tiles and more to a reduction step (9 x 256 x 32 on 312 bins 12.3 / 16.8), of 128
+// where the other kernel's gathers are of 4 bytes or runs of eight planes (1134 x 8 x 32 on 544 bins 63 / 83).
+inline long tiles_32(const GemmParams &p) { return (long)p.bins * ((p.M + 31) / 32) * ((p.N + 31) / 32); }
+inline bool direct_pays(const Prepared &q) {
+    const GemmParams &p = q.prm;
+    if (q.split || p.layA.tsh < 3 || p.K <= 16) return false;
+    if ((p.M < p.N ? p.M : p.N) > (p.layA.tsh >= 5 ? 64 : 32)) return false;
+    return tiles_32(p) == tiles_64(p) || tiles_32(p) < (q.vec && p.layA.tsh >= 4 ? 32L : 128L) * p.K;
+}
 
 inline hipError_t prepare(const GemmProblem &g, const GemmSwitches &sw, Prepared *out) {
     const GemmOperand &A = g.A, &B = g.B;
@@ -187,6 +216,8 @@ inline hipError_t prepare(const GemmProblem &g, const GemmSwitches &sw, Prepared
     out->thin = sw.no_thin || sw.tile >= 0 || !thin_pays(prm, form, bkf, out->vec, out->bingroup) ? Thin::none : form;
     out->split = !out->bingroup && (akf || !bkf) && !sw.no_split && sw.tile < 0 && split_pays(prm, akf, bkf, out->vec) && !narrow_tile(prm, out->vec);
     out->split_alone = out->split && split_alone_pays(prm, akf, out->vec);
+    out->direct = direct_fits(prm, akf, bkf) && sw.tile < 0 && !sw.no_direct;
+    out->direct_alone = out->direct && out->thin == Thin::none && direct_pays(*out);
     return hipSuccess;
 }
 
@@ -223,6 +254,31 @@ inline bool shared_launch_pays(const Prepared &b, const Prepared &a) {
     if (a.prm.K == 1) return (double)a.prm.bins * a.prm.M * a.prm.N < 1.4e7;
     const double lost = lost_in_shared_tiles(a);
     return lost == 0 || lost + lost_in_shared_tiles(b) < 12 + 0.03 * b.prm.K;
+}
+
+// bprop and accGrad as one launch of the kernel that splits the reduction, where 64x64 tiles would be about half padding (over
+// 700 random layers, against the best of the other ways; us a backward pass).  Channel counts that are no multiple of four, with a
+// reduction of more than two chunks: 22 samples, 16 -> 311, 14x14 39.8 / 30.0, 1 x 86 -> 14, 65x65 38.1 / 28.5; fuller tiles
+// are behind (3 x 304 -> 207, 21x21 179 / 218) but with runs of 32 and more, whose lines a strip uses whole.  With runs of four planes up to
+// 6000 tiles (7 x 16 -> 6, 75x75 41.2 / 37.9; 8 x 359 -> 13, 87x87 256 / 345).  Multiples of four: from 48 steps on (6 x 16 -> 304,
+// 14x14 40.2 / 26.5; 5 x 368 -> 24, 14x14, 24 steps 29.0 / 31.4).
+inline bool direct_pair_pays(const Prepared &b, const Prepared &a) {
+    if (!b.direct || !a.direct || b.thin != Thin::none || a.thin != Thin::none) return false;
+    if (!b.akf || b.bkf || a.akf || a.bkf) return false;
+    const int tsh = b.prm.layA.tsh, K = b.prm.K > a.prm.K ? b.prm.K : a.prm.K;
+    const long t64 = tiles_64(b.prm) + tiles_64(a.prm);
+    const bool padded = tiles_32(b.prm) + tiles_32(a.prm) <= 2.2 * t64;
+    if (tsh == 2) return b.shifted && a.shifted && padded && t64 < 6000;
+    if (!b.vec || !a.vec) return K > 16 && (padded || (tsh >= 5 && !a.split));
+    return K >= 48 && padded && !a.split && !b.split;
+}
+
+// The two as one launch of 64x64 tiles with 4-byte gathers: 50 random layers a quarter faster in the mean than two launches for
+// the products and two for the inverse transforms (9 samples, 80 -> 38, 15x15 35.8 / 24.1 us a backward pass, 14 x 41 -> 112, 81x81
+// 193 / 158).
+inline bool scalar_pair_pays(const Prepared &b, const Prepared &a) {
+    return !(b.vec && a.vec) && b.akf && !b.bkf && !a.akf && !a.bkf && b.prm.layA.tsh >= 3 && !a.split && !b.split &&
+           b.thin == Thin::none && a.thin == Thin::none;
 }
 
 // Two contractions in one launch: bprop and accGrad of a layer, which share operand A and neither of

@@ -10,12 +10,12 @@ namespace fc {
 // that one dispatch (their elapsed time is the kernel's own execution time, without the gaps
 // that events recorded between launches would include).
 // Switches of the contraction for A/B runs (environment variables FFTCONV_GEMM_TILE, _NO_TAIL,
-// _NO_PAIR, _NO_BINGROUP, _NO_FAST, _NO_THIN, _NO_SPLIT and FFTCONV_BG_TILE), read once when a handle is
+// _NO_PAIR, _NO_BINGROUP, _NO_FAST, _NO_THIN, _NO_SPLIT, _NO_DIRECT and FFTCONV_BG_TILE), read once when a handle is
 // created; none changes a result beyond rounding.  All off by default.
 struct GemmSwitches {
     int tile = -1;          // 0..7: this tile shape of the fp32 kernel, in launches of their own, for all
                             // layers but those of the four-bins-per-line kernel; -1: the library's choice
-    bool no_tail = false, no_pair = false, no_bingroup = false, no_fast = false, no_thin = false, no_split = false;
+    bool no_tail = false, no_pair = false, no_bingroup = false, no_fast = false, no_thin = false, no_split = false, no_direct = false;
     int bg_tile = 0;        // per-wave tile of the four-bins-per-line kernel
 };
 GemmSwitches read_gemm_switches();
@@ -181,7 +181,9 @@ struct GemmProblem {
     long C_rs, C_cs;
     int M, N, K, bins, live;
 };
-hipError_t launch_cgemm_bins(const GemmProblem &g, LaunchCtx st);
+// partner: the other product of a backward pass that asks for one gradient only.  The one that is computed then sums in
+// the order of the shared launch, so that it is the same bits with and without the other (but for split tails).
+hipError_t launch_cgemm_bins(const GemmProblem &g, LaunchCtx st, const GemmProblem *partner = nullptr);
 
 // Two independent contractions in one launch (see cgemm_pair_kernel).  Possible when both
 // can use 16-byte gathers and neither is a case for the four-bins-per-line kernel.

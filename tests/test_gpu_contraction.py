@@ -182,3 +182,41 @@ def test_bf16_kernel_leaves_the_padding_bins_alone(hd, lib, side):
                                          (17, 1, 5, 40), (9, 15, 31, 35), (34, 18, 47, 46), (3, 66, 130, 55), (6, 31, 14, 63)])
 def test_any_channel_counts_on_runs_of_four(hd, S, f, fo, side):
     _check(hd, S, f, fo, side, side, 3, 2)
+
+
+# Long reductions with a narrow side or few tiles: one chunk of eight steps more or less than the waves, every layout's
+# run, both gradients in one launch, strides on and off the quad and the run.  (S, f, fo, image side)
+SPLIT = [(300, 5, 6, 8), (140, 8, 12, 8), (9, 132, 31, 8), (131, 7, 9, 13), (129, 16, 20, 13), (6, 16, 304, 14), (33, 13, 140, 20),
+         (4, 200, 6, 20), (200, 16, 12, 20), (17, 18, 17, 20), (25, 24, 30, 20), (5, 6, 150, 32), (160, 8, 16, 32), (33, 31, 97, 32),
+         (1, 69, 2, 13), (65, 65, 64, 13), (7, 16, 6, 40), (40, 33, 5, 13)]
+
+
+@pytest.mark.parametrize("S,f,fo,side", SPLIT)
+def test_reduction_split_over_waves(hd, S, f, fo, side):
+    _check(hd, S, f, fo, side, side, 3, 2)
+
+
+@pytest.mark.parametrize("S,f,fo,side", EDGES + SPLIT[::3])
+def test_the_kernels_that_these_replace_on_some_layers(lib, S, f, fo, side, monkeypatch):
+    """With the split reductions switched off their layers run on the tiles that other layers still take."""
+    monkeypatch.setenv("FFTCONV_GEMM_NO_DIRECT", "1")
+    h = lib.Handle(0)
+    try:
+        _check(h, S, f, fo, side, side, 3, 2)
+    finally:
+        h.close()
+
+
+@pytest.mark.parametrize("S,f,fo,side,k", [(70, 5, 6, 13, 3), (33, 13, 140, 20, 3), (129, 16, 20, 13, 3), (4, 72, 68, 9, 3), (20, 33, 70, 20, 3)])
+def test_a_gradient_alone_is_the_same_bits(hd, S, f, fo, side, k):
+    """Asking for one gradient only gives what asking for both gives, whatever launch both share."""
+    import torch
+    g = torch.Generator().manual_seed(8)
+    o = side - k + 1
+    x, w = torch.randn(S, f, side, side, generator=g).cuda(), torch.randn(fo, f, k, k, generator=g).cuda()
+    gy = torch.randn(S, fo, o, o, generator=g).cuda()
+    saved = torch.empty(hd.saved_bytes(S, f, fo, side, side, k, k) // 4, device="cuda")
+    hd.fft_conv_fprop_save(x, w, saved)
+    gx, gw = hd.fft_conv_backward(gy, saved, f, side, side, k, k)
+    assert torch.equal(hd.fft_conv_backward(gy, saved, f, side, side, k, k, want_gw=False)[0], gx)
+    assert torch.equal(hd.fft_conv_backward(gy, saved, f, side, side, k, k, want_gx=False)[1], gw)
