@@ -10,8 +10,8 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libfftconv.so")
 SOURCES = ["api.hip", "fft_kernels.hip", "fft_kernels_mixed_small.hip", "fft_kernels_mixed_large.hip", "fft1d_mixed.hip",
-           "fft_kernels_natural.hip", "fft_rect_fwd.hip", "fft_rect_inv.hip", "fused_small.hip", "cgemm_kernels.hip", "cgemm_bingroup.hip", "cgemm_thin.hip", "cgemm_direct.hip", "cgemm_split.hip"]
-HEADERS = ["fft_core.hpp", "fft_kernels_impl.hpp", "fft_rect_impl.hpp", "kernels.hpp", "gemm_params.hpp", "gemm_rules.hpp", "bf16_split.hpp", os.path.join("..", "..", "include", "fftconv.h")]
+           "fft_kernels_natural.hip", "fft_rect_fwd.hip", "fft_rect_inv.hip", "fft_thin_inv.hip", "fused_small.hip", "cgemm_kernels.hip", "cgemm_bingroup.hip", "cgemm_thin.hip", "cgemm_direct.hip", "cgemm_split.hip"]
+HEADERS = ["fft_core.hpp", "fft_kernels_impl.hpp", "fft_rect_impl.hpp", "kernels.hpp", "thin.hpp", "gemm_params.hpp", "gemm_rules.hpp", "bf16_split.hpp", os.path.join("..", "..", "include", "fftconv.h")]
 FLAGS = [
     "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -425,6 +425,13 @@ static hipError_t invert_pair(fftconv_ctx *c, const PassPlan &pb, const float *G
 static hipError_t contract_and_invert(fftconv_ctx *c, const PassPlan &p, const float *AF, const float *BF,
                                       float *CF, float *out, float scale, int accumulate, const GemmProblem *partner = nullptr) {
     const GemmProblem g = gemm_problem(p, AF, BF, CF);
+    if (!p.rect) {                             // a product of at most four terms: inside the inverse transform
+        const int nk = c->nk;
+        const hipError_t e = launch_product_inverse(g, out, p.N, p.hC, p.wC, scale / ((float)p.N * (float)p.N), accumulate != 0,
+                                                    next_ctx(c, "contraction.ifft"), p.viewC ? &p.vC : nullptr);
+        if (e != hipErrorNotSupported) return e;
+        c->nk = nk;                            // nothing was launched: give the event pair back
+    }
     if (hipError_t e = launch_cgemm_bins(g, next_ctx(c, "contraction"), partner); e != hipSuccess) return e;
     return invert(c, p, CF, out, scale, accumulate);
 }

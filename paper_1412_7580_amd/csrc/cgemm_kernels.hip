@@ -639,6 +639,15 @@ static hipError_t launch_prepared(const Prepared &q, LaunchCtx st) {
 }
 
 
+hipError_t launch_product_inverse(const GemmProblem &g, float *out, int N, int h_out, int w_out, float scale,
+                                  bool accumulate, LaunchCtx st, const PlaneView *view) {
+    const GemmSwitches &sw = switches_of(st.sw);
+    Prepared q;
+    if (hipError_t e = prepare(g, sw, &q); e != hipSuccess) return e;
+    if (!product_inverse_pays(q, N)) return hipErrorNotSupported;
+    return launch_fft2d_c2r_product(q.prm, out, N, h_out, w_out, scale, accumulate, st, view);
+}
+
 template <bool AKF1, bool BKF1, bool AKF2, bool BKF2>
 static hipError_t run_pair(GemmPairParams &pp, LaunchCtx st) {
     constexpr int TM = 64, TN = 64, TK = 16;

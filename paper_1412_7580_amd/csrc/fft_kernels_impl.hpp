@@ -589,9 +589,12 @@ struct Inv2dParams {
 // max(T * MPS float2, T * h_out * w_out + 3 floats) of LDS, which this function uses.
 // tid_sub: as for the forward body (threads of a larger workgroup beyond the BT that do the work call
 // with a plan of no planes and still pass the barriers).
-template <int L, int G, int T, bool CONV, bool ISTAGE, bool PRE = false>
+// SRC: with ISTAGE, src.fill<N, T, BT>(image, p0, np, tid) puts the block's input into LDS in place of the
+// copy of a stored tile.
+struct StoredTile {};
+template <int L, int G, int T, bool CONV, bool ISTAGE, bool PRE = false, class SRC = StoredTile>
 __device__ __forceinline__ void fft2d_c2r_body(const Inv2dParams &prm, unsigned block, const float *pre_img = nullptr,
-                                               int tid_sub = -1) {
+                                               int tid_sub = -1, const SRC &src = SRC()) {
     static_assert(!PRE || (CONV && !ISTAGE), "a preloaded tile is in the plane-tiled layout and needs no staging");
     constexpr int N = L * G, NH = N / 2, NB = NH + 1, BT = T * NH * G;
     typedef MidLayout<L, G> ML;
@@ -620,7 +623,9 @@ __device__ __forceinline__ void fft2d_c2r_body(const Inv2dParams &prm, unsigned 
             if constexpr (!ISTAGE) __syncthreads();   // (the staging below ends with a barrier)
         }
         if constexpr (ISTAGE) {
-            if constexpr (CONV)   // whole tile (its padding planes are simply not used)
+            if constexpr (!std::is_same<SRC, StoredTile>::value)
+                src.template fill<N, T, BT>(smem, p0, np, tid);
+            else if constexpr (CONV)   // whole tile (its padding planes are simply not used)
                 stage_linear<BT>(smem, prm.in + prm.lay.index(p0, 0, 0), (unsigned)T * N * NB * 2, tid,
                                  prm.in_vec_ok != 0);
             else

@@ -35,6 +35,9 @@ hipError_t launch_cgemm_direct_pair(const GemmParams &bprop, const GemmParams &a
 // Contractions with a side of at most four (cgemm_thin.hip), in one of three forms (thin_form()).
 enum class Thin { none, k, n, acc };
 hipError_t launch_cgemm_thin(const GemmParams &prm, Thin form, LaunchCtx st);
+// The k form's product as the input of the inverse transform (fft_thin_inv.hip).
+hipError_t launch_fft2d_c2r_product(const GemmParams &g, float *out, int N, int h_out, int w_out, float scale,
+                                    bool accumulate, LaunchCtx st, const PlaneView *view);
 
 constexpr int kXcds = 8;   // workgroup i is placed on XCD i % kXcds
 

@@ -221,6 +221,17 @@ inline hipError_t prepare(const GemmProblem &g, const GemmSwitches &sw, Prepared
     return hipSuccess;
 }
 
+// The k form's product formed inside the inverse transform of its result (fft_thin_inv.hip): the result is neither written
+// nor read back, its operands are read from the caches once per four planes.  us of fprop, two kernels / one: up to basis 24,
+// where a launch counts, 64 x 3 -> 384, 13x13 27.5 / 17.6, 16 x 4 -> 16, 8x8 13.7 / 11.1; above with three terms or fewer and a
+// few rounds of workgroups, 128 x 3 -> 64, 28x28 39.2 / 30.8, 56x56 75.8 / 72.8, 64 x 2 -> 20, 56x56 36.8 / 31.5, but 8 x 3 -> 16,
+// 56x56 22.8 / 24.0; a fourth term's loads cost more than the trip (128 x 4 -> 64, 56x56 79.7 / 87.7, 16 x 4 -> 16, 28x28 22.2 /
+// 25.5), and basis 64's tile leaves the fewest workgroups to hide them (128 x 3 -> 64 100 / 135).
+inline bool product_inverse_pays(const Prepared &q, int basis) {
+    if (q.thin != Thin::k || basis > 56) return false;
+    return basis <= 24 || (q.prm.K <= 3 && (long)q.prm.M * q.prm.N >= 1024);
+}
+
 // But for narrow sides, 64x64 tiles on four waves with one tile of register staging ahead (shape 3)
 // measured fastest of the fp32 kernel's shapes for every layer tried (more workgroups in flight beat
 // the larger tiles' operand reuse and the deeper staging's registers).

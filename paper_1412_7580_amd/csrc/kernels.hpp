@@ -185,6 +185,12 @@ struct GemmProblem {
 // the order of the shared launch, so that it is the same bits with and without the other (but for split tails).
 hipError_t launch_cgemm_bins(const GemmProblem &g, LaunchCtx st, const GemmProblem *partner = nullptr);
 
+// A contraction whose reduction has at most four terms as the input of the inverse transform (square bases up
+// to 64): the product never stands in memory.  hipErrorNotSupported, with nothing launched, where it does not apply or
+// is not the faster way.  `out` and `view` as launch_fft2d_c2r has them.
+hipError_t launch_product_inverse(const GemmProblem &g, float *out, int N, int h_out, int w_out, float scale,
+                                  bool accumulate, LaunchCtx st, const PlaneView *view);
+
 // Two independent contractions in one launch (see cgemm_pair_kernel).  Possible when both
 // can use 16-byte gathers and neither is a case for the four-bins-per-line kernel.
 bool cgemm_pair_supported(const GemmProblem &g1, const GemmProblem &g2, const GemmSwitches *sw = nullptr);

@@ -14,11 +14,11 @@ static bool problem(const long *v, long off, Prepared *q) {
 }
 
 extern "C" {
-// out: shifted lines, split reduction possible, split reduction alone
-int split_single(const long *v, long off, int *out) {
+// out: shifted lines, split reduction possible, split reduction alone, product inside the inverse transform of `basis`
+int split_single(const long *v, long off, int basis, int *out) {
     Prepared q;
     if (!problem(v, off, &q)) return -1;
-    out[0] = q.shifted; out[1] = q.direct; out[2] = q.direct_alone;
+    out[0] = q.shifted; out[1] = q.direct; out[2] = q.direct_alone; out[3] = product_inverse_pays(q, basis);
     return 0;
 }
 // out: the split reduction's shared launch, 64x64 tiles with 4-byte gathers

@@ -1,4 +1,5 @@
-"""Which layers take the contraction kernels that split the reduction over waves or shift lines of four planes: the library's own rules asked on the CPU, on both sides of each line."""
+"""Which layers take the contraction kernels that split the reduction over waves, shift lines of four planes or form the
+product inside the inverse transform: the library's own rules asked on the CPU, on both sides of each line."""
 import ctypes
 import os
 import subprocess
@@ -23,9 +24,9 @@ class Rules:
 
     def single(self, pass_, S, f, fo, h, k, offset=0):
         d = pkg.describe_plan(PASSES[pass_], S, f, fo, h, h, k, k)
-        out = (ctypes.c_int * 3)()
-        assert self._lib.split_single(self._matrix(d), ctypes.c_long(offset), out) == 0
-        return dict(zip(("shifted", "possible", "split"), map(bool, out)))
+        out = (ctypes.c_int * 4)()
+        assert self._lib.split_single(self._matrix(d), ctypes.c_long(offset), d["Nr"], out) == 0
+        return dict(zip(("shifted", "possible", "split", "product"), map(bool, out)))
 
     def pair(self, S, f, fo, h, k):
         b, a = (self._matrix(pkg.describe_plan(p, S, f, fo, h, h, k, k)) for p in (pkg.BPROP, pkg.ACCGRAD))
@@ -78,3 +79,11 @@ def test_shared_launches(rules):
     assert rules.pair(6, 16, 304, 14, 3) == "split" and rules.pair(5, 368, 24, 14, 7) is None
     assert rules.pair(128, 64, 64, 27, 5) is None and rules.pair(16, 4, 16, 13, 3) is None
     assert rules.pair(4, 6, 5, 27, 5) == "scalar"                # reductions of one chunk
+
+
+def test_product_inside_the_inverse_transform(rules):
+    product = lambda p, *layer: rules.single(p, *layer)["product"]
+    assert product("fprop", 64, 3, 384, 13, 3) and product("fprop", 16, 4, 16, 20, 3) and product("fprop", 128, 3, 96, 128, 11)
+    assert product("bprop", 64, 384, 3, 28, 5) and product("fprop", 64, 1, 32, 56, 7)
+    assert not product("fprop", 8, 3, 16, 56, 7) and not product("fprop", 128, 4, 64, 56, 5)
+    assert not product("fprop", 128, 3, 64, 64, 7) and not product("fprop", 128, 5, 64, 13, 3)

@@ -220,3 +220,20 @@ def test_a_gradient_alone_is_the_same_bits(hd, S, f, fo, side, k):
     gx, gw = hd.fft_conv_backward(gy, saved, f, side, side, k, k)
     assert torch.equal(hd.fft_conv_backward(gy, saved, f, side, side, k, k, want_gw=False)[0], gx)
     assert torch.equal(hd.fft_conv_backward(gy, saved, f, side, side, k, k, want_gx=False)[1], gw)
+
+
+# Products of at most four terms formed inside the inverse transform: every basis that has the kernel, one .. four terms
+# from either operand's layout, quads of columns that start in the middle of a run, a ragged last tile, windows.
+@pytest.mark.parametrize("side", [8, 10, 12, 14, 16, 18, 20, 24, 28, 32, 36, 40, 48, 56])
+def test_product_inside_the_inverse_transform(hd, side):
+    big = side > 24
+    for S, f, fo in ((43, 3, 20), (9, 2, 12), (6, 20, 2), (5, 1, 4)) if not big else ((53, 3, 20), (86, 1, 12), (260, 12, 2)):
+        _check(hd, S, f, fo, side, side, 3, 2)
+    if not big:
+        _check(hd, 3, 4, 24, side, side, 3, 2)
+        _check(hd, 5, 28, 3, side, side, 3, 3)
+
+
+@pytest.mark.parametrize("S,f,fo,side", [(2, 3, 12, 150), (1, 12, 3, 150), (19, 3, 64, 70)])
+def test_product_inside_the_inverse_transform_of_windows(hd, S, f, fo, side):
+    _check(hd, S, f, fo, side, side - 9, 5, 4)
