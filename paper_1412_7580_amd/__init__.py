@@ -12,6 +12,7 @@ import os
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIBPATH = os.path.join(_HERE, "libfftconv.so")
 _lib = None
+torch = None          # imported by load_library(), so that importing this package alone does not
 
 SYMBOLS = [
     "fftconv_create", "fftconv_destroy", "fftconv_set_stream", "fftconv_status_string",
@@ -39,7 +40,7 @@ class FFTConvError(RuntimeError):
 
 def load_library():
     """dlopen libfftconv.so (building it first only if it does not exist) and set prototypes."""
-    global _lib
+    global _lib, torch
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIBPATH):
@@ -47,7 +48,8 @@ def load_library():
         _build.build(force=True)
     # torch ships its own HIP runtime; import it first so that the library binds to the same
     # runtime instance that owns the tensors and streams it is handed.
-    import torch  # noqa: F401
+    import torch as _torch
+    torch = _torch
     lib = ctypes.CDLL(_LIBPATH)
     vp, i, l, f, sz = ctypes.c_void_p, ctypes.c_int, ctypes.c_long, ctypes.c_float, ctypes.c_size_t
     lib.fftconv_create.argtypes = [ctypes.POINTER(vp), i]
@@ -124,7 +126,6 @@ def _check(rc: int, what: str):
 
 
 def _dev_f32(t, name):
-    import torch
     if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == torch.float32 and t.is_contiguous()):
         raise FFTConvError(f"{name} must be a contiguous float32 tensor in device memory")
     return t.data_ptr()
@@ -161,6 +162,7 @@ class Handle:
         import torch
         if not torch.cuda.is_available():
             raise FFTConvError("no GPU visible: the HIP library cannot run (there is no CPU fallback)")
+        torch.cuda.init()
         self._lib = load_library()
         self._h = ctypes.c_void_p()
         _check(self._lib.fftconv_create(ctypes.byref(self._h), device), "fftconv_create")
@@ -179,8 +181,9 @@ class Handle:
             pass
 
     def _sync_stream(self):
-        import torch
-        s = torch.cuda.current_stream().cuda_stream
+        # The current device's current stream by its raw handle: torch.cuda.current_stream() builds a Stream object
+        # for it, 2.8 us of the 7.2 that a one-kernel call took (the launch itself is 2.6); this is 0.2.
+        s = torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         if s != self._stream:          # the handle keeps its stream: tell it only about changes
             _check(self._lib.fftconv_set_stream(self._h, ctypes.c_void_p(s)), "fftconv_set_stream")
             self._stream = s
@@ -215,7 +218,6 @@ class Handle:
 
     # ---- convolution passes -------------------------------------------------------------
     def fft_conv_fprop(self, x, wt, y=None, ws=None):
-        import torch
         S, f, h, w = x.shape
         fo, f2, kh, kw = wt.shape
         if f2 != f:
@@ -245,7 +247,6 @@ class Handle:
     def fft_conv_fprop_save(self, x, wt, saved, y=None, ws=None):
         """fprop that also leaves the transforms of x and wt in `saved` (a float32 device tensor
         of at least saved_bytes() bytes) for fft_conv_backward."""
-        import torch
         S, f, h, w = x.shape
         fo, f2, kh, kw = wt.shape
         if f2 != f:
@@ -261,7 +262,6 @@ class Handle:
     def fft_conv_backward(self, gy, saved, f, h, w, kh, kw, gx=None, gw=None, want_gx=True, want_gw=True,
                           scale=1.0, accumulate=False, ws=None):
         """bprop and accGrad of one layer from gy and the transforms saved by fft_conv_fprop_save."""
-        import torch
         S, fo, oh, ow = gy.shape
         if oh != h - kh + 1 or ow != w - kw + 1:
             raise FFTConvError("gy and (h, w, kh, kw) disagree")
@@ -280,7 +280,6 @@ class Handle:
         return gx, gw
 
     def fft_conv_bprop(self, gy, wt, h, w, gx=None, ws=None):
-        import torch
         S, fo, oh, ow = gy.shape
         fo2, f, kh, kw = wt.shape
         if fo2 != fo or oh != h - kh + 1 or ow != w - kw + 1:
@@ -293,7 +292,6 @@ class Handle:
         return gx
 
     def fft_conv_accgrad(self, x, gy, gw=None, scale=1.0, accumulate=False, ws=None):
-        import torch
         S, f, h, w = x.shape
         S2, fo, oh, ow = gy.shape
         if S2 != S:
@@ -325,7 +323,6 @@ class Handle:
         return nr.value, nc.value, bool(rc)
 
     def fft_conv_fprop_tiled(self, x, wt, tile_n, y=None, ws=None):
-        import torch
         S, f, h, w = x.shape
         fo, f2, kh, kw = wt.shape
         if f2 != f:
@@ -339,7 +336,6 @@ class Handle:
         return y
 
     def fft_conv_bprop_tiled(self, gy, wt, h, w, tile_n, gx=None, ws=None):
-        import torch
         S, fo, oh, ow = gy.shape
         fo2, f, kh, kw = wt.shape
         if fo2 != fo or oh != h - kh + 1 or ow != w - kw + 1:
@@ -353,7 +349,6 @@ class Handle:
         return gx
 
     def fft_conv_accgrad_tiled(self, x, gy, tile_n, gw=None, scale=1.0, accumulate=False, ws=None):
-        import torch
         S, f, h, w = x.shape
         S2, fo, oh, ow = gy.shape
         if S2 != S:
@@ -371,7 +366,6 @@ class Handle:
 
     def autotune_basis(self, x, wt, gy, y=None, gx=None, gw=None, reps=3):
         """Times the three passes at every candidate basis; returns (basis, ms of the three passes)."""
-        import torch
         S, f, h, w = x.shape
         fo, f2, kh, kw = wt.shape
         if f2 != f or tuple(gy.shape) != (S, fo, h - kh + 1, w - kw + 1):
@@ -394,7 +388,6 @@ class Handle:
         return int(self._lib.fftconv_backward_workspace_bytes_tiled(S, f, fo, h, w, kh, kw, tile_n))
 
     def fft_conv_fprop_save_tiled(self, x, wt, tile_n, saved, y=None, ws=None):
-        import torch
         S, f, h, w = x.shape
         fo, f2, kh, kw = wt.shape
         if f2 != f:
@@ -409,7 +402,6 @@ class Handle:
 
     def fft_conv_backward_tiled(self, gy, saved, f, h, w, kh, kw, tile_n, gx=None, gw=None, want_gx=True,
                                 want_gw=True, scale=1.0, accumulate=False, ws=None):
-        import torch
         S, fo, oh, ow = gy.shape
         if oh != h - kh + 1 or ow != w - kw + 1:
             raise FFTConvError("gy and (h, w, kh, kw) disagree")
@@ -434,7 +426,6 @@ class Handle:
 
     def fft_conv_transform_weights(self, wt, h, w, pad_h=0, pad_w=0, wf=None):
         """Transform of wt for layers of h x w images; returns the (float32 device) buffer."""
-        import torch
         fo, f, kh, kw = wt.shape
         if wf is None:
             wf = torch.empty(self.weights_bytes(f, fo, h, w, kh, kw, pad_h, pad_w) // 4, device=wt.device,
@@ -445,7 +436,6 @@ class Handle:
         return wf
 
     def fft_conv_fprop_weights(self, x, wf, fo, kh, kw, pad_h=0, pad_w=0, y=None, ws=None):
-        import torch
         S, f, h, w = x.shape
         if y is None:
             y = torch.empty((S, fo, h + 2 * pad_h - kh + 1, w + 2 * pad_w - kw + 1), device=x.device,
@@ -458,7 +448,6 @@ class Handle:
 
     def fft_conv_fprop_fused(self, x, wf, fo, kh, kw, y=None):
         """One-launch fprop of a small layer; raises FFTConvError("unsupported ...") for others."""
-        import torch
         S, f, h, w = x.shape
         if y is None:
             y = torch.empty((S, fo, h - kh + 1, w - kw + 1), device=x.device, dtype=torch.float32)
@@ -469,7 +458,6 @@ class Handle:
 
     def fft_conv_bprop_fused(self, gy, wf, f, h, w, kh, kw, gx=None):
         """One-launch bprop of a small layer; raises FFTConvError("unsupported ...") for others."""
-        import torch
         S, fo, oh, ow = gy.shape
         if oh != h - kh + 1 or ow != w - kw + 1:
             raise FFTConvError("gy and (h, w, kh, kw) disagree")
@@ -482,7 +470,6 @@ class Handle:
 
     def fft_conv_accgrad_fused(self, x, gy, gw=None, scale=1.0, accumulate=False):
         """One-launch accGrad of a small layer; raises FFTConvError("unsupported ...") for others."""
-        import torch
         S, f, h, w = x.shape
         S2, fo, oh, ow = gy.shape
         if S2 != S:
@@ -499,7 +486,6 @@ class Handle:
         return gw
 
     def fft_conv_bprop_weights(self, gy, wf, f, h, w, kh, kw, pad_h=0, pad_w=0, gx=None, ws=None):
-        import torch
         S, fo, oh, ow = gy.shape
         if oh != h + 2 * pad_h - kh + 1 or ow != w + 2 * pad_w - kw + 1:
             raise FFTConvError("gy and (h, w, kh, kw, padding) disagree")
@@ -516,7 +502,6 @@ class Handle:
         return int(self._lib.fftconv_padded_workspace_bytes(pass_, S, f, fo, h, w, kh, kw, pad_h, pad_w))
 
     def fft_conv_fprop_padded(self, x, wt, pad_h, pad_w, y=None, ws=None):
-        import torch
         S, f, h, w = x.shape
         fo, f2, kh, kw = wt.shape
         if f2 != f:
@@ -531,7 +516,6 @@ class Handle:
         return y
 
     def fft_conv_bprop_padded(self, gy, wt, h, w, pad_h, pad_w, gx=None, ws=None):
-        import torch
         S, fo, oh, ow = gy.shape
         fo2, f, kh, kw = wt.shape
         if fo2 != fo or oh != h + 2 * pad_h - kh + 1 or ow != w + 2 * pad_w - kw + 1:
@@ -545,7 +529,6 @@ class Handle:
         return gx
 
     def fft_conv_accgrad_padded(self, x, gy, pad_h, pad_w, gw=None, scale=1.0, accumulate=False, ws=None):
-        import torch
         S, f, h, w = x.shape
         S2, fo, oh, ow = gy.shape
         if S2 != S:
@@ -568,7 +551,6 @@ class Handle:
         return int(self._lib.fftconv_backward_workspace_bytes_padded(S, f, fo, h, w, kh, kw, pad_h, pad_w))
 
     def fft_conv_fprop_save_padded(self, x, wt, pad_h, pad_w, saved, y=None, ws=None):
-        import torch
         S, f, h, w = x.shape
         fo, f2, kh, kw = wt.shape
         if f2 != f:
@@ -584,7 +566,6 @@ class Handle:
 
     def fft_conv_backward_padded(self, gy, saved, f, h, w, kh, kw, pad_h, pad_w, gx=None, gw=None,
                                  want_gx=True, want_gw=True, scale=1.0, accumulate=False, ws=None):
-        import torch
         S, fo, oh, ow = gy.shape
         if oh != h + 2 * pad_h - kh + 1 or ow != w + 2 * pad_w - kw + 1:
             raise FFTConvError("gy, (h, w, kh, kw) and the padding disagree")
@@ -606,12 +587,11 @@ class Handle:
     @staticmethod
     def _ws(ws):
         if ws is None:
-            return ctypes.c_void_p(0), 0
-        return ctypes.c_void_p(ws.data_ptr()), ws.numel() * ws.element_size()
+            return None, 0
+        return ws.data_ptr(), ws.numel() * ws.element_size()
 
     # ---- stand-alone FFTs ---------------------------------------------------------------
     def fft_r2c_1d(self, x, n, out=None):
-        import torch
         B, n_in = x.shape
         if out is None:
             out = torch.empty((B, n // 2 + 1, 2), device=x.device, dtype=torch.float32)
@@ -620,7 +600,6 @@ class Handle:
         return out
 
     def fft_c2r_1d(self, X, n, n_out, out=None):
-        import torch
         B = X.shape[0]
         if tuple(X.shape[1:]) != (n // 2 + 1, 2):
             raise FFTConvError("in must be [B, n/2+1, 2]")
@@ -631,7 +610,6 @@ class Handle:
         return out
 
     def fft_r2c_2d(self, x, n, out=None):
-        import torch
         B, h_in, w_in = x.shape
         if out is None:
             out = torch.empty((B, n, n // 2 + 1, 2), device=x.device, dtype=torch.float32)
@@ -640,7 +618,6 @@ class Handle:
         return out
 
     def fft_c2r_2d(self, X, n, h_out, w_out, out=None):
-        import torch
         B = X.shape[0]
         if tuple(X.shape[1:]) != (n, n // 2 + 1, 2):
             raise FFTConvError("in must be [B, n, n/2+1, 2]")
