@@ -421,17 +421,33 @@ static hipError_t invert_pair(fftconv_ctx *c, const PassPlan &pb, const float *G
     return invert(c, pa, GWF, gw, scale, accumulate);
 }
 
+// Both gradients' inverse transforms in one launch after contractions of their own: a launch less, but the first
+// product is no longer read right after it was written.  260 random layers, apart / one: up to 32 MB of products 0.77 .. 0.98 (16 x 16 -> 16
+// 34x34 26.3 / 21.3 us, 38 x 64 -> 19, 48x48 76.2 / 69.9), up to 96 MB 0.92 .. 0.99, from 160 MB on it loses (102 x 320 -> 4, 34x34 191.9 / 202.6);
+// on basis 64, whose workgroups of 1024 threads a part of the weights' fills worst, already from 40 MB on (22 x 176 -> 16 64x64, 113 MB, 130.7 /
+// 144.0).  Not on the bases 16 and 28, where a launch for both takes another kernel than one alone (a gradient alone is the same bits).
+static bool inverse_pair_pays(const PassPlan &pb, const PassPlan &pa) {
+    if (pb.rect || pa.rect || pb.N != pa.N || pb.N == 16 || pb.N == 28) return false;
+    const double bytes = (double)(pb.lay.floats(pb.planesC) + pa.lay.floats(pa.planesC)) * sizeof(float);
+    return bytes <= (pb.N == 64 ? 32e6 : 96e6);
+}
+
+// The product of a reduction of at most four terms inside the inverse transform.  hipErrorNotSupported, with nothing launched,
+// where that does not apply.
+static hipError_t product_inverse(fftconv_ctx *c, const PassPlan &p, const GemmProblem &g, float *out, float scale, int accumulate) {
+    if (p.rect) return hipErrorNotSupported;
+    const int nk = c->nk;
+    const hipError_t e = launch_product_inverse(g, out, p.N, p.hC, p.wC, scale / ((float)p.N * (float)p.N), accumulate != 0,
+                                                next_ctx(c, "contraction.ifft"), p.viewC ? &p.vC : nullptr);
+    if (e == hipErrorNotSupported) c->nk = nk;   // nothing was launched: give the event pair back
+    return e;
+}
+
 // Contraction + inverse transform of one pass, operands already in the frequency domain.
 static hipError_t contract_and_invert(fftconv_ctx *c, const PassPlan &p, const float *AF, const float *BF,
                                       float *CF, float *out, float scale, int accumulate, const GemmProblem *partner = nullptr) {
     const GemmProblem g = gemm_problem(p, AF, BF, CF);
-    if (!p.rect) {                             // a product of at most four terms: inside the inverse transform
-        const int nk = c->nk;
-        const hipError_t e = launch_product_inverse(g, out, p.N, p.hC, p.wC, scale / ((float)p.N * (float)p.N), accumulate != 0,
-                                                    next_ctx(c, "contraction.ifft"), p.viewC ? &p.vC : nullptr);
-        if (e != hipErrorNotSupported) return e;
-        c->nk = nk;                            // nothing was launched: give the event pair back
-    }
+    if (const hipError_t e = product_inverse(c, p, g, out, scale, accumulate); e != hipErrorNotSupported) return e;
     if (hipError_t e = launch_cgemm_bins(g, next_ctx(c, "contraction"), partner); e != hipSuccess) return e;
     return invert(c, p, CF, out, scale, accumulate);
 }
@@ -928,6 +944,18 @@ static int backward_impl(fftconv_handle hd, const float *gy, float *gx, float *g
         if ((e = launch_cgemm_pair(a_first ? qa : qb, a_first ? qb : qa, next_ctx(hd, "contraction.pair"))) != hipSuccess) return hip_fail(hd, e);
         if ((e = invert_pair(hd, pb, GXF, gx, pa, GWF, gw, scale, accumulate)) != hipSuccess) return hip_fail(hd, e);
         return FFTCONV_OK;
+    }
+    if (gx && gw && inverse_pair_pays(pb, pa)) {
+        const hipError_t eb = product_inverse(hd, pb, qb, gx, 1.0f, 0), ea = product_inverse(hd, pa, qa, gw, scale, accumulate);
+        if (eb != hipSuccess && eb != hipErrorNotSupported) return hip_fail(hd, eb);
+        if (ea != hipSuccess && ea != hipErrorNotSupported) return hip_fail(hd, ea);
+        if (eb != hipSuccess && (e = launch_cgemm_bins(qb, next_ctx(hd, "contraction"))) != hipSuccess) return hip_fail(hd, e);
+        if (ea != hipSuccess && (e = launch_cgemm_bins(qa, next_ctx(hd, "contraction"))) != hipSuccess) return hip_fail(hd, e);
+        if (eb != hipSuccess && ea != hipSuccess) e = invert_pair(hd, pb, GXF, gx, pa, GWF, gw, scale, accumulate);
+        else if (eb != hipSuccess) e = invert(hd, pb, GXF, gx, 1.0f, 0);
+        else if (ea != hipSuccess) e = invert(hd, pa, GWF, gw, scale, accumulate);
+        else e = hipSuccess;
+        return e == hipSuccess ? FFTCONV_OK : hip_fail(hd, e);
     }
     if (gx && (e = contract_and_invert(hd, pb, GYF, WF, GXF, gx, 1.0f, 0, gw ? nullptr : &qa)) != hipSuccess) return hip_fail(hd, e);
     if (gw && (e = contract_and_invert(hd, pa, GYFa, XF, GWF, gw, scale, accumulate, gx ? nullptr : &qb)) != hipSuccess) return hip_fail(hd, e);

@@ -123,8 +123,13 @@ hipError_t launch_fft2d_c2r_pair(const InvOperand *ops, int N, LaunchCtx st) {
         if (ops[o].planes <= 0 || rows > N || cols > N) return hipErrorNotSupported;
     }
     switch (N) {
+        // fft_conv_backward after a shared contraction, two launches -> one: basis 8, 54 random layers 0.78 of the time in the mean (105 x 64 -> 320, 6x6
+        // 45.7 -> 40.7 us), the bases from 36 to 64, 53 layers, 0.87 (27 x 16 -> 26, 50x50 50.6 -> 44.5); none slower
+        case 8: return run_inv2d_pair<8, 1, 64>(ops, st);
         case 16: return run_inv2d_pair<16, 1, 32>(ops, st);   // 22.1 + 29.7 -> 52.5 us at 384 channels: the launch gap
         case 32: return run_inv2d_pair<8, 4, 8>(ops, st);
+        case 64: return run_inv2d_pair<8, 8, 4>(ops, st);
+        case 128: return run_inv2d_pair<16, 8, 1>(ops, st);
         default: return launch_fft2d_c2r_pair_mixed(ops, N, st);
     }
 }

@@ -222,6 +222,37 @@ def test_a_gradient_alone_is_the_same_bits(hd, S, f, fo, side, k):
     assert torch.equal(hd.fft_conv_backward(gy, saved, f, side, side, k, k, want_gx=False)[1], gw)
 
 
+# Both inverse transforms of a backward pass in one launch on every basis: few channels (odd counts, a ragged last tile) and a
+# shared contraction, then both contractions of their own; windows and padding; scale and accumulate stay with their product.
+@pytest.mark.parametrize("side", [8, 10, 12, 14, 18, 20, 24, 32, 36, 40, 48, 56, 64, 80, 96, 112, 128])
+def test_both_inverse_transforms_in_one_launch(hd, side):
+    import torch
+    import torch.nn.functional as F
+    g = torch.Generator().manual_seed(9)
+    k = 33 if side > 64 else 3
+    o = side - k + 1
+    for S, f, fo in ((7, 5, 9), (6, 3, 16)) if side <= 64 else ((3, 2, 5),):
+        x, w = torch.randn(S, f, side, side, generator=g).cuda(), torch.randn(fo, f, k, k, generator=g).cuda()
+        gy = torch.randn(S, fo, o, o, generator=g).cuda()
+        saved = torch.empty(hd.saved_bytes(S, f, fo, side, side, k, k) // 4, device="cuda")
+        hd.fft_conv_fprop_save(x, w, saved)
+        old = torch.randn(fo, f, k, k, generator=g).cuda()
+        gw = old.clone()
+        hd.set_profiling(True)
+        try:
+            gx, _ = hd.fft_conv_backward(gy, saved, f, side, side, k, k, gw=gw, scale=0.5, accumulate=True)
+            assert hd.last_kernel_labels()[-1] == "ifft.pair"
+        finally:
+            hd.set_profiling(False)
+        assert torch.equal(hd.fft_conv_backward(gy, saved, f, side, side, k, k, want_gw=False)[0], gx)
+        alone = old.clone()
+        hd.fft_conv_backward(gy, saved, f, side, side, k, k, gw=alone, want_gx=False, scale=0.5, accumulate=True)
+        assert torch.equal(alone, gw)
+        xd, wd, gd = x.cpu().double(), w.cpu().double(), gy.cpu().double()
+        assert _relerr(gx, F.conv_transpose2d(gd, wd)) <= TOL
+        assert _relerr(gw, old.cpu().double() + 0.5 * F.conv2d(xd.transpose(0, 1), gd.transpose(0, 1)).transpose(0, 1)) <= TOL
+
+
 # Products of at most four terms formed inside the inverse transform: every basis that has the kernel, one .. four terms
 # from either operand's layout, quads of columns that start in the middle of a run, a ragged last tile, windows.
 @pytest.mark.parametrize("side", [8, 10, 12, 14, 16, 18, 20, 24, 28, 32, 36, 40, 48, 56])
