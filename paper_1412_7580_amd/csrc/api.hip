@@ -490,11 +490,13 @@ static int run_pass_weights(fftconv_ctx *c, int pass, const float *opA, const vo
     if (wf_bytes < align_up(p.lay.floats(p.planesB) * sizeof(float), 256)) return FFTCONV_WORKSPACE_TOO_SMALL;
     // Latency-bound layers (a few dozen small planes) run as ONE launch: three launches of a few
     // microseconds each cost more than their arithmetic (Section 6 plans such an integration).
-    // The one-launch kernels carry one sample per workgroup, so they pay while the samples are a
-    // single round of workgroups.
-    if (!p.tiled && !p.rect && ph == 0 && pw == 0 && S <= 512) {
+    if (!p.tiled && !p.rect && ph == 0 && pw == 0) {
         const float *wff = static_cast<const float *>(wf);
-        const bool ok = pass == FFTCONV_FPROP ? fused_fprop_supported(p.N, f, fo, wff) : fused_bprop_supported(p.N, f, fo, wff);
+        const bool ok = pass == FFTCONV_FPROP ? fused_fprop_pays(p.N, S, f, fo, wff) : fused_bprop_pays(p.N, S, f, fo, wff);
+        // The smallest layers ask for no workspace.  The others do as if they used it: a call that has too little is
+        // told so, and the handle's own grows for the calls (captured ones, say) that come after.
+        const bool tiny = S <= 512 && fused_fprop_supported(p.N, f, fo, wff);
+        if (ok && !tiny && (rc = get_workspace(c, p.total, &ws, ws_bytes)) != FFTCONV_OK) return rc;
         if (ok) {
             c->nk = 0;
             const hipError_t e = pass == FFTCONV_FPROP

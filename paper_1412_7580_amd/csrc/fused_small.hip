@@ -4,7 +4,8 @@
 // workgroup carries one sample through the whole pass:
 //   R2C of its f input planes (spectra stay in LDS)  ->  Y_j = sum_i X_i . conj(W_ji) per bin
 //   on the vector ALUs (one sample is a matrix-vector product per bin: no tile for the matrix
-//   cores), W from the weight transform computed ahead  ->  C2R + crop of its f' planes.
+//   cores), W from the weight transform computed ahead  ->  C2R + crop of its f' planes, or of a
+//   share of them where the samples alone leave compute units idle (fused_part()).
 // No workgroup waits for another one, so there is no grid-wide synchronisation.
 #include "fft_kernels_impl.hpp"
 
@@ -16,6 +17,7 @@ struct FusedParams {
     const float *wf;           // weight transform in the layout fwd.lay, plane = j * f + i
     int f, fo;
     long x_stride, y_stride;   // floats per sample
+    int part, parts;           // result planes a workgroup, workgroups a sample
     int img;                   // float offset of the second LDS image (the product's)
 };
 
@@ -24,7 +26,8 @@ __global__ void __launch_bounds__(T *(L * G / 2) * G) fused_fprop_kernel(FusedPa
     constexpr int N = L * G, NH = N / 2, NB = NH + 1, BT = T * NH * G, BINS = N * NB;
     extern __shared__ float smem[];
     const int tid = threadIdx.x;
-    const long s = blockIdx.x;
+    const long s = blockIdx.x / fp.parts;
+    const int j0 = (int)(blockIdx.x - s * fp.parts) * fp.part, cnt = fp.fo - j0 < fp.part ? fp.fo - j0 : fp.part;
 
     Fwd2dParams fw = fp.fwd;
     fw.in += s * fp.x_stride;
@@ -36,10 +39,10 @@ __global__ void __launch_bounds__(T *(L * G / 2) * G) fused_fprop_kernel(FusedPa
     // for several outputs at once, or for the first ones ahead of the forward transform,
     // measured slower: 14.0 against 11.7 us on the 16-plane 13x13 layer.)
     float *yimg = smem + fp.img;
-    const int f = fp.f, fo = fp.fo;
-    for (int o = tid; o < BINS * fo; o += BT) {
-        const int bin = o / fo, j = o - bin * fo;
-        const float *wr = fp.wf + fp.fwd.lay.index((long)j * f, bin, 0);
+    const int f = fp.f;
+    for (int o = tid; o < BINS * cnt; o += BT) {
+        const int bin = o / cnt, j = o - bin * cnt;
+        const float *wr = fp.wf + fp.fwd.lay.index((long)(j0 + j) * f, bin, 0);
         const float *wi = wr + T;
         const float *xr = smem + (bin * 2) * T, *xi = xr + T;
         float yr = 0.f, yi = 0.f;
@@ -57,7 +60,8 @@ __global__ void __launch_bounds__(T *(L * G / 2) * G) fused_fprop_kernel(FusedPa
     __syncthreads();
 
     Inv2dParams iv = fp.inv;
-    iv.out += s * fp.y_stride;
+    iv.out += s * fp.y_stride + (long)j0 * iv.h_out * iv.w_out;
+    iv.planes = cnt;
     fft2d_c2r_body<L, G, T, true, false, true>(iv, 0, yimg);
 }
 
@@ -71,21 +75,22 @@ __global__ void __launch_bounds__(T *(L * G / 2) * G) fused_bprop_kernel(FusedPa
     constexpr int N = L * G, NH = N / 2, NB = NH + 1, BT = T * NH * G, BINS = N * NB;
     extern __shared__ float smem[];
     const int tid = threadIdx.x;
-    const long s = blockIdx.x;
+    const long s = blockIdx.x / fp.parts;
+    const int i0 = (int)(blockIdx.x - s * fp.parts) * fp.part, cnt = fp.f - i0 < fp.part ? fp.f - i0 : fp.part;
 
     Fwd2dParams fw = fp.fwd;
     fw.in += s * fp.x_stride;
     fft2d_r2c_body<L, G, T, true, true, true>(fw, 0);      // GY[(bin * 2 + c) * T + j] at smem
 
     float *ximg = smem + fp.img;
-    const int f = fp.f, fo = fp.fo, f4 = f >> 2;
+    const int f = fp.f, fo = fp.fo, f4 = cnt >> 2;
     for (int o = tid; o < BINS * f4; o += BT) {
         const int bin = o / f4, i = (o - bin * f4) << 2;
         const float *gr = smem + (bin * 2) * T, *gi = gr + T;
         float4 xr = make_float4(0.f, 0.f, 0.f, 0.f), xi = xr;
 #pragma unroll 4
         for (int j = 0; j < fo; ++j) {
-            const float *wr = fp.wf + fp.fwd.lay.index((long)j * f + i, bin, 0);
+            const float *wr = fp.wf + fp.fwd.lay.index((long)j * f + i0 + i, bin, 0);
             const float4 a = *reinterpret_cast<const float4 *>(wr), b = *reinterpret_cast<const float4 *>(wr + T);
             const float yr = gr[j], yi = gi[j];
             // gy . w = (yr wr - yi wi) + i (yr wi + yi wr)
@@ -100,8 +105,23 @@ __global__ void __launch_bounds__(T *(L * G / 2) * G) fused_bprop_kernel(FusedPa
     __syncthreads();
 
     Inv2dParams iv = fp.inv;
-    iv.out += s * fp.y_stride;
+    iv.out += s * fp.y_stride + (long)i0 * iv.h_out * iv.w_out;
+    iv.planes = cnt;
     fft2d_c2r_body<L, G, T, true, false, true>(iv, 0, ximg);
+}
+
+// Result planes a workgroup.  Each workgroup of a sample transforms all its input planes again, which costs nothing while
+// compute units are idle: up to 256 workgroups share out the products and the inverse transforms.  A part is not
+// smaller than helps: fprop 32 products a bin (four terms, 16 results: 8.1 us with 8 planes, 9.9 with one), bprop the planes whose
+// quads, four results a lane, are one round of the workgroup.  us by planes a workgroup, 13x13: fprop, 32 samples of 32 -> 32 31.3 (all),
+// 19.4 (16), 13.3 (8), 10.8 (4), 11.0 (2: 512 workgroups); 8 of 16 -> 16 10.0, 8.8 (8), 8.4 (2); 128 of 16 -> 16 10.3, 8.8 (8), 9.9 (4), 32.3 (1);
+// bprop, 32 of 32 -> 32 14.7, 11.0 (16), 12.0 (8), 14.4 (4); basis 16 18.7, 15.4, 14.4, 17.2.
+static int fused_part(int N, int S, int terms, int results, bool bprop) {
+    const int bins = N * (N / 2 + 1), threads = (1 << fft2d_tile_log2(N)) * N;
+    int part = bprop ? (4 * bins <= threads ? 16 : 8) : terms < 32 ? 32 / terms : 1;
+    if (!bprop && terms * results <= 64) return results;
+    while (part < results && (long)S * ((results + part - 1) / part) > 256) part *= 2;
+    return part < results ? part : results;
 }
 
 template <int L, int G, int T>
@@ -140,24 +160,38 @@ static hipError_t run_fused(const float *x, const float *wf, float *y, int S, in
     if (lds > 160 * 1024) return hipErrorInvalidValue;
     auto k = bprop ? fused_bprop_kernel<L, G, T> : fused_fprop_kernel<L, G, T>;
     if (hipError_t e = allow_big_lds((const void *)k, lds); e != hipSuccess) return e;
-    launch_kernel(k, dim3((unsigned)S), dim3(BT), lds, st, fp);
+    fp.part = fused_part(N, S, in_planes, out_planes, bprop);
+    fp.parts = (out_planes + fp.part - 1) / fp.part;
+    launch_kernel(k, dim3((unsigned)S * fp.parts), dim3(BT), lds, st, fp);
     return hipGetLastError();
 }
 
-bool fused_fprop_supported(int N, int f, int fo, const float *wf) {
-    const int tsh = fft2d_tile_log2(N);
+static bool fused_fits(int N, int f, int fo, const float *wf) {
+    const int tsh = fft2d_tile_log2(N), T = 1 << tsh;
     if (tsh < 5 || N > 16) return false;                // bases 8 .. 16: 32 or 64 planes per tile
-    const int T = 1 << tsh;
-    // bins x weight planes up to 40000: beyond that the vector-ALU product stage takes longer
-    // than the launches it saves (measured at basis 14: 16 x 16 planes 10.1 us against 14.9 for
-    // the three-launch path, 16 x 32 13.2 against 14.6, 32 x 16 19.3 against 15.9, 32 x 32 31 against 16)
-    return f <= T && fo <= T && (long)N * (N / 2 + 1) * f * fo <= 40000 && f % 4 == 0 && T % f == 0 &&
-           ((size_t)wf & 15) == 0;
+    return f <= T && fo <= T && f % 4 == 0 && T % f == 0 && ((size_t)wf & 15) == 0;
+}
+
+// Against three launches (us, one / three).  The product stage of a workgroup sets the limit, 40000 products in fprop
+// (13x13, 32 -> 32 by the samples 1 9.8 / 14.0, 32 10.8 / 15.2, 128 (16 planes, 57344) 20.0 / 18.8), three times that in bprop, which forms
+// four with each load (32 -> 32, all planes, 114688: 256 samples 16.9 / 23.8, 349 samples 14x14 29.8 / 30.4; 7x7, 64 -> 64, 163840: 256 samples
+// 21.5 / 20.7).  512 samples are two rounds of workgroups; up to 1024 layers of few products still gain (16 -> 16, 15x15 30.2 / 40.3; 16 -> 8,
+// 7x7 10.5 / 18.8) unless the reduction of four terms or fewer goes into the inverse transform (8 -> 3, 16x16 bprop 37.8 / 21.8).
+static bool fused_pays(int N, int S, int terms, int results, bool bprop) {
+    const long work = (long)N * (N / 2 + 1) * terms * fused_part(N, S, terms, results, bprop);
+    return S <= 512 ? work <= (bprop ? 120000 : 40000) : S <= 1024 && terms > 4 && work <= 40000;
+}
+bool fused_fprop_pays(int N, int S, int f, int fo, const float *wf) { return fused_fits(N, f, fo, wf) && fused_pays(N, S, f, fo, false); }
+bool fused_bprop_pays(int N, int S, int f, int fo, const float *wf) { return fused_fits(N, f, fo, wf) && fused_pays(N, S, fo, f, true); }
+
+// The calls by name take what one workgroup a sample was faster for: bins x weight planes up to 40000.
+bool fused_fprop_supported(int N, int f, int fo, const float *wf) {
+    return fused_fits(N, f, fo, wf) && (long)N * (N / 2 + 1) * f * fo <= 40000;
 }
 
 hipError_t launch_fused_fprop(const float *x, const float *wf, float *y, int S, int f, int fo, int h, int w,
                               int kh, int kw, int N, LaunchCtx st) {
-    if (!fused_fprop_supported(N, f, fo, wf) || h > N || w > N) return hipErrorInvalidValue;
+    if (!fused_fits(N, f, fo, wf) || h > N || w > N) return hipErrorInvalidValue;
     switch (N) {
         // lane pairs: twice the lanes for the product stage, whose W gathers set its pace
         case 8: return run_fused<4, 2, 64>(x, wf, y, S, f, fo, h, w, kh, kw, st);
@@ -176,7 +210,7 @@ bool fused_bprop_supported(int N, int f, int fo, const float *wf) {
 
 hipError_t launch_fused_bprop(const float *gy, const float *wf, float *gx, int S, int f, int fo, int h, int w,
                               int kh, int kw, int N, LaunchCtx st) {
-    if (!fused_bprop_supported(N, f, fo, wf) || h > N || w > N) return hipErrorInvalidValue;
+    if (!fused_fits(N, f, fo, wf) || h > N || w > N) return hipErrorInvalidValue;
     switch (N) {
         case 8: return run_fused<4, 2, 64>(gy, wf, gx, S, f, fo, h, w, kh, kw, st, true);
         case 10: return run_fused<5, 2, 32>(gy, wf, gx, S, f, fo, h, w, kh, kw, st, true);

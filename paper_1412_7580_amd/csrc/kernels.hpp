@@ -141,14 +141,17 @@ hipError_t launch_fft2d_c2r_pair(const InvOperand *ops, int N, LaunchCtx st);
 // The same on a rectangular basis (whole planes only).
 hipError_t launch_fft2d_c2r_rect_pair(const InvOperand *ops, int nr, int nc, LaunchCtx st);
 
-// One-launch fprop of a small layer (basis N <= 16, f and f' within one plane tile): one
-// workgroup per sample; wf is the weight transform in the layout of basis N.
+// One-launch fprop of a small layer (basis N <= 16, f and f' within one plane tile): workgroups of
+// their own for each sample; wf is the weight transform in the layout of basis N.  _supported: the layers that
+// the calls by name take; _pays: those that measured faster than three launches, more of them.
 bool fused_fprop_supported(int N, int f, int fo, const float *wf);
+bool fused_fprop_pays(int N, int S, int f, int fo, const float *wf);
 hipError_t launch_fused_fprop(const float *x, const float *wf, float *y, int S, int f, int fo, int h, int w,
                               int kh, int kw, int N, LaunchCtx st);
 
-// bprop likewise (GX_i = sum_j GY_j . W_ji): one workgroup per sample, same support rule.
+// bprop likewise (GX_i = sum_j GY_j . W_ji).
 bool fused_bprop_supported(int N, int f, int fo, const float *wf);
+bool fused_bprop_pays(int N, int S, int f, int fo, const float *wf);
 hipError_t launch_fused_bprop(const float *gy, const float *wf, float *gx, int S, int f, int fo, int h, int w,
                               int kh, int kw, int N, LaunchCtx st);
 

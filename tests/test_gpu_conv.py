@@ -360,6 +360,34 @@ def test_weights_ahead_passes_take_one_launch_for_small_layers(hd):
     assert _relerr(_np(yb), oracle.conv_fprop(xb, wb)) <= TOL
 
 
+@pytest.mark.parametrize("side", [7, 9, 12, 13, 16])
+@pytest.mark.parametrize("S,f,fo", [(1, 32, 32), (3, 32, 13), (9, 16, 31), (70, 32, 20), (2, 4, 32), (129, 8, 17), (600, 8, 5), (1, 64, 61)])
+def test_small_layers_share_a_sample_among_workgroups(hd, side, S, f, fo):
+    """Layers whose result planes several workgroups share: ragged shares, one share, more than 512 samples; the scratch
+    memory that the three launches would use is asked for as before."""
+    import torch
+    if f > 32 and side > 8:
+        f, fo = 32, 29
+    x, w, gy = synth.conv_inputs(seed=93, S=S, f=f, fo=fo, h=side, w=side, kh=3, kw=2)
+    dx, dw, dgy = _dev(x), _dev(w), _dev(gy)
+    wf = hd.fft_conv_transform_weights(dw, side, side)
+    hd.set_profiling(True)
+    try:
+        y = hd.fft_conv_fprop_weights(dx, wf, fo, 3, 2)
+        one = hd.last_kernel_labels() == ["fused"]
+        gx = hd.fft_conv_bprop_weights(dgy, wf, f, side, side, 3, 2)
+        one_b = hd.last_kernel_labels() == ["fused"]
+    finally:
+        hd.set_profiling(False)
+    assert _relerr(_np(y), oracle.conv_fprop(x, w)) <= TOL
+    assert _relerr(_np(gx), oracle.conv_bprop(gy, w, side, side)) <= TOL
+    assert S > 64 or (one and one_b)
+    bins = {7: 40, 9: 60, 12: 84, 13: 112, 16: 144}[side]
+    if one and bins * f * fo > 40000:
+        with pytest.raises(Exception):
+            hd.fft_conv_fprop_weights(dx, wf, fo, 3, 2, ws=torch.empty(64, device="cuda"))
+
+
 @pytest.mark.parametrize("cfg", FUSED, ids=lambda c: "S{S}f{f}fo{fo}_{h}x{w}_k{kh}x{kw}".format(**c))
 def test_fused_bprop(hd, lib, cfg):
     """The one-launch bprop of small layers against the oracle and against the three-launch path."""
