@@ -168,6 +168,25 @@ __device__ __forceinline__ float lane_xor3(float v) { return quad_dpp<0x1B>(v); 
 __device__ __forceinline__ float lane_xor7(float v) { return quad_dpp<0x141>(v); }
 __device__ __forceinline__ float lane_xor4(float v) { return lane_xor3(lane_xor7(v)); }
 
+// (a, b) += s * (the partner lane's a, b): one multiply-add each that reads the partner through DPP.  The compiler folds such a
+// read into additions but not into multiply-adds, where it takes a move of its own.  A DPP read of a register needs two wait
+// states after the vector instruction that wrote it, which the compiler does not count for an asm block: s_nop 1 at its head.
+// The transforms are bound by their vector instructions (0.7 .. 0.9 of the cycles): inverse of basis 28, both products
+// 27.2 -> 24.3 us, of basis 128 19.8 -> 17.3, forward of basis 80 12.7 -> 11.7.
+__device__ __forceinline__ void add_xor1(float &a, float &b, float s) {
+    asm("s_nop 1\n\tv_fmac_f32_dpp %0, %0, %2 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %1, %1, %2 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf" : "+v"(a), "+v"(b) : "v"(s));
+}
+__device__ __forceinline__ void add_xor2(float &a, float &b, float s) {
+    asm("s_nop 1\n\tv_fmac_f32_dpp %0, %0, %2 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %1, %1, %2 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf" : "+v"(a), "+v"(b) : "v"(s));
+}
+__device__ __forceinline__ void add_xor4(float &a, float &b, float s) {
+    const float a7 = lane_xor7(a), b7 = lane_xor7(b);
+    asm("s_nop 1\n\tv_fmac_f32_dpp %0, %2, %4 quad_perm:[3,2,1,0] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %1, %3, %4 quad_perm:[3,2,1,0] row_mask:0xf bank_mask:0xf" : "+v"(a), "+v"(b) : "v"(a7), "v"(b7), "v"(s));
+}
+
 // Block of output bins held by lane g after fft_group: lane g holds X[k + L*group_block(g)].
 template <int G>
 __device__ __forceinline__ int group_block(int g) {
@@ -180,7 +199,9 @@ __device__ __forceinline__ int group_block(int g) {
 // in register m; on exit lane g holds X[k + L*group_block<G>(g)] in register k.  All G lanes
 // of a group must be active together.  The cross-lane part is one (G = 2) or two (G = 4)
 // radix-2 decimation-in-time steps: the upper lane of each pair multiplies by the step's
-// twiddle, the pair swaps values through DPP and forms sum / difference.
+// twiddle, the pair swaps values through DPP and forms sum / difference.  The upper lane's factor is
+// minus the twiddle: with x on the lower and x' = -t on the upper lane both results are own + s * other, s = -1 below and
+// +1 above, one v_fmac_f32 that reads its partner through DPP instead of a move and a multiply-add.
 // HALF (lane pairs only): the result is scaled by 1/2, at no cost: the factor goes into the
 // twiddles of the cross-lane step, whose product every lane forms anyway.
 template <int L, int G, int DIR, bool HALF = false>
@@ -190,20 +211,19 @@ __device__ __forceinline__ void fft_group(float (&re)[L], float (&im)[L], int g)
     constexpr double SCALE = HALF ? 0.5 : 1.0;
     fft_leaf<L, DIR>(re, im);
     if constexpr (G == 2) {
-        float sgn = g ? -1.0f : 1.0f;
+        float sgn = g ? 1.0f : -1.0f;
         // (opaque to the compiler: knowing that it is +-1 it would form both the sum and the
         // difference and select between them, three instructions where a product and a sum do)
         asm volatile("" : "+v"(sgn));
         static_for<0, L>([&](auto kk) {
             constexpr int k = decltype(kk)::value;
             constexpr cplx_d w = unit_root(DIR * k, 2 * L);
-            constexpr float cr = (float)(SCALE * w.re), ci = (float)(SCALE * w.im), one = (float)SCALE;
+            constexpr float cr = (float)(-SCALE * w.re), ci = (float)(-SCALE * w.im), one = (float)SCALE;
             const float wr = g ? cr : one, wi = g ? ci : 0.0f;
             const float tr = wr * re[k] - wi * im[k];
             const float ti = wr * im[k] + wi * re[k];
-            const float qr = lane_xor1(tr), qi = lane_xor1(ti);
-            re[k] = qr + sgn * tr;
-            im[k] = qi + sgn * ti;
+            re[k] = tr; im[k] = ti;
+            add_xor1(re[k], im[k], sgn);
         });
     } else if constexpr (G == 4) {
         const bool up = (g >> 1) != 0, odd = (g & 1) != 0, last = g == 3;
@@ -267,8 +287,8 @@ __device__ __forceinline__ void fft_group(float (&re)[L], float (&im)[L], int g)
 
 // The per-lane twiddles of the cross-lane steps of a line spread over G lanes, as a table for
 // kernels that keep it in LDS: entry (step s, register k, lane g) is the factor lane g applies
-// to register k before step s (1 for the lanes that keep their value), for DIR = +1; the
-// other direction uses the conjugate.  Step s pairs lanes that differ in bit log2(G)-1-s of g;
+// to register k before step s (1 for the lanes that keep their value, minus the twiddle for the
+// others, see fft_group), for DIR = +1; the other direction uses the conjugate.  Step s pairs lanes that differ in bit log2(G)-1-s of g;
 // the exponent collects the bits already used (see fft_group).  One 8-byte LDS read replaces
 // the selects among compile-time constants (up to four constants moved into registers and
 // three selects per component), a third of the vector instructions of the eight-lane kernels.
@@ -289,9 +309,9 @@ struct GroupTwiddles {
                     const bool on = ((g >> (S - 1 - s)) & 1) != 0;
                     int e = k;
                     for (int t = 0; t < s; ++t) e += ((g >> (S - 1 - t)) & 1) * (L << t);
-                    const cplx_d w = on ? unit_root(e, (2 << s) * L) : cplx_d{1.0, 0.0};
-                    v[((s * L + k) * G + g) * 2 + 0] = (float)w.re;
-                    v[((s * L + k) * G + g) * 2 + 1] = (float)w.im;
+                    const cplx_d w = on ? unit_root(e, (2 << s) * L) : cplx_d{-1.0, 0.0};
+                    v[((s * L + k) * G + g) * 2 + 0] = (float)-w.re;
+                    v[((s * L + k) * G + g) * 2 + 1] = (float)-w.im;
                 }
     }
 };
@@ -318,28 +338,28 @@ __device__ __forceinline__ void fft_group_lds(float (&re)[L], float (&im)[L], in
         xr = tr; xi = ti;
     };
     if constexpr (G == 8) {
-        const float s1 = (g & 4) ? -1.0f : 1.0f, s2 = (g & 2) ? -1.0f : 1.0f, s3 = (g & 1) ? -1.0f : 1.0f;
+        const float s1 = (g & 4) ? 1.0f : -1.0f, s2 = (g & 2) ? 1.0f : -1.0f, s3 = (g & 1) ? 1.0f : -1.0f;
         static_for<0, L>([&](auto kk) {
             constexpr int k = decltype(kk)::value;
             float xr = re[k], xi = im[k];
             twiddle(tw[(0 * L + k) * 8], xr, xi);
-            float yr = lane_xor4(xr) + s1 * xr, yi = lane_xor4(xi) + s1 * xi;
-            twiddle(tw[(1 * L + k) * 8], yr, yi);
-            float zr = lane_xor2(yr) + s2 * yr, zi = lane_xor2(yi) + s2 * yi;
-            twiddle(tw[(2 * L + k) * 8], zr, zi);
-            re[k] = lane_xor1(zr) + s3 * zr;
-            im[k] = lane_xor1(zi) + s3 * zi;
+            add_xor4(xr, xi, s1);
+            twiddle(tw[(1 * L + k) * 8], xr, xi);
+            add_xor2(xr, xi, s2);
+            twiddle(tw[(2 * L + k) * 8], xr, xi);
+            add_xor1(xr, xi, s3);
+            re[k] = xr; im[k] = xi;
         });
     } else {
-        const float s1 = (g & 2) ? -1.0f : 1.0f, s2 = (g & 1) ? -1.0f : 1.0f;
+        const float s1 = (g & 2) ? 1.0f : -1.0f, s2 = (g & 1) ? 1.0f : -1.0f;
         static_for<0, L>([&](auto kk) {
             constexpr int k = decltype(kk)::value;
             float xr = re[k], xi = im[k];
             twiddle(tw[(0 * L + k) * 4], xr, xi);
-            float yr = lane_xor2(xr) + s1 * xr, yi = lane_xor2(xi) + s1 * xi;
-            twiddle(tw[(1 * L + k) * 4], yr, yi);
-            re[k] = lane_xor1(yr) + s2 * yr;
-            im[k] = lane_xor1(yi) + s2 * yi;
+            add_xor2(xr, xi, s1);
+            twiddle(tw[(1 * L + k) * 4], xr, xi);
+            add_xor1(xr, xi, s2);
+            re[k] = xr; im[k] = xi;
         });
     }
 }
@@ -382,6 +402,11 @@ __device__ __forceinline__ int split_slot(int g, int k) {
         }
     }
 }
+
+// From register 1 on the slots of a lane go up by one from register to register on even lanes and down by one on odd lanes:
+// slot(k) = split_slot(g, 1) + (k - 1) * split_step(g).  An addition a register; the cases of split_slot() written out for every
+// register are branches over the lanes of a wave (with the reads and the split below, forward of basis 56 39.7 -> 36.6 us, of 48 27.0 -> 25.1).
+__device__ __forceinline__ int split_step(int g) { return (g & 1) ? -1 : 1; }
 
 // After a forward fft_group of z = a + i b (a, b real lines), split the spectrum into the
 // spectra of a and b (the standard two-for-one trick the paper cites in Section 5.2).
@@ -436,17 +461,20 @@ __device__ __forceinline__ void split_two_real(const float (&re)[L], const float
                 aim[0] = first ? (odd ? im[0] : o0r) : (odd ? b_i : a_i);
             }
         }
+        // With u, v = (re, im) on even lanes and (im, re) on odd lanes both are (u + v', v - u') / 2, v' and u' the mirror lane's:
+        // two selections a register instead of two sums and differences of which one each is dropped.
+        float u[L], v[L];
+#pragma unroll
+        for (int k = 1; k < L; ++k) { u[k] = odd ? im[k] : re[k]; v[k] = odd ? re[k] : im[k]; }
         static_for<1, L>([&](auto kk) {
             constexpr int k = decltype(kk)::value;
-            float orr, oi;
-            if constexpr (G == 2) { orr = lane_xor1(re[L - k]); oi = lane_xor1(im[L - k]); }
-            else if constexpr (G == 4) { orr = lane_xor3(re[L - k]); oi = lane_xor3(im[L - k]); }
-            else { orr = lane_xor7(re[L - k]); oi = lane_xor7(im[L - k]); }
+            float ou, ov;
+            if constexpr (G == 2) { ov = lane_xor1(v[L - k]); ou = lane_xor1(u[L - k]); }
+            else if constexpr (G == 4) { ov = lane_xor3(v[L - k]); ou = lane_xor3(u[L - k]); }
+            else { ov = lane_xor7(v[L - k]); ou = lane_xor7(u[L - k]); }
             constexpr float h = TWICE ? 1.0f : 0.5f;
-            const float a_r = h * (re[k] + orr), a_i = h * (im[k] - oi);
-            const float b_r = h * (oi + im[k]), b_i = h * (re[k] - orr);
-            are[k] = odd ? b_r : a_r;
-            aim[k] = odd ? b_i : a_i;
+            are[k] = h * (u[k] + ov);
+            aim[k] = h * (v[k] - ou);
         });
         bre[0] = 0.f; bim[0] = 0.f;
     }

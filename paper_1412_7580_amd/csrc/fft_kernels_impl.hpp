@@ -103,6 +103,31 @@ __device__ __forceinline__ void stage_linear(float *dst, const float *src, unsig
     }
 }
 
+// The same for a number of floats known at compile time: no bounds but for the last round.
+template <int BT, int TOTAL>
+__device__ __forceinline__ void stage_whole(float *dst, const float *src, int tid, bool vec_ok) {
+    if constexpr (TOTAL % 4 == 0) {
+        if (vec_ok) {
+            constexpr int TOTAL4 = TOTAL / 4, FULL = TOTAL4 / BT, REST = TOTAL4 % BT, U = 8;
+            const float4 *s4 = reinterpret_cast<const float4 *>(src) + tid;
+            float4 *d4 = reinterpret_cast<float4 *>(dst) + tid;
+            float4 last;
+            if (REST && tid < REST) last = s4[FULL * BT];
+#pragma unroll
+            for (int r0 = 0; r0 < FULL; r0 += U) {
+                float4 v[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) if (r0 + u < FULL) v[u] = s4[(r0 + u) * BT];
+#pragma unroll
+                for (int u = 0; u < U; ++u) if (r0 + u < FULL) d4[(r0 + u) * BT] = v[u];
+            }
+            if (REST && tid < REST) d4[FULL * BT] = last;
+            return;
+        }
+    }
+    stage_linear<BT>(dst, src, TOTAL, tid, false);
+}
+
 // Copy `total` floats from LDS to contiguous global memory (optionally accumulating); vec_ok
 // as for stage_linear, with the roles of dst and src exchanged.
 template <int BT>
@@ -361,6 +386,23 @@ struct BinStore {
 // tid_sub) runs the transform in its own part of LDS, lds_off floats (a multiple of 4) from the
 // start; every thread of the workgroup must then make a call of this function, since its barriers
 // are the workgroup's.
+// Reads of a zero-padded line under a condition measured faster than unconditional ones plus selects, which cost registers and
+// occupancy on the two-lane kernels.  On two and four lanes f(m, there) for the elements g + G * m, of which the first n are there: n is
+// the same for all lanes, and only where the line ends between the lanes of a group is there a test of its own for each, instead of two exec masks
+// an element.  On one lane the plain tests are uniform already and this form is behind (fft.a of basis 14 6.0 -> 6.4 us), on eight lanes few
+// elements are left to save and a short line takes more branches (35 of 112 rows 21.5 -> 23.4).
+template <int G> constexpr bool kWholeGroups = G == 2 || G == 4;
+template <int L, int G, class F>
+__device__ __forceinline__ void each_of_line(int g, int n, F &&f) {
+#pragma unroll
+    for (int m = 0; m < L; ++m) {
+        const int left = n - G * m;
+        if (left >= G) f(m, true);
+        else if (left > 0) f(m, g < left);
+        else f(m, false);
+    }
+}
+
 template <int L, int G, int T, bool CONV, bool OSTAGE, bool KEEP = false>
 __device__ __forceinline__ void fft2d_r2c_body(const Fwd2dParams &prm, unsigned block, int tid_sub = -1,
                                                unsigned lds_off = 0) {
@@ -414,17 +456,21 @@ __device__ __forceinline__ void fft2d_r2c_body(const Fwd2dParams &prm, unsigned 
     float are[NA], aim[NA], bre[NBR], bim[NBR];
     if (row_active) {
         float re[L], im[L];
-        // (Conditional reads: the compiler turns them into uniform branches that skip the
-        // loads of the zero padding; measured faster than unconditional reads plus selects,
-        // which cost registers and occupancy on the two-lane kernels.)
         const float *pa = sin + p * prm.IPS + ra * prm.RS;
         const float *pb = sin + p * prm.IPS + rb * prm.RS;
+        if constexpr (kWholeGroups<G>) {
+            each_of_line<L, G>(g, w_in, [&](int m, bool in) { re[m] = in ? pa[g + G * m] : 0.f; });
 #pragma unroll
-        for (int m = 0; m < L; ++m) {
-            const int j = g + G * m;
-            const bool in = j < w_in;
-            re[m] = in ? pa[j] : 0.0f;
-            im[m] = (in && hasb) ? pb[j] : 0.0f;
+            for (int m = 0; m < L; ++m) im[m] = 0.f;
+            if (hasb) each_of_line<L, G>(g, w_in, [&](int m, bool in) { if (in) im[m] = pb[g + G * m]; });
+        } else {
+#pragma unroll
+            for (int m = 0; m < L; ++m) {
+                const int j = g + G * m;
+                const bool in = j < w_in;
+                re[m] = in ? pa[j] : 0.0f;
+                im[m] = (in && hasb) ? pb[j] : 0.0f;
+            }
         }
         fft_lines<L, G, -1>(re, im, g, smem + prm.tw_off);
         split_two_real<L, G, kDeferHalf<G>>(re, im, g, are, aim, bre, bim);   // (doubled: halved in the column phase)
@@ -442,9 +488,11 @@ __device__ __forceinline__ void fft2d_r2c_body(const Fwd2dParams &prm, unsigned 
         } else {
             const int row = (g & 1) ? rb : ra;
             if (!(g & 1) || hasb) {
+                mp += row * MRS;
+                mp[MidLayout<L, G>::slot(split_slot<L, G>(g, 0))] = make_float2(are[0], aim[0]);
+                int at = MidLayout<L, G>::slot(split_slot<L, G>(g, 1));
 #pragma unroll
-                for (int k = 0; k < L; ++k)
-                    mp[row * MRS + MidLayout<L, G>::slot(split_slot<L, G>(g, k))] = make_float2(are[k], aim[k]);
+                for (int k = 1; k < L; ++k, at += split_step(g)) mp[at] = make_float2(are[k], aim[k]);
             }
         }
     }
@@ -460,12 +508,19 @@ __device__ __forceinline__ void fft2d_r2c_body(const Fwd2dParams &prm, unsigned 
     float re[L], im[L];
     if (col_active) {
         const float2 *mp = mid + cp * prm.MPS + MidLayout<L, G>::slot(cc);
+        if constexpr (kWholeGroups<G>) {
+            each_of_line<L, G>(cg, h_in, [&](int m, bool in) {
+                const float2 v = in ? mp[(cg + G * m) * MRS] : make_float2(0.f, 0.f);
+                re[m] = v.x; im[m] = v.y;
+            });
+        } else {
 #pragma unroll
-        for (int m = 0; m < L; ++m) {
-            const int r = cg + G * m;
-            float2 v = make_float2(0.f, 0.f);
-            if (r < h_in) v = mp[r * MRS];
-            re[m] = v.x; im[m] = v.y;
+            for (int m = 0; m < L; ++m) {
+                const int r = cg + G * m;
+                float2 v = make_float2(0.f, 0.f);
+                if (r < h_in) v = mp[r * MRS];
+                re[m] = v.x; im[m] = v.y;
+            }
         }
         fft_lines<L, G, -1, kDeferHalf<G>>(re, im, cg, smem + prm.tw_off);
     }
@@ -518,16 +573,15 @@ __device__ __forceinline__ void fft2d_r2c_body(const Fwd2dParams &prm, unsigned 
             } else {
                 // even lanes hold the spectrum of column 0, odd lanes that of column N/2
                 const int k2 = (cg & 1) ? NH : 0;
+                int k1 = split_slot<L, G>(cg, 0);
+                const bool packed = k1 == 0;             // real bins 0 and N/2
+                st(k1, k2, ur[0], packed ? 0.f : ui[0]);
+                st(packed ? NH : N - k1, k2, packed ? ui[0] : ur[0], packed ? 0.f : -ui[0]);
+                k1 = split_slot<L, G>(cg, 1);
 #pragma unroll
-                for (int k = 0; k < L; ++k) {
-                    const int k1 = split_slot<L, G>(cg, k);
-                    if (k1 == 0) {                       // packed real bins 0 and N/2
-                        st(0, k2, ur[k], 0.f);
-                        st(NH, k2, ui[k], 0.f);
-                    } else {
-                        st(k1, k2, ur[k], ui[k]);
-                        st(N - k1, k2, ur[k], -ui[k]);
-                    }
+                for (int k = 1; k < L; ++k, k1 += split_step(cg)) {
+                    st(k1, k2, ur[k], ui[k]);
+                    st(N - k1, k2, ur[k], -ui[k]);
                 }
             }
         }
@@ -626,8 +680,7 @@ __device__ __forceinline__ void fft2d_c2r_body(const Inv2dParams &prm, unsigned 
             if constexpr (!std::is_same<SRC, StoredTile>::value)
                 src.template fill<N, T, BT>(smem, p0, np, tid);
             else if constexpr (CONV)   // whole tile (its padding planes are simply not used)
-                stage_linear<BT>(smem, prm.in + prm.lay.index(p0, 0, 0), (unsigned)T * N * NB * 2, tid,
-                                 prm.in_vec_ok != 0);
+                stage_whole<BT, T * N * NB * 2>(smem, prm.in + prm.lay.index(p0, 0, 0), tid, prm.in_vec_ok != 0);
             else
                 stage_linear<BT>(smem, prm.in + (size_t)p0 * N * NB * 2, (unsigned)np * N * NB * 2, tid,
                                  prm.in_vec_ok != 0);
@@ -636,19 +689,19 @@ __device__ __forceinline__ void fft2d_c2r_body(const Inv2dParams &prm, unsigned 
         float cre[L], cim[L];
         if (cp < np) {
             if constexpr (CONV) {
-                const float *base = (PRE ? pre_img : ISTAGE ? smem : prm.in + prm.lay.index(p0, 0, 0)) + cp;
-                const int tsh = prm.lay.tsh;
+                // (the layout's runs are as long as the tile: every offset but the first is a constant; with the run length
+                // as an argument every element had 64-bit address arithmetic, basis 16 8.3 us instead of 5.1, 14 5.8 instead of 5.0)
+                const float *base = (PRE ? pre_img : ISTAGE ? smem : prm.in + prm.lay.index(p0, 0, 0)) + cp + cg * NB * 2 * T;
+                const float *q = base + cc * 2 * T;
 #pragma unroll
-                for (int m = 0; m < L; ++m) {
-                    const int k1 = cg + G * m;
-                    const float *q = base + ((size_t)((k1 * NB + cc) * 2) << tsh);
-                    float xr = q[0], xi = q[(size_t)1 << tsh];
-                    if (cc == 0) {   // pack columns 0 and N/2:  z = y0 + i yN
-                        const float *qn = base + ((size_t)((k1 * NB + NH) * 2) << tsh);
-                        const float nr = qn[0], ni = qn[(size_t)1 << tsh];
-                        xr -= ni; xi += nr;
+                for (int m = 0; m < L; ++m) { cre[m] = q[G * m * NB * 2 * T]; cim[m] = q[G * m * NB * 2 * T + T]; }
+                if (cc == 0) {       // pack columns 0 and N/2:  z = y0 + i yN
+#pragma unroll
+                    for (int m = 0; m < L; ++m) {
+                        const float *qn = base + (G * m * NB + NH) * 2 * T;
+                        const float nr = qn[0], ni = qn[T];
+                        cre[m] -= ni; cim[m] += nr;
                     }
-                    cre[m] = xr; cim[m] = xi;
                 }
             } else {
                 const float2 *base = reinterpret_cast<const float2 *>(smem) + cp * N * NB;
@@ -670,9 +723,10 @@ __device__ __forceinline__ void fft2d_c2r_body(const Inv2dParams &prm, unsigned 
             // row a = k + L * block: k rows plus `block` whole blocks of L rows
             const int blk = group_block<G>(cg);
             float2 *mp = mid + cp * prm.MPS + cc + blk * (L * ML::MRS + ML::RP);
+            const int rows = h_out - L * blk;
 #pragma unroll
             for (int k = 0; k < L; ++k) {
-                if (k + L * blk < h_out) mp[k * ML::MRS] = make_float2(cre[k], cim[k]);
+                if (k < rows) mp[k * ML::MRS] = make_float2(cre[k], cim[k]);
             }
         }
     }
@@ -694,7 +748,7 @@ __device__ __forceinline__ void fft2d_c2r_body(const Inv2dParams &prm, unsigned 
             const int slot = (k2 == NH) ? 0 : (k2 < NH ? k2 : N - k2);
             const float2 a = A[slot];
             float2 b = B[slot];
-            if (!hasb) b = make_float2(0.f, 0.f);
+            if ((h_out & 1) && !hasb) b = make_float2(0.f, 0.f);   // (an even number of rows leaves none without a partner)
             float xr, xi;
             if (k2 == 0) { xr = a.x; xi = b.x; }
             else if (k2 == NH) { xr = a.y; xi = b.y; }
@@ -706,14 +760,15 @@ __device__ __forceinline__ void fft2d_c2r_body(const Inv2dParams &prm, unsigned 
     }
     __syncthreads();   // all reads of `mid` done; reuse the area as the output block
     if (active) {
-        float *oa = sout + (p * h_out + ra) * w_out;
-        float *ob = sout + (p * h_out + rb) * w_out;
+        const int b0 = L * group_block<G>(g), cols = w_out - b0;
+        float *oa = sout + (p * h_out + ra) * w_out + b0;
+        float *ob = sout + (p * h_out + rb) * w_out + b0;
+        const float scale = prm.scale;
 #pragma unroll
         for (int k = 0; k < L; ++k) {
-            const int b = k + L * group_block<G>(g);
-            if (b < w_out) {
-                oa[b] = re[k] * prm.scale;
-                if (hasb) ob[b] = im[k] * prm.scale;
+            if (k < cols) {
+                oa[k] = re[k] * scale;
+                if (hasb) ob[k] = im[k] * scale;
             }
         }
     }
@@ -844,12 +899,13 @@ __global__ void __launch_bounds__(TB / 2 * G) fft1d_r2c_kernel(Fwd1dParams prm) 
         } else {
             if (!(g & 1) || hasb) {
                 float2 *o = sout + ((g & 1) ? sb : sa) * NB;
+                int j = split_slot<L, G>(g, 0);
+                const bool packed = j == 0;              // real bins 0 and N/2
+                o[j] = make_float2(are[0], packed ? 0.f : aim[0]);
+                if (packed) o[NH] = make_float2(aim[0], 0.f);
+                j = split_slot<L, G>(g, 1);
 #pragma unroll
-                for (int k = 0; k < L; ++k) {
-                    const int j = split_slot<L, G>(g, k);
-                    if (j == 0) { o[0] = make_float2(are[k], 0.f); o[NH] = make_float2(aim[k], 0.f); }
-                    else o[j] = make_float2(are[k], aim[k]);
-                }
+                for (int k = 1; k < L; ++k, j += split_step(g)) o[j] = make_float2(are[k], aim[k]);
             }
         }
     }

@@ -100,8 +100,11 @@ __device__ __forceinline__ void fft2d_r2c_rect_body(const RectFwdParams &prm, un
         } else {
             const int row = (g & 1) ? rb : ra;
             if (!(g & 1) || hasb) {
+                mp += row * MRS;
+                mp[split_slot<LW, GW>(g, 0)] = make_float2(are[0], aim[0]);
+                int at = split_slot<LW, GW>(g, 1);
 #pragma unroll
-                for (int k = 0; k < LW; ++k) mp[row * MRS + split_slot<LW, GW>(g, k)] = make_float2(are[k], aim[k]);
+                for (int k = 1; k < LW; ++k, at += split_step(g)) mp[at] = make_float2(are[k], aim[k]);
             }
         }
     }
@@ -146,16 +149,15 @@ __device__ __forceinline__ void fft2d_r2c_rect_body(const RectFwdParams &prm, un
             }
         } else {
             const int k2 = (cg & 1) ? CH : 0;   // even lanes: column 0, odd lanes: column NC/2
+            int k1 = split_slot<LH, GH>(cg, 0);
+            const bool packed = k1 == 0;             // real bins 0 and NR/2
+            st(k1, k2, ur[0], packed ? 0.f : ui[0]);
+            st(packed ? RH : NR - k1, k2, packed ? ui[0] : ur[0], packed ? 0.f : -ui[0]);
+            k1 = split_slot<LH, GH>(cg, 1);
 #pragma unroll
-            for (int k = 0; k < LH; ++k) {
-                const int k1 = split_slot<LH, GH>(cg, k);
-                if (k1 == 0) {
-                    st(0, k2, ur[k], 0.f);
-                    st(RH, k2, ui[k], 0.f);
-                } else {
-                    st(k1, k2, ur[k], ui[k]);
-                    st(NR - k1, k2, ur[k], -ui[k]);
-                }
+            for (int k = 1; k < LH; ++k, k1 += split_step(cg)) {
+                st(k1, k2, ur[k], ui[k]);
+                st(NR - k1, k2, ur[k], -ui[k]);
             }
         }
     }

@@ -95,6 +95,21 @@ def test_c2r_2d(hd, n, B):
         assert _relerr(got, oracle.idft_c2r_2d(X, n, h_out, w_out)) <= TOL, (h_out, w_out)
 
 
+# Lines that end between the lanes of a group, odd numbers of rows (one without a partner) and outputs cut in the middle of a
+# lane's block.  A step of a transform adds at most about a rounding (2^-24) of the largest value, of either sign, and there are
+# 2 log2(n) steps: four times that many roundings in one direction.
+@pytest.mark.parametrize("n", [20, 28, 32, 36, 40, 48, 56, 64, 112, 128])
+def test_2d_lines_that_end_within_a_group_of_lanes(hd, n):
+    tol = 4 * 2.0 ** -24 * 2 * np.log2(n)
+    x = synth.normal01(21, 6, (9, n, n))
+    X = oracle.dft_r2c_2d(x, n).astype(np.complex64).astype(np.complex128)
+    for h, w in [(n - 1, n - 2), (n - 2, n - 3), (n - 5, n - 1), (7, 9), (n // 2 - 1, n // 2 + 3)]:
+        xs = np.ascontiguousarray(x[:, :h, :w])
+        assert _relerr(_c(hd.fft_r2c_2d(_dev(xs), n)), oracle.dft_r2c_2d(xs, n)) <= tol, (h, w)
+        got = hd.fft_c2r_2d(_cdev(X), n, h, w).cpu().numpy().astype(np.float64)
+        assert _relerr(got, oracle.idft_c2r_2d(X, n, h, w)) <= tol, (h, w)
+
+
 def _random_real_signal_spectrum(seed, B, n):
     """A random complex half spectrum [B, n, n/2+1] that is the transform of SOME real n x n
     signal without being computed from one: columns 0 < k2 < n/2 are free; the two
