@@ -1,4 +1,4 @@
-// Per-bin complex contraction for matrices with a narrow side or few tiles: 32x32 tiles whose reduction is
+// Per-bin complex contraction for matrices with a narrow side or few tiles: tiles of 32 or 16 rows whose reduction is
 // split over the waves of a workgroup, operands straight from memory into the matrix cores' registers.
 //
 // Same operation as cgemm_kernels.hip (the Cgemm row of Table 1 of the fbfft paper).  A 64x64 tile on a 16 x 6
@@ -12,6 +12,9 @@
 namespace fc {
 
 constexpr int kChunk = 8;       // reduction steps of a chunk: four of the matrix instruction, two halves of a wave
+constexpr int kChunk16 = 16;    // the same with 16-row tiles: four of the matrix instruction, four quarters of a wave
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 // How an operand's planes are addressed.  x: plane number from the start of the uniform base's plane tile.
 struct Planes {
@@ -20,12 +23,12 @@ struct Planes {
     __device__ __forceinline__ unsigned offset(unsigned x) const { return (x >> tsh) * tile_floats + (x & ((1u << tsh) - 1)); }
 };
 
-// One operand's chunk: lane (row = lane % 32, h = lane / 32) holds k0 + 4 h + 0 .. 3 of its row.  The matrix
-// instruction's step i then multiplies k0 + i and k0 + 4 + i; which pair is a step's does not matter as long
+// One operand's chunk: lane (row = lane % ROWS, h = lane / ROWS) holds k0 + 4 h + 0 .. 3 of its row.  The matrix
+// instruction's step i then multiplies k0 + 4 h + i for every h; which of them are a step's does not matter as long
 // as both operands agree.  KF: the reduction index is the contiguous plane index, else the row is.
 // Along the reduction a lane gathers 16 bytes, MODE 0 at any alignment; across it 4 bytes a step.  MODE 2: a lane's
 // part of the address never changes.
-template <bool KF, int MODE>
+template <bool KF, int MODE, int ROWS = 32>
 struct Strip {
     const float *base;          // bin's real parts, plane tile 0
     Planes pl;
@@ -41,7 +44,7 @@ struct Strip {
         rs = row_stride; cs = k_stride;
         im = 1u << lay.tsh;
         r0 = first;
-        row = lane_id & 31; h = lane_id >> 5;
+        row = lane_id % ROWS; h = lane_id / ROWS;
         if (r0 + row >= rows) row = rows - 1 - r0;         // (its results are not stored)
         if constexpr (MODE == 2) {
             if constexpr (KF) lane = pl.offset((unsigned)row * (unsigned)rs) + pl.offset(4u * h);
@@ -180,6 +183,105 @@ __device__ __forceinline__ void cgemm_direct_body(const GemmParams &prm, const i
     }
 }
 
+// A side of at most 16 (a few images served through a wide layer): 16x16x4 instructions, GA x GB of them a step, one
+// of the two 1 and the other 2.  Half of a 32-row tile's products and registers would be padding, and its waves wait for
+// memory: a chunk of 16 steps reads 64 bytes of a row at once (a whole run of 16 planes), keeps twice as many bytes in flight and
+// halves the chain of chunks; half the partial tiles let more workgroups in.  us a pass on weights ahead, 32-row tiles / these:
+// 8 x 256 -> 256, 27x27 87 / 61 (fprop and bprop; the contraction alone 236 MB, 76 / 50), 2 x 64 -> 256, 32x32 40 / 30, 7 x 130 -> 301,
+// 27x27 bprop 90 / 60, 11 x 64 -> 256, 10x10 15.4 / 13.6; accGrad of 128 x 16 -> 304, 32x32 141 / 121.  Over 105 passes of random
+// layers nothing was slower.
+template <bool AKF, bool BKF, int MODE, int GA, int GB>
+__device__ __forceinline__ void cgemm_direct16_body(const GemmParams &prm, const int group, const unsigned wg) {
+    constexpr int P = GA * GB;
+    extern __shared__ float red[];                  // [wave][component][product][register][lane]
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int waves = blockDim.x >> 6, slices = waves / group, slice = wave / group;
+    const int tiles = prm.tiles_m * prm.tiles_n, groups_per_xcd = prm.bins / group / kXcds;
+    const int xcd = wg % kXcds, slot = wg / kXcds;
+    const int bin = (xcd * groups_per_xcd + slot / tiles) * group + wave % group;
+    const int tile = slot % tiles;
+    const int m0 = (tile / prm.tiles_n) * 32, n0 = (tile % prm.tiles_n) * 32;
+
+    // Gauss's three products, as in cgemm_bins_kernel
+    floatx4 p1[P], p2[P], p3[P];
+#pragma unroll
+    for (int j = 0; j < P; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) { p1[j][v] = 0.f; p2[j][v] = 0.f; p3[j][v] = 0.f; }
+    if (bin < prm.live) {
+        Strip<AKF, MODE, 16> a[GA];
+        Strip<BKF, MODE, 16> b[GB];
+        // (a second strip past the end repeats the first; its results are not stored)
+#pragma unroll
+        for (int j = 0; j < GA; ++j)
+            a[j].init(prm.A, prm.layA, bin, prm.a_rs, prm.a_cs, m0 + 16 * j < prm.M ? m0 + 16 * j : m0, prm.M, lane);
+#pragma unroll
+        for (int j = 0; j < GB; ++j)
+            b[j].init(prm.B, prm.layB, bin, prm.b_cs, prm.b_rs, n0 + 16 * j < prm.N ? n0 + 16 * j : n0, prm.N, lane);
+        struct Chunk { float ar[GA][4], ai[GA][4], br[GB][4], bi[GB][4]; } now, next;
+        const int K = prm.K, step = slices * kChunk16;
+        auto fetch = [&](Chunk &x, int k0) {
+#pragma unroll
+            for (int j = 0; j < GA; ++j) a[j].load(x.ar[j], x.ai[j], k0, K);
+#pragma unroll
+            for (int j = 0; j < GB; ++j) b[j].load(x.br[j], x.bi[j], k0, K);
+        };
+        int k0 = slice * kChunk16;
+        fetch(next, k0);                              // (past the end: zeros)
+        while (k0 < K) {                              // the next chunk's loads are in flight while one is multiplied
+            now = next;
+            k0 += step;
+            fetch(next, k0);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < P; ++j) {
+                    const float ar = now.ar[j / GB][i], ai = flip(now.ai[j / GB][i], prm.a_sign);
+                    const float br = now.br[j % GB][i], bi = flip(now.bi[j % GB][i], prm.b_sign);
+                    p1[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar, br, p1[j], 0, 0, 0);
+                    p2[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ai, bi, p2[j], 0, 0, 0);
+                    p3[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar + ai, br + bi, p3[j], 0, 0, 0);
+                }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < P; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            red[(((wave * 2 + 0) * P + j) * 4 + v) * 64 + lane] = p1[j][v] - p2[j][v];
+            red[(((wave * 2 + 1) * P + j) * 4 + v) * 64 + lane] = p3[j][v] - p1[j][v] - p2[j][v];
+        }
+    __syncthreads();
+    // D layout of the 16x16x4 instruction: register v of lane l is row 4 (l / 16) + v, column l % 16.  The slices of a
+    // bin share its registers out.
+    if (bin >= prm.live) return;
+    const long pc = (long)m0 * prm.c_rs + n0;
+    Planes pl{(unsigned)prm.layC.bins * 2u << prm.layC.tsh, prm.layC.tsh};
+    float *cb = prm.C + prm.layC.index(0, bin, 0) + (size_t)(pc >> pl.tsh) * pl.tile_floats;
+    const unsigned within = (unsigned)pc & ((1u << pl.tsh) - 1);
+    const int per = P * 4 / slices;                 // (slices: at most eight, a power of two)
+    for (int r = slice * per; r < (slice + 1) * per; ++r) {
+        float cr = 0.f, ci = 0.f;
+        for (int s = 0; s < slices; ++s) {
+            const float *q = red + (((s * group + wave % group) * 2) * P * 4 + r) * 64 + lane;
+            cr += q[0];
+            ci += q[P * 4 * 64];
+        }
+        const int j = r / 4, mm = 16 * (j / GB) + 4 * (lane >> 4) + r % 4, nn = 16 * (j % GB) + (lane & 15);
+        if (m0 + mm < prm.M && n0 + nn < prm.N) {
+            float *q = cb + pl.offset(within + (unsigned)mm * (unsigned)prm.c_rs + nn);
+            q[0] = cr;
+            q[1u << pl.tsh] = ci;
+        }
+    }
+}
+
+template <bool AKF, bool BKF, int MODE, int GA, int GB>
+__global__ void __launch_bounds__(512, 4) cgemm_direct16_kernel(GemmParams prm, int group) {
+    cgemm_direct16_body<AKF, BKF, MODE, GA, GB>(prm, group, blockIdx.x);
+}
+
 template <bool AKF, bool BKF, int MODE>
 __global__ void __launch_bounds__(512, 4) cgemm_direct_kernel(GemmParams prm, int group) {
     cgemm_direct_body<AKF, BKF, MODE>(prm, group, blockIdx.x);
@@ -218,16 +320,16 @@ static long direct_tiles(const GemmParams &p) { return (long)((p.M + 31) / 32) *
 // Slices of the reduction, of at least one chunk each, until two waves a SIMD are there: over 630 products of random layers as fast as
 // any other number (1024 .. 2560 waves within 2 %), where 8192 with up to 16 waves a workgroup, whose partial tiles leave one workgroup a
 // compute unit, cost 8 % on runs of 16 planes.  Up to eight waves (64 KB of partial tiles, two workgroups a compute unit).
-static int direct_waves(int K, int group, long bin_tiles) {
+static int direct_waves(int K, int group, long bin_tiles, int chunk = kChunk) {
     int slices = 1;
-    while (slices * group < 8 && slices * kChunk < K && (slices * group < 4 || bin_tiles * slices < 2048)) slices *= 2;
+    while (slices * group < 8 && slices * chunk < K && (slices * group < 4 || bin_tiles * slices < 2048)) slices *= 2;
     return slices * group;
 }
 
 template <class P, class... Q>
-static hipError_t launch_direct(void (*k)(P, Q...), long grid, int waves, LaunchCtx st, const P &prm, Q... q) {
+static hipError_t launch_direct(void (*k)(P, Q...), long grid, int waves, int regs, LaunchCtx st, const P &prm, Q... q) {
     if (grid > 0x7fffffffL) return hipErrorInvalidValue;
-    const size_t lds = (size_t)waves * 2 * 16 * 64 * sizeof(float);
+    const size_t lds = (size_t)waves * 2 * regs * 64 * sizeof(float);
     if (hipError_t e = allow_big_lds((const void *)k, lds); e != hipSuccess) return e;
     if (st.start || st.stop) hipExtLaunchKernelGGL(k, dim3((unsigned)grid), dim3(64 * waves), (unsigned)lds, st.stream, st.start, st.stop, 0, prm, q...);
     else hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(64 * waves), lds, st.stream, prm, q...);
@@ -238,11 +340,29 @@ template <bool AKF, bool BKF>
 static hipError_t dispatch_direct(const GemmParams &prm, int group, int waves, LaunchCtx st) {
     const long grid = (long)(prm.bins / group) * prm.tiles_m * prm.tiles_n;
     const int mode = direct_mode(prm, AKF, BKF);
-    if (mode == 2) return launch_direct(cgemm_direct_kernel<AKF, BKF, 2>, grid, waves, st, prm, group);
+    if (mode == 2) return launch_direct(cgemm_direct_kernel<AKF, BKF, 2>, grid, waves, 16, st, prm, group);
     if constexpr (AKF || BKF) {
-        if (mode == 0) return launch_direct(cgemm_direct_kernel<AKF, BKF, 0>, grid, waves, st, prm, group);
+        if (mode == 0) return launch_direct(cgemm_direct_kernel<AKF, BKF, 0>, grid, waves, 16, st, prm, group);
     }
-    return launch_direct(cgemm_direct_kernel<AKF, BKF, 1>, grid, waves, st, prm, group);
+    return launch_direct(cgemm_direct_kernel<AKF, BKF, 1>, grid, waves, 16, st, prm, group);
+}
+
+// (direct_fits() bounds eight reduction steps to 2^32 bytes; offsets count floats, so sixteen fit, too)
+static bool direct_16(const GemmParams &p) { return p.M <= 16 || p.N <= 16; }
+
+template <bool AKF, bool BKF, int GA, int GB>
+static hipError_t dispatch_direct16(const GemmParams &prm, int group, LaunchCtx st) {
+    const long grid = (long)(prm.bins / group) * prm.tiles_m * prm.tiles_n;
+    const int mode = direct_mode(prm, AKF, BKF), waves = direct_waves(prm.K, group, prm.bins * direct_tiles(prm), kChunk16);
+    if (mode == 2) return launch_direct(cgemm_direct16_kernel<AKF, BKF, 2, GA, GB>, grid, waves, 8, st, prm, group);
+    if constexpr (AKF || BKF) {
+        if (mode == 0) return launch_direct(cgemm_direct16_kernel<AKF, BKF, 0, GA, GB>, grid, waves, 8, st, prm, group);
+    }
+    return launch_direct(cgemm_direct16_kernel<AKF, BKF, 1, GA, GB>, grid, waves, 8, st, prm, group);
+}
+template <bool AKF, bool BKF>
+static hipError_t dispatch_direct16(const GemmParams &prm, int group, LaunchCtx st) {
+    return prm.M <= 16 ? dispatch_direct16<AKF, BKF, 1, 2>(prm, group, st) : dispatch_direct16<AKF, BKF, 2, 1>(prm, group, st);
 }
 
 // Waves of the shared launch of two products.
@@ -254,6 +374,12 @@ hipError_t launch_cgemm_direct(GemmParams prm, bool akf, bool bkf, LaunchCtx st,
     prm.tiles_m = (prm.M + 31) / 32;
     prm.tiles_n = (prm.N + 31) / 32;
     const int group = direct_group(prm);
+    if (!partner && direct_16(prm)) {
+        if (akf && bkf) return dispatch_direct16<true, true>(prm, group, st);
+        if (akf && !bkf) return dispatch_direct16<true, false>(prm, group, st);
+        if (!akf && !bkf) return dispatch_direct16<false, false>(prm, group, st);
+        return dispatch_direct16<false, true>(prm, group, st);
+    }
     const int waves = partner ? direct_pair_waves(prm, *partner, group) : direct_waves(prm.K, group, prm.bins * direct_tiles(prm));
     if (akf && bkf) return dispatch_direct<true, true>(prm, group, waves, st);
     if (akf && !bkf) return dispatch_direct<true, false>(prm, group, waves, st);
@@ -270,9 +396,9 @@ hipError_t launch_cgemm_direct_pair(const GemmParams &bprop, const GemmParams &a
     if (grid > 0x7fffffffL) return hipErrorInvalidValue;
     dp.first = (unsigned)first;
     const int mb = direct_mode(bprop, true, false), ma = direct_mode(accgrad, false, false);
-    if (mb == 2 && ma == 2) return launch_direct(cgemm_direct_pair_kernel<2>, grid, waves, st, dp);
-    if (mb == 0) return launch_direct(cgemm_direct_pair_kernel<0>, grid, waves, st, dp);
-    return launch_direct(cgemm_direct_pair_kernel<1>, grid, waves, st, dp);
+    if (mb == 2 && ma == 2) return launch_direct(cgemm_direct_pair_kernel<2>, grid, waves, 16, st, dp);
+    if (mb == 0) return launch_direct(cgemm_direct_pair_kernel<0>, grid, waves, 16, st, dp);
+    return launch_direct(cgemm_direct_pair_kernel<1>, grid, waves, 16, st, dp);
 }
 
 }  // namespace fc

@@ -196,6 +196,15 @@ def test_reduction_split_over_waves(hd, S, f, fo, side):
     _check(hd, S, f, fo, side, side, 3, 2)
 
 
+# Sides of at most 16 on either matrix: one row, 15 and 16 rows, a second strip that is empty, part of one or full (columns 16,
+# 17, 33, 47, 64), reductions that end within a chunk of 16 and, at odd counts, within four steps.
+@pytest.mark.parametrize("side", [8, 13, 20, 32], ids=["run64", "run32", "run16", "run8"])
+@pytest.mark.parametrize("S,f,fo", [(1, 40, 33), (15, 36, 64), (16, 64, 47), (5, 37, 81), (9, 256, 17), (40, 16, 28), (70, 12, 100),
+                                    (3, 19, 16), (17, 90, 15)])
+def test_sides_of_at_most_sixteen(hd, S, f, fo, side):
+    _check(hd, S, f, fo, side, side, 3, 2)
+
+
 @pytest.mark.parametrize("S,f,fo,side", EDGES + SPLIT[::3])
 def test_the_kernels_that_these_replace_on_some_layers(lib, S, f, fo, side, monkeypatch):
     """With the split reductions switched off their layers run on the tiles that other layers still take."""
