@@ -171,13 +171,15 @@ struct Prepared {
 // what the bf16 cores do.  A tile of 32 reads its operands for half as many products, so a side above 32 (64 on runs of 32
 // and more, whose lines a strip uses whole) stays with 64x64 tiles (48 x 304 x 57 on 544 bins 50 / 68), and so do, unless the
 // tile of 64 would be half padding, grids of 32 tiles and more to a reduction step (9 x 256 x 32 on 312 bins 12.3 / 16.8), of 128
-// where the other kernel's gathers are of 4 bytes or runs of eight planes (1134 x 8 x 32 on 544 bins 63 / 83).
+// where the other kernel's gathers are of 4 bytes or runs of eight planes (1134 x 8 x 32 on 544 bins 63 / 83).  Sides of at most 16,
+// which have tiles of their own, are ahead on those grids, too (fprop of 8 x 32 -> 301, 21x21 27.9 / 24.7, 4 x 32 -> 130 21.3 / 19.1, 12 x 32 ->
+// 256, 17x17 20.0 / 19.4; 13 such passes of random layers 1.03 .. 1.36x, none slower).
 inline long tiles_32(const GemmParams &p) { return (long)p.bins * ((p.M + 31) / 32) * ((p.N + 31) / 32); }
 inline bool direct_pays(const Prepared &q) {
     const GemmParams &p = q.prm;
     if (q.split || p.layA.tsh < 3 || p.K <= 16) return false;
     if ((p.M < p.N ? p.M : p.N) > (p.layA.tsh >= 5 ? 64 : 32)) return false;
-    return tiles_32(p) == tiles_64(p) || tiles_32(p) < (q.vec && p.layA.tsh >= 4 ? 32L : 128L) * p.K;
+    return p.M <= 16 || p.N <= 16 || tiles_32(p) == tiles_64(p) || tiles_32(p) < (q.vec && p.layA.tsh >= 4 ? 32L : 128L) * p.K;
 }
 
 inline hipError_t prepare(const GemmProblem &g, const GemmSwitches &sw, Prepared *out) {

@@ -52,7 +52,8 @@ def test_split_reduction(rules):
     assert not split("fprop", 5, 8, 32, 13, 3)                   # one chunk
     assert not split("fprop", 128, 64, 64, 27, 5)                # wide
     assert not split("fprop", 128, 384, 384, 13, 3) and not split("fprop", 108, 290, 112, 8, 4)      # bf16
-    assert split("fprop", 3, 48, 320, 32, 3) and not split("fprop", 3, 24, 384, 32, 3)              # 128 tiles to a step
+    assert split("fprop", 3, 48, 320, 32, 3) and not split("fprop", 20, 24, 384, 32, 3)             # 128 tiles to a step
+    assert split("fprop", 16, 24, 384, 32, 3) and not split("fprop", 17, 24, 384, 32, 3)            # ... at sides above 16
     assert not split("fprop", 5, 176, 248, 40, 3)                # lines of four bins
     assert not split("fprop", 128, 3, 96, 128, 11)               # thin
 
