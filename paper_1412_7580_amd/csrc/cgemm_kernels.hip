@@ -604,14 +604,18 @@ static hipError_t run_tail(GemmParams prm, long full, long rem, LaunchCtx st) {
     return hipGetLastError();
 }
 
-static hipError_t launch_prepared(const Prepared &q, LaunchCtx st) {
+static hipError_t launch_prepared(const Prepared &q, Kernel kernel, LaunchCtx st) {
     const GemmParams &prm = q.prm;
     const GemmSwitches &sw = switches_of(st.sw);
-    if (q.thin != Thin::none) return launch_cgemm_thin(prm, q.thin, st);
-    if (q.direct_alone) return launch_cgemm_direct(prm, q.akf, q.bkf, st);
-    if (q.bingroup) return launch_cgemm_bingroup(prm, q.akf, q.bkf, st);
-    if (q.shifted) return launch_cgemm_bingroup_shifted(prm, q.akf, q.bkf, st);
-    if (q.split_alone) return launch_cgemm_split(prm, q.akf, q.bkf, q.vec, st);
+    switch (kernel) {
+        case Kernel::thin: return launch_cgemm_thin(prm, q.thin, st);
+        case Kernel::direct: return launch_cgemm_direct(prm, q.akf, q.bkf, st);
+        case Kernel::bingroup: return launch_cgemm_bingroup(prm, q.akf, q.bkf, st);
+        case Kernel::shifted: return launch_cgemm_bingroup_shifted(prm, q.akf, q.bkf, st);
+        case Kernel::split: return launch_cgemm_split(prm, q.akf, q.bkf, q.vec, st);
+        case Kernel::tiles: break;
+        case Kernel::product: return hipErrorInvalidValue;      // (launch_product_inverse)
+    }
     const int shape = pick_tile(sw, prm, q.vec);
     if (q.vec && shape == 3 && sw.tile < 0 && !sw.no_tail) {
         // a short last round (at most a quarter of the resident workgroups): split its tiles
@@ -644,7 +648,7 @@ hipError_t launch_product_inverse(const GemmProblem &g, float *out, int N, int h
     const GemmSwitches &sw = switches_of(st.sw);
     Prepared q;
     if (hipError_t e = prepare(g, sw, &q); e != hipSuccess) return e;
-    if (!product_inverse_pays(q, N)) return hipErrorNotSupported;
+    if (kernel_of_pass(q, N) != Kernel::product) return hipErrorNotSupported;
     return launch_fft2d_c2r_product(q.prm, out, N, h_out, w_out, scale, accumulate, st, view);
 }
 
@@ -692,18 +696,6 @@ static hipError_t pair_second(const Prepared &q2, GemmPairParams &pp, LaunchCtx 
     return run_pair<AKF1, BKF1, false, true>(pp, st);
 }
 
-// The shared launch of bprop and accGrad that a layer takes.
-enum class Shared { none, direct, form, scalar };
-static Shared shared_launch(const Prepared &q1, const Prepared &q2, const GemmSwitches &sw) {
-    if (sw.tile < 0 && !sw.no_pair) {
-        const Prepared &b = q1.akf ? q1 : q2, &a = q1.akf ? q2 : q1;
-        if (q1.akf != q2.akf && direct_pair_pays(b, a)) return Shared::direct;
-        if (pair_form(q1, q2, sw) != Pair::none) return Shared::form;
-        if (q1.akf != q2.akf && scalar_pair_pays(b, a)) return Shared::scalar;
-    }
-    return Shared::none;
-}
-
 bool cgemm_pair_supported(const GemmProblem &g1, const GemmProblem &g2, const GemmSwitches *swp) {
     const GemmSwitches &sw = switches_of(swp);
     Prepared q1, q2;
@@ -717,11 +709,11 @@ hipError_t launch_cgemm_bins(const GemmProblem &g, LaunchCtx st, const GemmProbl
     Prepared q, o;
     if (hipError_t e = prepare(g, sw, &q); e != hipSuccess) return e;
     if (partner && prepare(*partner, sw, &o) == hipSuccess) {
-        const Shared how = shared_launch(q, o, sw);
-        if (how == Shared::direct) return launch_cgemm_direct(q.prm, q.akf, q.bkf, st, &o.prm);
-        if (how != Shared::none) q.direct_alone = false;
+        const Lone lone = lone_gradient(q, o, sw);
+        if (lone.as_shared) return launch_cgemm_direct(q.prm, q.akf, q.bkf, st, &o.prm);
+        return launch_prepared(q, lone.kernel, st);
     }
-    return launch_prepared(q, st);
+    return launch_prepared(q, kernel_alone(q), st);
 }
 
 hipError_t launch_cgemm_pair(const GemmProblem &g1, const GemmProblem &g2, LaunchCtx st) {
@@ -735,7 +727,7 @@ hipError_t launch_cgemm_pair(const GemmProblem &g1, const GemmProblem &g2, Launc
     GemmPairParams pp;
     pp.p1 = q1.prm; pp.p2 = q2.prm; pp.n1 = 0;
     if (how == Shared::scalar) return run_scalar_pair(pp, q1.akf, st);
-    if (pair_form(q1, q2, sw) == Pair::split) return launch_cgemm_split_pair(q1.prm, q1.akf, q2.prm, st);
+    if (how == Shared::split) return launch_cgemm_split_pair(q1.prm, q1.akf, q2.prm, st);
     if (q1.akf && q1.bkf) return pair_second<true, true>(q2, pp, st);
     if (q1.akf && !q1.bkf) return pair_second<true, false>(q2, pp, st);
     if (!q1.akf && !q1.bkf) return pair_second<false, false>(q2, pp, st);

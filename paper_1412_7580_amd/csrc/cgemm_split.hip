@@ -311,7 +311,7 @@ hipError_t launch_cgemm_split(GemmParams p, bool akf, bool bkf, bool vec, Launch
     return hipGetLastError();
 }
 
-// Both with 16-byte gathers (pair_form()).
+// Both with 16-byte gathers (shared_launch()).
 hipError_t launch_cgemm_split_pair(const GemmParams &p1, bool akf1, const GemmParams &p2, LaunchCtx st) {
     SplitPairParams pp{p1, p2, 0};
     const long n1 = tile_grid(pp.p1), n2 = tile_grid(pp.p2);

@@ -235,6 +235,20 @@ inline bool product_inverse_pays(const Prepared &q, int basis) {
     return basis <= 24 || (q.prm.K <= 3 && (long)q.prm.M * q.prm.N >= 1024);
 }
 
+// The kernel that a contraction takes in a launch of its own.
+enum class Kernel { product, thin, direct, bingroup, shifted, split, tiles };
+inline Kernel kernel_alone(const Prepared &q) {
+    if (q.thin != Thin::none) return Kernel::thin;
+    if (q.direct_alone) return Kernel::direct;
+    if (q.bingroup) return Kernel::bingroup;
+    if (q.shifted) return Kernel::shifted;
+    return q.split_alone ? Kernel::split : Kernel::tiles;
+}
+// With the inverse transform behind it; basis: the square basis of the pass, 0 for a rectangular one.
+inline Kernel kernel_of_pass(const Prepared &q, int basis) {
+    return basis && product_inverse_pays(q, basis) ? Kernel::product : kernel_alone(q);
+}
+
 // But for narrow sides, 64x64 tiles on four waves with one tile of register staging ahead (shape 3)
 // measured fastest of the fp32 kernel's shapes for every layer tried (more workgroups in flight beat
 // the larger tiles' operand reuse and the deeper staging's registers).
@@ -297,18 +311,35 @@ inline bool scalar_pair_pays(const Prepared &b, const Prepared &a) {
 
 // Two contractions in one launch: bprop and accGrad of a layer, which share operand A and neither of
 // which waits for the other.
-enum class Pair { none, tiles, split };
-inline Pair pair_form(const Prepared &q1, const Prepared &q2, const GemmSwitches &sw) {
-    if (sw.tile >= 0 || sw.no_pair) return Pair::none;       // A/B runs of single-kernel shapes
-    if (!q1.vec || !q2.vec || q1.bingroup || q2.bingroup) return Pair::none;
+enum class Shared { none, direct, tiles, split, scalar };
+inline Shared shared_launch(const Prepared &q1, const Prepared &q2, const GemmSwitches &sw) {
+    if (sw.tile >= 0 || sw.no_pair) return Shared::none;     // A/B runs of single-kernel shapes
     const Prepared &b = q1.akf ? q1 : q2, &a = q1.akf ? q2 : q1;
-    if (!shared_launch_pays(b, a)) return Pair::none;
-    if (b.thin != Thin::none || a.thin != Thin::none) return Pair::tiles;
-    if (q1.bkf || q2.bkf || q1.akf == q2.akf) return Pair::tiles;
-    if (!b.split || !a.split) return Pair::tiles;
-    // Under general addressing small grids are behind (128 x 48 -> 48, 7x7, 40 tiles 27.6 / 29.0; 128 x 32 -> 96, 80 28.5 /
-    // 29.6; 64 x 96 -> 96, 160 26.3 / 26.3; 64 x 32 -> 384, 240 53.0 / 51.3).
-    return a.prm.fast || tiles_64(a.prm) >= 100 ? Pair::split : Pair::tiles;
+    const bool apart = q1.akf != q2.akf;
+    if (apart && direct_pair_pays(b, a)) return Shared::direct;
+    if (q1.vec && q2.vec && !q1.bingroup && !q2.bingroup && shared_launch_pays(b, a)) {
+        if (b.thin != Thin::none || a.thin != Thin::none) return Shared::tiles;
+        if (q1.bkf || q2.bkf || !apart) return Shared::tiles;
+        if (!b.split || !a.split) return Shared::tiles;
+        // Under general addressing small grids are behind (128 x 48 -> 48, 7x7, 40 tiles 27.6 / 29.0; 128 x 32 -> 96, 80 28.5 /
+        // 29.6; 64 x 96 -> 96, 160 26.3 / 26.3; 64 x 32 -> 384, 240 53.0 / 51.3).
+        return a.prm.fast || tiles_64(a.prm) >= 100 ? Shared::split : Shared::tiles;
+    }
+    return apart && scalar_pair_pays(b, a) ? Shared::scalar : Shared::none;
+}
+
+// One gradient of a backward pass asked for alone: the kernel that it takes, and whether that is the direct kernel on the
+// waves of the shared launch.
+struct Lone {
+    Kernel kernel;
+    bool as_shared;
+};
+inline Lone lone_gradient(const Prepared &q, const Prepared &partner, const GemmSwitches &sw) {
+    const Shared how = shared_launch(q, partner, sw);
+    if (how == Shared::direct) return {Kernel::direct, true};
+    Prepared own = q;
+    if (how != Shared::none) own.direct_alone = false;
+    return {kernel_alone(own), false};
 }
 
 }  // namespace fc

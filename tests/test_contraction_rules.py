@@ -1,50 +1,15 @@
-"""Which kernel runs a contraction, asked of the library's own rules on the CPU (a small program around
-the header that holds them), for the matrices that the planner gives each pass of a layer."""
-import ctypes
+"""Which kernel runs a contraction, asked of the library's own rules on the CPU, and that the GPU tests' layers reach every
+kernel."""
 import importlib.util
 import os
-import subprocess
 
 import pytest
 
+import contraction_rules
 import paper_1412_7580_amd as pkg
+from contraction_rules import PASSES
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
-PASSES = {"fprop": pkg.FPROP, "bprop": pkg.BPROP, "accgrad": pkg.ACCGRAD}
-
-
-class Rules:
-    def __init__(self, path):
-        self._lib = ctypes.CDLL(path)
-
-    @staticmethod
-    def _matrix(pass_, S, f, fo, h, w, kh, kw, basis=-1):
-        d = pkg.describe_plan(PASSES[pass_], S, f, fo, h, w, kh, kw, basis)
-        return (ctypes.c_long * 11)(d["M"], d["N"], d["K"], d["bins"], d["tile_log2"], d["a_rs"], d["a_cs"], d["b_rs"],
-                                    d["b_cs"], d["c_rs"], d["c_cs"])
-
-    def _ask(self, pass_, layer, tile):
-        out = (ctypes.c_int * 9)()
-        assert self._lib.rules_single(self._matrix(pass_, *layer), (ctypes.c_long * 2)(tile, 0), out) == 0
-        return list(out)
-
-    def rows(self, pass_, *layer):
-        return self._ask(pass_, layer, -1)[8]
-
-    def single(self, pass_, *layer, tile=-1):
-        """(kernel, gathers): kernel one of thin_k, thin_n, thin_acc, bin4, bf16, tile<shape>; gathers one of
-        fast, vec, scalar."""
-        _, _, vec, fast, thin, bin4, bf16, shape, _ = self._ask(pass_, layer, tile)
-        gathers = "fast" if fast else "vec" if vec else "scalar"
-        if thin:
-            return ("thin_k", "thin_n", "thin_acc")[thin - 1], gathers
-        return ("bin4" if bin4 else "bf16" if bf16 else f"tile{shape}"), gathers
-
-    def pair(self, *layer, no_pair=False):
-        got = self._lib.rules_pair(self._matrix("bprop", *layer), self._matrix("accgrad", *layer),
-                                   (ctypes.c_long * 2)(-1, no_pair))
-        return ("two launches", "tiles", "bf16")[got]
 
 
 def _module(path):
@@ -56,11 +21,7 @@ def _module(path):
 
 @pytest.fixture(scope="module")
 def rules(tmp_path_factory):
-    path = str(tmp_path_factory.mktemp("rules") / "rules.so")
-    subprocess.check_call([os.path.join(ROCM, "llvm", "bin", "clang++"), "-std=c++17", "-O1", "-fPIC", "-shared", "-x", "c++",
-                           "-D__HIP_PLATFORM_AMD__", "-I" + os.path.join(ROCM, "include"), "-Wno-unused-function",
-                           os.path.join(HERE, "contraction_rules", "rules.cpp"), "-o", path])
-    return Rules(path)
+    return contraction_rules.build(tmp_path_factory.mktemp("rules"))
 
 
 def _layer(S, f, fo, h, k):
@@ -71,9 +32,11 @@ def test_ordinary_layers(rules):
     assert rules.single("fprop", *_layer(128, 64, 64, 27, 5)) == ("tile3", "fast")
     assert rules.single("fprop", *_layer(128, 384, 384, 13, 3)) == ("bf16", "fast")
     assert rules.single("fprop", *_layer(32, 128, 128, 64, 31)) == ("bin4", "fast")
-    assert rules.single("fprop", *_layer(128, 3, 96, 128, 11)) == ("thin_k", "scalar")
+    assert rules.single("fprop", *_layer(128, 3, 96, 128, 11)) == ("product", "scalar")
     assert rules.single("accgrad", *_layer(128, 3, 96, 128, 11)) == ("thin_acc", "scalar")
-    assert rules.single("fprop", *_layer(8, 256, 256, 27, 5)) == ("tile6", "fast")
+    assert rules.single("fprop", *_layer(8, 256, 256, 27, 5)) == ("direct", "fast")
+    assert rules.single("fprop", *_layer(8, 256, 256, 27, 5), no_direct=True) == ("tile6", "fast")
+    assert rules.single("fprop", *_layer(20, 32, 128, 28, 3)) == ("tile6", "fast")
     assert rules.single("bprop", *_layer(50, 37, 75, 30, 7)) == ("tile3", "scalar")
     assert rules.pair(*_layer(128, 64, 64, 27, 5)) == "tiles"
     assert rules.pair(*_layer(128, 384, 384, 13, 3)) == "bf16"
@@ -139,17 +102,18 @@ def test_thin_products_that_another_kernel_does_faster(rules):
         assert rules.single("bprop", *_layer(*layer))[0] == "bin4", layer
     for layer in ((128, 4, 64, 56, 5), (256, 4, 16, 64, 5), (8, 3, 64, 40, 5), (64, 3, 384, 56, 5), (128, 3, 384, 40, 5)):
         assert rules.single("bprop", *_layer(*layer))[0] == "thin_n", layer
-    assert rules.single("bprop", *_layer(64, 3, 384, 40, 5)) == ("tile3", "scalar")
+    assert rules.single("bprop", *_layer(64, 3, 384, 40, 5)) == ("shifted", "scalar")
     for layer in ((32, 4, 256, 56, 5), (64, 4, 256, 48, 5), (256, 4, 256, 40, 5)):
         assert rules.single("fprop", *_layer(*layer))[0] == "bin4", layer
-    for layer in ((16, 4, 256, 64, 5), (128, 4, 64, 56, 5), (128, 4, 16, 40, 5), (128, 3, 384, 56, 5)):
+    for layer in ((16, 4, 256, 64, 5), (128, 4, 64, 56, 5), (128, 4, 16, 40, 5)):
         assert rules.single("fprop", *_layer(*layer))[0] == "thin_k", layer
+    assert rules.single("fprop", *_layer(128, 3, 384, 56, 5))[0] == "product"
     assert rules.single("bprop", *_layer(128, 256, 4, 56, 5))[0] == "thin_k"
     assert rules.single("fprop", *_layer(128, 4, 4, 8, 3))[0] == "tile3"
-    assert rules.single("fprop", *_layer(128, 4, 4, 20, 3))[0] == "thin_k"
-    assert rules.single("fprop", *_layer(512, 4, 4, 8, 3))[0] == "thin_k"
-    for layer, kernel in (((1, 64, 64, 56, 3), "thin_k"), ((1, 128, 256, 56, 3), "bin4"), ((1, 256, 256, 40, 5), "bin4"),
-                          ((1, 256, 256, 56, 5), "thin_k"), ((1, 128, 129, 48, 5), "thin_k"), ((256, 4, 256, 64, 5), "bin4"),
+    assert rules.single("fprop", *_layer(128, 4, 4, 20, 3))[0] == "product"
+    assert rules.single("fprop", *_layer(512, 4, 4, 8, 3))[0] == "product"
+    for layer, kernel in (((1, 64, 64, 56, 3), "product"), ((1, 128, 256, 56, 3), "bin4"), ((1, 256, 256, 40, 5), "bin4"),
+                          ((1, 256, 256, 56, 5), "product"), ((1, 128, 129, 48, 5), "product"), ((256, 4, 256, 64, 5), "bin4"),
                           ((256, 4, 64, 64, 5), "thin_acc"), ((256, 4, 256, 56, 5), "thin_acc")):
         assert rules.single("accgrad", *_layer(*layer))[0] == kernel, layer
 
@@ -191,40 +155,52 @@ def test_the_gpu_test_reaches_every_kernel(rules):
     """Every kernel that a contraction can take, with every kind of gather and operand order it is built
     for, with rows, columns and reduction that leave a remainder, on short and on long runs."""
     gpu = _module(os.path.join(HERE, "test_gpu_contraction.py"))
-    params = lambda test: next(m.args[1] for m in test.pytestmark if m.name == "parametrize" and m.args[0] == "S,f,fo")
-    layers = [(S, f, fo, h, h, 3, 2) for S, f, fo, h in gpu.EDGES]
+    params = lambda test, names="S,f,fo": next(m.args[1] for m in test.pytestmark if m.name == "parametrize" and m.args[0] == names)
+    layers = [(S, f, fo, h, h, 3, 2) for S, f, fo, h in gpu.EDGES + gpu.SPLIT + params(gpu.test_any_channel_counts_on_runs_of_four, "S,f,fo,side")]
     layers += [(*c, h, h, 3, 3) for c in params(gpu.test_thin_sides) for h in gpu.SIDES.values()]
-    layers += [(*c, h, h, 3, 2) for c in params(gpu.test_tile_edges) for h in (8, 13, 20, 32)]
+    layers += [(*c, h, h, 3, 2) for t in (gpu.test_tile_edges, gpu.test_sides_of_at_most_sixteen) for c in params(t) for h in (8, 13, 20, 32)]
     got, ragged, pairs, walks = set(), set(), set(), set()
     for layer in layers:
         for p in PASSES:
             d = pkg.describe_plan(PASSES[p], *layer)
             kernel, gathers = rules.single(p, *layer)
             runs = "long" if d["tile_log2"] >= 5 else "short"
+            if kernel == "direct":
+                kernel += "16" if min(d["M"], d["N"]) <= 16 else "32"
             got.add((kernel, gathers, p, runs))
-            tm, tn = {"tile6": (32, 128), "tile7": (128, 32)}.get(kernel, (64, 64))
-            for side, v in (("M", d["M"] % tm), ("N", d["N"] % tn), ("K", d["K"] % 16)):
+            tm, tn = {"tile6": (32, 128), "tile7": (128, 32), "direct16": (16, 16), "direct32": (32, 32), "shifted": (32, 32)}.get(kernel, (64, 64))
+            for side, v in (("M", d["M"] % tm), ("N", d["N"] % tn), ("K", d["K"] % (8 if kernel == "direct32" else 16))):
                 if v:
                     ragged.add((kernel, side))
             if kernel == "thin_k":
                 walks.add((p, rules.rows(p, *layer) > 1, min(d["K"], 4)))
+            if kernel == "product":
+                walks.add((p, "product", d["K"]))
         pairs.add((rules.pair(*layer), rules.single("bprop", *layer)[1],
                    rules.single("accgrad", *layer)[0].startswith("thin") or rules.single("bprop", *layer)[0].startswith("thin")))
     missing = []
     for p in PASSES:
         for runs in ("long", "short"):
-            missing += [k for k in (("bf16", "fast", p, runs), ("tile3", "fast", p, runs), ("tile3", "vec", p, runs),
-                                    ("tile3", "scalar", p, runs)) if k not in got]
+            missing += [k for k in (("bf16", "fast", p, runs), ("tile3", "vec", p, runs), ("tile3", "scalar", p, runs)) if k not in got]
+            # (fprop and bprop with fast addressing on long runs have a reduction of 32 and more: what the bf16 kernel leaves of
+            # them is the direct kernel's or the narrow tiles')
+            if runs == "short" or p == "accgrad":
+                missing += [("tile3", "fast", p, runs)] * (("tile3", "fast", p, runs) not in got)
         for g in ("fast", "vec"):
             missing += [("narrow", g, p)] * (not any((t, g, p, r) in got for t in ("tile6", "tile7") for r in ("long", "short")))
+        missing += [(d, g, p) for d in ("direct16", "direct32") for g in ("fast", "vec", "scalar")
+                    if not any((d, g, p, r) in got for r in ("long", "short"))]
         missing += [("bin4", p)] * (("bin4", "fast", p, "short") not in got)
+        missing += [("shifted", p)] * (("shifted", "scalar", p, "short") not in got)
         missing += [("bf16", "vec", p)] * (("bf16", "vec", p, "long") not in got or ("bf16", "vec", p, "short") not in got)
     missing += [("bf16", "scalar", r) for r in ("long", "short") if ("bf16", "scalar", "accgrad", r) not in got]
     missing += [(t, g) for t in ("tile6", "tile7") for g in ("fast", "vec") if not any(k[:2] == (t, g) for k in got)]
-    missing += [(k, s) for k in ("tile3", "tile6", "tile7", "bf16") for s in "MNK" if (k, s) not in ragged]
+    missing += [(k, s) for k in ("tile3", "tile6", "tile7", "bf16", "direct16", "direct32", "shifted") for s in "MNK" if (k, s) not in ragged]
     missing += [t for t in ("thin_n", "thin_acc") if not any(k[0] == t for k in got)]
-    missing += [w for w in (("fprop", True, 3), ("bprop", True, 3), ("fprop", False, 4), ("bprop", False, 4), ("bprop", False, 1),
-                            ("accgrad", False, 1)) if w not in walks]
+    missing += [w for w in (("fprop", True, 4), ("bprop", True, 4), ("fprop", False, 3), ("bprop", False, 3), ("bprop", False, 1),
+                            ("fprop", "product", 1), ("fprop", "product", 3), ("fprop", "product", 4), ("bprop", "product", 2),
+                            ("bprop", "product", 3), ("bprop", "product", 4), ("accgrad", "product", 1)) if w not in walks]
     missing += [q for q in (("bf16", "fast", False), ("bf16", "vec", False), ("tiles", "fast", False), ("tiles", "vec", False),
-                            ("tiles", "vec", True), ("two launches", "scalar", True)) if q not in pairs]
+                            ("tiles", "vec", True), ("two launches", "scalar", True), ("direct", "scalar", False), ("direct", "vec", False),
+                            ("direct", "fast", False), ("scalar", "scalar", False)) if q not in pairs]
     assert not missing, missing

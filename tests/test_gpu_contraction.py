@@ -85,6 +85,9 @@ EDGES = [
     (130, 123, 127, 13), (130, 123, 127, 20), (131, 125, 129, 8),                                       # bf16, 4-byte gathers
     (160, 4, 8, 40), (90, 3, 96, 40), (90, 96, 3, 40), (260, 4, 4, 8), (20, 4, 12, 20), (12, 40, 4, 13),  # thin sides
     (1, 36, 44, 20), (1, 64, 64, 40), (33, 64, 64, 40),
+    (20, 32, 128, 28), (20, 128, 32, 28), (33, 128, 32, 28), (32, 32, 256, 16), (20, 36, 132, 28), (36, 132, 28, 28),   # 32x128
+    (130, 32, 32, 28), (33, 32, 128, 28), (130, 36, 28, 28), (130, 28, 36, 28), (36, 28, 132, 28),           # 128x32
+    (150, 4, 96, 40), (150, 96, 4, 40), (40, 12, 2, 20),                                                # thin sides
 ]
 
 
