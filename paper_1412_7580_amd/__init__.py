@@ -183,6 +183,8 @@ class Handle:
     def _sync_stream(self):
         # The current device's current stream by its raw handle: torch.cuda.current_stream() builds a Stream object
         # for it, 2.8 us of the 7.2 that a one-kernel call took (the launch itself is 2.6); this is 0.2.
+        if not torch.cuda.is_initialized():
+            torch.cuda.init()          # refuses a process that was forked after the device's initialisation
         s = torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         if s != self._stream:          # the handle keeps its stream: tell it only about changes
             _check(self._lib.fftconv_set_stream(self._h, ctypes.c_void_p(s)), "fftconv_set_stream")

@@ -1,0 +1,25 @@
+"""The Python binding's own checks, on the CPU: no handle is created, no device is touched."""
+import pytest
+import torch
+
+import paper_1412_7580_amd as pkg
+
+
+class NoCalls:
+    """Stands in for the library: any call is a mistake."""
+
+    def __getattr__(self, name):
+        raise AssertionError(f"{name} was called")
+
+
+def test_a_handle_in_a_forked_process_is_refused(monkeypatch):
+    """As torch's own stream query does: the device must not be touched from a child forked after its initialisation."""
+    pkg.load_library()
+    h = pkg.Handle.__new__(pkg.Handle)
+    h._lib, h._h, h.device, h._stream = NoCalls(), None, 0, 0
+    monkeypatch.setattr(torch.cuda, "_initialized", True)
+    monkeypatch.setattr(torch.cuda, "_is_in_bad_fork", lambda: True)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 0)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda d: 0)
+    with pytest.raises(RuntimeError, match="forked subprocess"):
+        h._sync_stream()
