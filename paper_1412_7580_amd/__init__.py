@@ -185,7 +185,10 @@ class Handle:
         # for it, 2.8 us of the 7.2 that a one-kernel call took (the launch itself is 2.6); this is 0.2.
         if not torch.cuda.is_initialized():
             torch.cuda.init()          # refuses a process that was forked after the device's initialisation
-        s = torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        try:
+            s = torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:         # (not part of torch's interface)
+            s = torch.cuda.current_stream().cuda_stream
         if s != self._stream:          # the handle keeps its stream: tell it only about changes
             _check(self._lib.fftconv_set_stream(self._h, ctypes.c_void_p(s)), "fftconv_set_stream")
             self._stream = s

@@ -23,3 +23,26 @@ def test_a_handle_in_a_forked_process_is_refused(monkeypatch):
     monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda d: 0)
     with pytest.raises(RuntimeError, match="forked subprocess"):
         h._sync_stream()
+
+
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_the_stream_without_the_private_queries(monkeypatch, missing):
+    """torch's raw-handle queries are not part of its interface: without them the public one serves."""
+    class Stream:
+        cuda_stream = 0x1234
+
+    told = []
+
+    class Library(NoCalls):
+        def fftconv_set_stream(self, handle, stream):
+            told.append(stream.value)
+            return 0
+
+    pkg.load_library()
+    h = pkg.Handle.__new__(pkg.Handle)
+    h._lib, h._h, h.device, h._stream = Library(), None, 0, 0
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", Stream)
+    monkeypatch.delattr(torch._C, missing)
+    h._sync_stream()
+    assert told == [0x1234] and h._stream == 0x1234
