@@ -121,7 +121,6 @@ static hipError_t dispatch_product(int N, const ProductTile &src, float *out, lo
         case 40: return run_product<10, 4, 4>(src, out, planes, h, w, scale, acc, st, view);
         case 48: return run_product<12, 4, 4>(src, out, planes, h, w, scale, acc, st, view);
         case 56: return run_product<14, 4, 4>(src, out, planes, h, w, scale, acc, st, view);
-        case 64: return run_product<8, 8, 4>(src, out, planes, h, w, scale, acc, st, view);
         default: return hipErrorNotSupported;
     }
 }

@@ -189,7 +189,7 @@ struct GemmProblem {
 hipError_t launch_cgemm_bins(const GemmProblem &g, LaunchCtx st, const GemmProblem *partner = nullptr);
 
 // A contraction whose reduction has at most four terms as the input of the inverse transform (square bases up
-// to 64): the product never stands in memory.  hipErrorNotSupported, with nothing launched, where it does not apply or
+// to 56): the product never stands in memory.  hipErrorNotSupported, with nothing launched, where it does not apply or
 // is not the faster way.  `out` and `view` as launch_fft2d_c2r has them.
 hipError_t launch_product_inverse(const GemmProblem &g, float *out, int N, int h_out, int w_out, float scale,
                                   bool accumulate, LaunchCtx st, const PlaneView *view);
