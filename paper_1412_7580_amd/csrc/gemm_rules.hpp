@@ -230,9 +230,28 @@ inline hipError_t prepare(const GemmProblem &g, const GemmSwitches &sw, Prepared
 // few rounds of workgroups, 128 x 3 -> 64, 28x28 39.2 / 30.8, 56x56 75.8 / 72.8, 64 x 2 -> 20, 56x56 36.8 / 31.5, but 8 x 3 -> 16,
 // 56x56 22.8 / 24.0; a fourth term's loads cost more than the trip (128 x 4 -> 64, 56x56 79.7 / 87.7, 16 x 4 -> 16, 28x28 22.2 /
 // 25.5), and basis 64's tile leaves the fewest workgroups to hide them (128 x 3 -> 64 100 / 135).
+// On basis 28 the ordinary inverse has a lane a line, which with three terms is ahead on full grids (bprop 480 x 36 -> 3, 27x27 46.2 / 52.3, 64 x 304
+// -> 3 47.5 / 53.3, fprop 300 x 3 -> 64, 28x28 47.4 / 56.8), but for bprop's wide results in whole pairs of tiles (64 x 384 -> 3, 28x28 56.6 / 55.1).
+// Four terms on bases up to 24, over 450 layers (weights ahead, fprop / bprop).  fprop, whose columns are four planes apart, gathers whole
+// lines of the weights for each: only small results above basis 14 (233 x 4 -> 316, 16x16 46.3 / 56.5; 280 x 4 -> 128, 18x18 43.1 / 51.5;
+// 379 x 4 -> 68, 24x24 54.9 / 70.9), on basis 16 not the smallest (1 x 4 -> 368 12.7 / 13.5), on 18 and 20 the smallest where a tile holds whole
+// quads or rows of columns (34 x 4 -> 8, 18x18 15.2 / 15.7, 301 x 4 -> 4 16.7 / 15.4; 10 x 4 -> 28, 20x20 14.3 / 16.5), on 24 with four columns (52 x 4
+// -> 28 19.2 / 23.1, 416 x 4 -> 4 20.8 / 18.9).  bprop is behind on basis 24 alone, where columns do not fill a tile (11 x 12 -> 4, 23x23 15.6 / 16.9).
 inline bool product_inverse_pays(const Prepared &q, int basis) {
     if (q.thin != Thin::k || basis > 56) return false;
-    return basis <= 24 || (q.prm.K <= 3 && (long)q.prm.M * q.prm.N >= 1024);
+    const int N = q.prm.N;
+    const long planes = (long)q.prm.M * N;
+    if (q.prm.K <= 3) {
+        if (basis == 28 && q.prm.K == 3 && planes >= 16384) return !q.bkf && N >= 192 && N % 32 == 0;
+        return basis <= 24 || planes >= 1024;
+    }
+    if (basis > 24) return false;
+    if (!q.bkf) return basis <= 20 || N % 16 == 0 || planes >= 3000 || (N == 4 && planes >= 960);
+    if (basis <= 12) return true;
+    if (basis == 14) return planes < 65536;
+    if (basis == 16) return planes >= 1024 && planes < 65536;
+    if (basis == 24) return N == 4 && planes >= 960;
+    return N == 4 || (planes < 12000 && (N == 16 || planes >= 2400));
 }
 
 // The kernel that a contraction takes in a launch of its own.

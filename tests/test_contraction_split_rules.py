@@ -1,5 +1,8 @@
 """Which layers take the contraction kernels that split the reduction over waves, shift lines of four planes or form the
 product inside the inverse transform: the library's own rules asked on the CPU, on both sides of each line."""
+import importlib.util
+import os
+
 import pytest
 
 import contraction_rules
@@ -59,3 +62,36 @@ def test_product_inside_the_inverse_transform(rules):
     assert product("bprop", 64, 384, 3, 28, 5) and product("fprop", 64, 1, 32, 56, 7)
     assert not product("fprop", 8, 3, 16, 56, 7) and not product("fprop", 128, 4, 64, 56, 5)
     assert not product("fprop", 128, 3, 64, 64, 7) and not product("fprop", 128, 5, 64, 13, 3)
+
+
+def test_four_terms_and_full_grids_outside_the_inverse_transform(rules):
+    """Where two kernels are the faster way: a fourth term's gathers on bases 16 .. 24, weights with many rows first, and the
+    four-lane inverse of basis 28 on large grids."""
+    product = lambda p, *layer: rules.single(p, *_layer(*layer))[0] == "product"
+    for layer in ((52, 4, 28, 24, 2), (33, 4, 72, 23, 3), (54, 4, 4, 24, 7), (1, 4, 368, 16, 3), (233, 4, 316, 16, 3),
+                  (280, 4, 128, 18, 3), (34, 4, 8, 18, 3), (10, 4, 28, 20, 3), (384, 4, 64, 20, 3), (491, 4, 112, 24, 3)):
+        assert not product("fprop", *layer), layer
+    assert not product("fprop", 1108, 4, 120, 13, 3) and product("fprop", 128, 4, 96, 13, 3)
+    for layer in ((64, 4, 64, 16, 3), (16, 4, 16, 20, 3), (301, 4, 4, 18, 3), (40, 4, 64, 20, 3), (416, 4, 4, 24, 3)):
+        assert product("fprop", *layer), layer
+    for layer in ((11, 12, 4, 23, 7), (4, 308, 4, 23, 3), (106, 4, 4, 24, 3)):
+        assert not product("bprop", *layer), layer
+    for layer in ((64, 16, 4, 22, 3), (30, 216, 4, 24, 3), (416, 4, 4, 22, 3), (42, 112, 4, 20, 3)):
+        assert product("bprop", *layer), layer
+    assert not product("bprop", 480, 36, 3, 27, 3) and product("bprop", 196, 52, 3, 27, 3)
+    assert not product("fprop", 300, 3, 64, 28, 3) and product("fprop", 300, 1, 64, 28, 3) and not product("bprop", 64, 304, 3, 27, 3)
+
+
+def test_the_gpu_test_forms_products_inside_every_inverse_transform(rules):
+    """Every basis that has the kernel, one to four terms of either operand's layout (above basis 24 three at most)."""
+    path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "test_gpu_contraction.py")
+    spec = importlib.util.spec_from_file_location("gpu_contraction_layers", path)
+    gpu = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(gpu)
+    for side in gpu.PRODUCT_SIDES:
+        got = {(p, l[1 if p == "fprop" else 2]) for l in gpu.product_layers(side) for p in ("fprop", "bprop")
+               if rules.single(p, l[0], l[1], l[2], side, side, 3, l[3])[0] == "product"}
+        want = {("fprop", 1), ("fprop", 3), ("bprop", 2)}
+        if side <= 24:
+            want |= {("fprop", 2), ("fprop", 4), ("bprop", 3), ("bprop", 4)}
+        assert want <= got, (side, want - got)

@@ -267,14 +267,20 @@ def test_both_inverse_transforms_in_one_launch(hd, side):
 
 # Products of at most four terms formed inside the inverse transform: every basis that has the kernel, one .. four terms
 # from either operand's layout, quads of columns that start in the middle of a run, a ragged last tile, windows.
-@pytest.mark.parametrize("side", [8, 10, 12, 14, 16, 18, 20, 24, 28, 32, 36, 40, 48, 56])
+PRODUCT_SIDES = [8, 10, 12, 14, 16, 18, 20, 24, 28, 32, 36, 40, 48, 56]
+
+
+def product_layers(side):
+    if side > 24:
+        return [(53, 3, 20, 2), (86, 1, 12, 2), (260, 12, 2, 2)]
+    return [(43, 3, 20, 2), (9, 2, 12, 2), (6, 20, 2, 2), (5, 1, 4, 2), (3, 4, 24, 2), (5, 28, 3, 3),
+            (43, 4, 24, 2), (5, 4, 16, 2), (241, 4, 4, 2), (7, 32, 4, 2)]
+
+
+@pytest.mark.parametrize("side", PRODUCT_SIDES)
 def test_product_inside_the_inverse_transform(hd, side):
-    big = side > 24
-    for S, f, fo in ((43, 3, 20), (9, 2, 12), (6, 20, 2), (5, 1, 4)) if not big else ((53, 3, 20), (86, 1, 12), (260, 12, 2)):
-        _check(hd, S, f, fo, side, side, 3, 2)
-    if not big:
-        _check(hd, 3, 4, 24, side, side, 3, 2)
-        _check(hd, 5, 28, 3, side, side, 3, 3)
+    for S, f, fo, kw in product_layers(side):
+        _check(hd, S, f, fo, side, side, 3, kw)
 
 
 @pytest.mark.parametrize("S,f,fo,side", [(2, 3, 12, 150), (1, 12, 3, 150), (19, 3, 64, 70)])
