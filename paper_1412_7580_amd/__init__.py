@@ -13,6 +13,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIBPATH = os.path.join(_HERE, "libfftconv.so")
 _lib = None
 torch = None          # imported by load_library(), so that importing this package alone does not
+_forked = False       # this process was forked from one that had loaded the library
 
 SYMBOLS = [
     "fftconv_create", "fftconv_destroy", "fftconv_set_stream", "fftconv_status_string",
@@ -38,6 +39,11 @@ class FFTConvError(RuntimeError):
     pass
 
 
+def _after_fork():
+    global _forked
+    _forked = True
+
+
 def load_library():
     """dlopen libfftconv.so (building it first only if it does not exist) and set prototypes."""
     global _lib, torch
@@ -50,6 +56,7 @@ def load_library():
     # runtime instance that owns the tensors and streams it is handed.
     import torch as _torch
     torch = _torch
+    os.register_at_fork(after_in_child=_after_fork)
     lib = ctypes.CDLL(_LIBPATH)
     vp, i, l, f, sz = ctypes.c_void_p, ctypes.c_int, ctypes.c_long, ctypes.c_float, ctypes.c_size_t
     lib.fftconv_create.argtypes = [ctypes.POINTER(vp), i]
@@ -183,7 +190,7 @@ class Handle:
     def _sync_stream(self):
         # The current device's current stream by its raw handle: torch.cuda.current_stream() builds a Stream object
         # for it, 2.8 us of the 7.2 that a one-kernel call took (the launch itself is 2.6); this is 0.2.
-        if not torch.cuda.is_initialized():
+        if _forked:
             torch.cuda.init()          # refuses a process that was forked after the device's initialisation
         try:
             s = torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
