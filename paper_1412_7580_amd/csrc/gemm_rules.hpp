@@ -140,6 +140,26 @@ inline bool shifted_pays(const GemmParams &p) {
     return ((p.M + 31) / 32) * ((p.N + 31) / 32) < 4 * ((p.M + 63) / 64) * ((p.N + 63) / 64) || (p.M > 64 && p.N > 64);
 }
 
+// In a launch of its own, over 8000 products of random layers (whole passes, 64x64 tiles / this).  Its 32x32 tiles save padding while
+// there are fewer than two to a 64x64 one (1.04 .. 1.57x), but few of them leave compute units without a workgroup where the others are one
+// round, three a compute unit, and a reduction of one K tile then has nothing to make up for it (704 tiles 0.93 .. 1.0, 864 1.0 .. 1.1).  Two to
+// one save little, and half as many workgroups fill their last round worse: behind in one round (fprop 0.92 .. 0.98; accGrad's longest
+// 1.04 .. 1.14) and, up to one K tile, about two (1632 and 1728 tiles 0.93 .. 0.97; 1216 and 1408 1.0 .. 1.08, from 2048 1.0 .. 1.1, up to four terms
+// from 2304).  Three and more to one, with a side of 33 .. 64, read the operands twice for little padding: up to two K tiles only where the
+// others' results are single planes of every line (odd columns) and the tiles well filled (64 x 91 x 16 1.24, 60 x 65 x 8 1.27; 41 x 152 x 2,
+// six tenths, 0.93, 58 x 80 x 5 0.95, 34 x 78 x 1 0.90).
+inline bool shifted_alone_pays(const GemmParams &p, bool akf) {
+    const long m = (p.M + 31) / 32, n = (p.N + 31) / 32, t32 = m * n, t64 = ((m + 1) / 2) * ((n + 1) / 2), tiles = p.bins * t64;
+    const bool one_round = tiles <= 3 * 256;
+    if (t32 < 2 * t64) return p.K > 16 || !one_round;
+    if (t32 == 2 * t64) {
+        if (one_round) return !akf && p.K > 64;
+        return p.K > 16 || (tiles > 1024 && (tiles < 1536 || tiles >= (p.K <= 4 ? 2304 : 2048)));
+    }
+    if (t32 < 3 * t64 || (m > 2 && n > 2)) return true;
+    return p.K > 32 || (p.N % 2 == 1 && 8L * p.M * p.N >= 5 * 1024 * t32);
+}
+
 // Whether the kernel that splits the reduction over waves (cgemm_direct.hip) can run: runs of at least a quad, and
 // 32-bit offsets that reach 32 rows and the reduction of an operand whose reduction index is contiguous, 64 rows and
 // eight reduction steps of the others, 32 rows of the result.
@@ -157,7 +177,8 @@ struct Prepared {
     bool akf, bkf;     // the reduction index is the contiguous plane index of A / B
     bool vec;          // 16-byte gathers are possible
     bool bingroup;     // the four-bins-per-line kernel applies
-    bool shifted;      // its form for any channel counts does
+    bool shifted;      // its form for any channel counts does ...
+    bool shifted_alone; // ... and is the fastest in a launch of its own
     bool direct;       // the kernel that splits the reduction over waves can run ...
     bool direct_alone; // ... and is the fastest in a launch of its own
     bool split;        // bound by the fp32 matrix cores: the bf16 kernel applies (cgemm_split.hip) ...
@@ -215,6 +236,7 @@ inline hipError_t prepare(const GemmProblem &g, const GemmSwitches &sw, Prepared
                     bins % (4 * kXcds) == 0 && (akf || A.rs == 1) && (bkf || B.cs == 1) && g.C_cs == 1 &&
                     g.C_rs % 4 == 0 && N % 4 == 0 && ((size_t)g.C & 15) == 0;
     out->shifted = !out->vec && !sw.no_bingroup && sw.tile < 0 && shifted_lines(prm, akf, bkf) && shifted_pays(prm);
+    out->shifted_alone = out->shifted && shifted_alone_pays(prm, akf);
     const Thin form = thin_form(prm);
     out->thin = sw.no_thin || sw.tile >= 0 || !thin_pays(prm, form, bkf, out->vec, out->bingroup) ? Thin::none : form;
     out->split = !out->bingroup && (akf || !bkf) && !sw.no_split && sw.tile < 0 && split_pays(prm, akf, bkf, out->vec) && !narrow_tile(prm, out->vec);
@@ -260,7 +282,7 @@ inline Kernel kernel_alone(const Prepared &q) {
     if (q.thin != Thin::none) return Kernel::thin;
     if (q.direct_alone) return Kernel::direct;
     if (q.bingroup) return Kernel::bingroup;
-    if (q.shifted) return Kernel::shifted;
+    if (q.shifted_alone) return Kernel::shifted;
     return q.split_alone ? Kernel::split : Kernel::tiles;
 }
 // With the inverse transform behind it; basis: the square basis of the pass, 0 for a rectangular one.

@@ -47,6 +47,20 @@ def test_shifted_lines(rules):
     assert shifted("accgrad", 26, 229, 175, 50, 3)                            # full tiles, many of them
 
 
+def test_shifted_lines_only_where_they_are_faster(rules):
+    """By the 32x32 tiles to a 64x64 one, the reduction, and whether the 64x64 tiles are one round of workgroups."""
+    shifted = lambda p, *layer: rules.single(p, *_layer(*layer))[0] == "shifted"
+    assert not shifted("fprop", 9, 7, 30, 36, 3) and shifted("fprop", 9, 18, 30, 36, 3)             # one tile, one round
+    assert shifted("fprop", 9, 7, 30, 40, 3)                                                        # ... more than one round
+    assert not shifted("fprop", 20, 65, 47, 36, 3) and shifted("accgrad", 65, 20, 47, 36, 3)        # two tiles, one round
+    assert not shifted("fprop", 20, 6, 47, 40, 3) and shifted("fprop", 20, 18, 47, 40, 3)           # ... and few terms
+    assert shifted("fprop", 20, 6, 47, 48, 3) and not shifted("fprop", 20, 6, 47, 56, 3) and shifted("fprop", 20, 6, 47, 64, 3)
+    assert not shifted("fprop", 46, 6, 134, 40, 3) and not shifted("bprop", 41, 217, 29, 38, 3)     # nearly full tiles
+    assert shifted("bprop", 41, 217, 70, 38, 3) and not shifted("fprop", 40, 30, 90, 40, 3)
+    assert shifted("bprop", 64, 91, 14, 48, 3) and not shifted("bprop", 152, 41, 2, 55, 3)          # ... and odd columns
+    assert shifted("fprop", 66, 6, 130, 40, 3) and shifted("accgrad", 14, 81, 108, 51, 2)           # three by four
+
+
 def test_shared_launches(rules):
     pair = lambda *layer: rules.pair(*_layer(*layer))
     assert pair(22, 16, 311, 14, 7) == "direct" and pair(7, 16, 6, 75, 3) == "direct"
