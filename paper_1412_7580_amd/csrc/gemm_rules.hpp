@@ -191,7 +191,9 @@ struct Prepared {
 // 277 on 40 bins 28.9 -> 9.2, 16 x 16 x 192 on 112 bins 18.5 -> 7.6.  Not for two chunks of reduction or less (5 x 32 x
 // 8: 4.0 / 9.5), nor with runs of four planes, where whole lines are worth more (5 x 248 x 176 on 864 bins 82 / 124), nor
 // what the bf16 cores do.  A tile of 32 reads its operands for half as many products, so a side above 32 (64 on runs of 32
-// and more, whose lines a strip uses whole) stays with 64x64 tiles (48 x 304 x 57 on 544 bins 50 / 68), and so do, unless the
+// and more, whose lines a strip uses whole) stays with 64x64 tiles (48 x 304 x 57 on 544 bins 50 / 68), and so does one of 33 .. 64 whose tiles
+// of 64 are nearly full and give every compute unit one, with 32 steps and less or gathers that cross runs (whole passes 44 x 399 x 29 on 88 bins
+// 25.6 / 29.8, 391 x 63 x 63 42.0 / 47.3, 50 x 256 x 182 50.1 / 55.2; but 35 x 198 x 228 1.15x, accGrad's 39 x 144 x 188 51 / 42), and so do, unless the
 // tile of 64 would be half padding, grids of 32 tiles and more to a reduction step (9 x 256 x 32 on 312 bins 12.3 / 16.8), of 128
 // where the other kernel's gathers are of 4 bytes or runs of eight planes (1134 x 8 x 32 on 544 bins 63 / 83).  Sides of at most 16,
 // which have tiles of their own, are ahead on those grids, too (fprop of 8 x 32 -> 301, 21x21 27.9 / 24.7, 4 x 32 -> 130 21.3 / 19.1, 12 x 32 ->
@@ -200,7 +202,9 @@ inline long tiles_32(const GemmParams &p) { return (long)p.bins * ((p.M + 31) / 
 inline bool direct_pays(const Prepared &q) {
     const GemmParams &p = q.prm;
     if (q.split || p.layA.tsh < 3 || p.K <= 16) return false;
-    if ((p.M < p.N ? p.M : p.N) > (p.layA.tsh >= 5 ? 64 : 32)) return false;
+    const int side = p.M < p.N ? p.M : p.N;
+    if (side > (p.layA.tsh >= 5 ? 64 : 32)) return false;
+    if (side > 32 && 3 * tiles_32(p) >= 10 * tiles_64(p) && tiles_64(p) >= 256 && (p.K < 32 || (q.akf && (p.K == 32 || p.K % 4 != 0)))) return false;
     return p.M <= 16 || p.N <= 16 || tiles_32(p) == tiles_64(p) || tiles_32(p) < (q.vec && p.layA.tsh >= 4 ? 32L : 128L) * p.K;
 }
 

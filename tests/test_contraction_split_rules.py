@@ -31,6 +31,16 @@ def test_split_reduction(rules):
     assert not split("fprop", 128, 3, 96, 128, 11)               # thin
 
 
+def test_split_reduction_of_full_tiles(rules):
+    """Sides of 33 .. 64 that fill their 64x64 tiles, where those give every compute unit one: with more than 32 steps in whole quads."""
+    split = lambda p, *layer: rules.single(p, *_layer(*layer))[0] == "direct"
+    assert split("fprop", 40, 63, 130, 10, 3) and not split("fprop", 40, 63, 300, 10, 3)          # 192, 320 tiles
+    assert not split("bprop", 44, 399, 29, 11, 2) and not split("bprop", 34, 208, 27, 13, 5)
+    assert not split("bprop", 50, 256, 182, 14, 3) and split("bprop", 35, 198, 228, 10, 2)
+    assert split("accgrad", 188, 144, 39, 13, 5) and not split("accgrad", 17, 53, 288, 13, 2)
+    assert split("accgrad", 179, 38, 72, 15, 3) and split("bprop", 92, 36, 66, 15, 3)             # three 32x32 tiles to one
+
+
 def test_split_reduction_possible_at_any_alignment_of_4_bytes(rules):
     for off in (0, 4, 8, 12, 16):
         assert rules.single("fprop", *_layer(15, 353, 12, 11, 3), offset=off)[0] == "direct"
