@@ -425,7 +425,8 @@ static hipError_t invert_pair(fftconv_ctx *c, const PassPlan &pb, const float *G
 // product is no longer read right after it was written.  260 random layers, apart / one: up to 32 MB of products 0.77 .. 0.98 (16 x 16 -> 16
 // 34x34 26.3 / 21.3 us, 38 x 64 -> 19, 48x48 76.2 / 69.9), up to 96 MB 0.92 .. 0.99, from 160 MB on it loses (102 x 320 -> 4, 34x34 191.9 / 202.6);
 // on basis 64, whose workgroups of 1024 threads a part of the weights' fills worst, already from 40 MB on (22 x 176 -> 16 64x64, 113 MB, 130.7 /
-// 144.0).  Not on the bases 16 and 28, where a launch for both takes another kernel than one alone (a gradient alone is the same bits).
+// 144.0).  Not on the bases 16 and 28, where a launch for both takes another kernel than one alone: a gradient alone
+// is the same bits (after a shared contraction it is so to rounding there).
 static bool inverse_pair_pays(const PassPlan &pb, const PassPlan &pa) {
     if (pb.rect || pa.rect || pb.N != pa.N || pb.N == 16 || pb.N == 28) return false;
     const double bytes = (double)(pb.lay.floats(pb.planesC) + pa.lay.floats(pa.planesC)) * sizeof(float);

@@ -373,6 +373,28 @@ inline Shared shared_launch(const Prepared &q1, const Prepared &q2, const GemmSw
     return apart && scalar_pair_pays(b, a) ? Shared::scalar : Shared::none;
 }
 
+// Whether one gradient alone takes the waves of the shared direct launch, so that its product is the same bits with and without the
+// other, or a kernel of its own.  10000 lone gradients of random layers, 64x64 tiles / shared waves (whole backward calls): 1.0 .. 2x where
+// a tile of 32 is one of 64, but with runs of four planes for long reductions on many bins (4 x 21 x 339 on 704 bins 87 / 99), not with more
+// than 9 tiles to 4 (512 x 317 x 4, 13x13 74.8 / 100.3 us), and between them with runs of eight (1.05 .. 1.2x).  With more than 16 steps
+// otherwise up to the grids that the split reduction alone stops at; with fewer, where the shared launch leaves most of its waves without a
+// chunk, while there are few tiles (runs of 16 and up to 8 steps: 1.05x below 4096, 0.90 .. 0.98 above; 9 .. 16: 1.0 below 1024, 0.91 .. 0.97; longer
+// runs 1.02 .. 1.09x below 1024, 0.95; 9 .. 16 steps 0.97 from one tile a compute unit to two), and with runs of four and 9 .. 16 steps not for
+// two tiles to one of 64 (704 bins 0.91, 864 0.97).
+inline bool lone_as_shared_pays(const Prepared &q) {
+    const GemmParams &p = q.prm;
+    const long t32 = tiles_32(p), t64 = tiles_64(p);
+    const int tsh = p.layA.tsh;
+    if (tsh == 2 && t32 * p.K >= 80000) return false;
+    if (t32 == t64) return true;
+    if (4 * t32 > 9 * t64) return false;
+    if (tsh == 3) return true;
+    if (tsh == 2) return p.K <= 8 || p.K > 16 || t32 < 2 * t64 || t64 > p.bins;
+    if (p.K > 16) return t32 < (q.vec ? 32L : 128L) * p.K;
+    if (tsh == 4) return t32 < (p.K <= 8 ? 4096 : 1024);
+    return t32 < 1024 && (p.K <= 8 || t32 < 256 || t32 >= 512);
+}
+
 // One gradient of a backward pass asked for alone: the kernel that it takes, and whether that is the direct kernel on the
 // waves of the shared launch.
 struct Lone {
@@ -381,9 +403,9 @@ struct Lone {
 };
 inline Lone lone_gradient(const Prepared &q, const Prepared &partner, const GemmSwitches &sw) {
     const Shared how = shared_launch(q, partner, sw);
-    if (how == Shared::direct) return {Kernel::direct, true};
+    if (how == Shared::direct && lone_as_shared_pays(q)) return {Kernel::direct, true};
     Prepared own = q;
-    if (how != Shared::none) own.direct_alone = false;
+    if (how != Shared::none && how != Shared::direct) own.direct_alone = false;
     return {kernel_alone(own), false};
 }
 

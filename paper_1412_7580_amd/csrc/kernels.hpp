@@ -184,8 +184,10 @@ struct GemmProblem {
     long C_rs, C_cs;
     int M, N, K, bins, live;
 };
-// partner: the other product of a backward pass that asks for one gradient only.  The one that is computed then sums in
-// the order of the shared launch, so that it is the same bits with and without the other (but for split tails).
+// partner: the other product of a backward pass that asks for one gradient only.  Where both would share a launch of the
+// split reduction or of 64x64 tiles with 4-byte gathers, the one that is computed sums in that launch's order, so that it is the same
+// bits with and without the other, unless a kernel of its own is faster (lone_gradient()).  Beside the other shared launches it
+// takes its own kernel, and the two agree to rounding.
 hipError_t launch_cgemm_bins(const GemmProblem &g, LaunchCtx st, const GemmProblem *partner = nullptr);
 
 // A contraction whose reduction has at most four terms as the input of the inverse transform (square bases up

@@ -80,6 +80,22 @@ def test_shared_launches(rules):
     assert pair(4, 6, 5, 27, 5) == "scalar"                      # reductions of one chunk
 
 
+def test_a_lone_gradient_on_the_waves_of_the_shared_launch(rules):
+    """... unless that costs it more than a kernel of its own: full tiles, few steps or large grids."""
+    lone = lambda p, *layer: rules.lone(p, *_layer(*layer))
+    for p, layer in (("bprop", (512, 317, 4, 11, 5)), ("bprop", (362, 387, 25, 11, 4)), ("accgrad", (3, 288, 347, 9, 3)),
+                     ("bprop", (275, 121, 16, 9, 4)), ("accgrad", (40, 399, 184, 13, 3)), ("bprop", (453, 12, 32, 17, 3)),
+                     ("bprop", (4, 21, 339, 34, 3)), ("bprop", (70, 9, 13, 13, 3)), ("bprop", (34, 18, 15, 34, 3)),
+                     ("accgrad", (13, 201, 31, 20, 3)), ("bprop", (900, 17, 4, 20, 3))):
+        assert rules.pair(*_layer(*layer)) == "direct" and lone(p, *layer) != "direct+", (p, layer)
+    for p, layer in (("bprop", (70, 5, 6, 13, 3)), ("accgrad", (70, 5, 6, 13, 3)), ("bprop", (33, 13, 140, 20, 3)),
+                     ("accgrad", (4, 72, 68, 9, 3)), ("accgrad", (129, 16, 20, 13, 3)), ("bprop", (65, 65, 64, 13, 3)),
+                     ("bprop", (75, 14, 7, 32, 3)), ("bprop", (163, 5, 4, 112, 5)), ("bprop", (8, 7, 16, 65, 3)),
+                     ("bprop", (70, 9, 13, 8, 3)), ("bprop", (66, 18, 15, 34, 3))):
+        assert rules.pair(*_layer(*layer)) == "direct" and lone(p, *layer) == "direct+", (p, layer)
+    assert rules.pair(*_layer(20, 33, 70, 20, 3)) == "scalar" and lone("bprop", 20, 33, 70, 20, 3) == "tile"
+
+
 def test_product_inside_the_inverse_transform(rules):
     product = lambda p, *layer: rules.single(p, *_layer(*layer))[0] == "product"
     assert product("fprop", 64, 3, 384, 13, 3) and product("fprop", 16, 4, 16, 20, 3) and product("fprop", 128, 3, 96, 128, 11)

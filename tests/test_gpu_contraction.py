@@ -234,6 +234,27 @@ def test_a_gradient_alone_is_the_same_bits(hd, S, f, fo, side, k):
     assert torch.equal(hd.fft_conv_backward(gy, saved, f, side, side, k, k, want_gx=False)[1], gw)
 
 
+# Where a lone gradient takes a kernel of its own: a thin side, bf16 in the shared launch only, more than nine 32x32 tiles to four, 9 .. 16
+# steps, a grid too large for the steps, and the inverse transforms of bases 16 and 28.  (S, f, fo, image side)
+@pytest.mark.parametrize("S,f,fo,side", [(16, 4, 16, 13), (16, 144, 144, 13), (128, 93, 4, 11), (70, 9, 13, 13), (300, 12, 32, 17),
+                                         (4, 21, 120, 34), (43, 42, 70, 15), (9, 16, 44, 15), (26, 10, 16, 26), (3, 60, 61, 26)])
+def test_a_gradient_alone_is_right_on_a_kernel_of_its_own(hd, S, f, fo, side):
+    import torch
+    import torch.nn.functional as F
+    g = torch.Generator().manual_seed(10)
+    x, w = torch.randn(S, f, side, side, generator=g), torch.randn(fo, f, 3, 3, generator=g)
+    gy = torch.randn(S, fo, side - 2, side - 2, generator=g)
+    saved = torch.empty(hd.saved_bytes(S, f, fo, side, side, 3, 3) // 4, device="cuda")
+    hd.fft_conv_fprop_save(x.cuda(), w.cuda(), saved)
+    gx = hd.fft_conv_backward(gy.cuda(), saved, f, side, side, 3, 3, want_gw=False)[0]
+    old = torch.randn(fo, f, 3, 3, generator=g)
+    gw = old.cuda()
+    hd.fft_conv_backward(gy.cuda(), saved, f, side, side, 3, 3, gw=gw, want_gx=False, scale=0.5, accumulate=True)
+    xd, wd, gd = x.double(), w.double(), gy.double()
+    assert _relerr(gx, F.conv_transpose2d(gd, wd)) <= TOL
+    assert _relerr(gw, old.double() + 0.5 * F.conv2d(xd.transpose(0, 1), gd.transpose(0, 1)).transpose(0, 1)) <= TOL
+
+
 # Both inverse transforms of a backward pass in one launch on every basis: few channels (odd counts, a ragged last tile) and a
 # shared contraction, then both contractions of their own; windows and padding; scale and accumulate stay with their product.
 @pytest.mark.parametrize("side", [8, 10, 12, 14, 18, 20, 24, 32, 36, 40, 48, 56, 64, 80, 96, 112, 128])
