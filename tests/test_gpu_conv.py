@@ -384,7 +384,7 @@ def test_small_layers_share_a_sample_among_workgroups(hd, side, S, f, fo):
     assert S > 64 or (one and one_b)
     bins = {7: 40, 9: 60, 12: 84, 13: 112, 16: 144}[side]
     if one and bins * f * fo > 40000:
-        with pytest.raises(Exception):
+        with pytest.raises(Exception, match="workspace too small"):
             hd.fft_conv_fprop_weights(dx, wf, fo, 3, 2, ws=torch.empty(64, device="cuda"))
 
 
