@@ -630,7 +630,7 @@ def roofline_entry(ms, model):
 KERNEL_FUNCTIONS = {   # which kernel function runs a stage (for matching rocprofv3 kernel stats)
     "fft": "fft2d_r2c_multi_kernel (both operands in one launch)", "fft_a": "fft2d_r2c_kernel",
     "fft_b": "fft2d_r2c_kernel", "ifft": "fft2d_c2r_kernel / fft2d_c2r_pair_kernel",
-    "contraction": "cgemm_bins_kernel / cgemm_tail_kernel / cgemm_pair_kernel / cgemm_bingroup_kernel / cgemm_split_kernel / cgemm_split_pair_kernel / cgemm_thin_*_kernel / cgemm_direct*_kernel",
+    "contraction": "cgemm_bins_kernel / cgemm_tail_kernel / cgemm_pair_kernel / cgemm_bingroup_kernel / cgemm_split_kernel / cgemm_split_pair_kernel / cgemm_thin_*_kernel / cgemm_direct*_kernel / cgemm_bingroup_shifted_kernel / cgemm_scalar_pair_kernel",
 }
 
 # HBM bytes per launch of the headline's kernels from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs

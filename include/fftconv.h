@@ -239,8 +239,11 @@ int fft_conv_backward_tiled(fftconv_handle hd, const float *gy, float *gx, float
  * fft_conv_fprop(_padded) / fft_conv_bprop(_padded) with one forward transform instead of two.
  * The transform may run on another handle and stream than the passes (the caller orders
  * them).  Workspace as for the ordinary passes; a short wf gives FFTCONV_WORKSPACE_TOO_SMALL.
- * Small layers (those fft_conv_fprop_fused / fft_conv_bprop_fused support, up to 512 samples)
- * run as one launch by themselves and then touch no workspace.
+ * Small layers run as one launch by themselves: unpadded ones on a square basis of at most 16 with f
+ * and fo as fft_conv_fprop_fused takes them, while a workgroup's share of the products is small (up to
+ * 512 samples, few of them up to 1024).  Of these, the layers that fft_conv_fprop_fused supports ask for no
+ * workspace up to 512 samples.  The others use none either, but ask for it as three launches would: a ws that is too
+ * short gives FFTCONV_WORKSPACE_TOO_SMALL, the handle's own grows.
  */
 size_t fftconv_weights_bytes(int f, int fo, int h, int w, int kh, int kw, int pad_h, int pad_w);
 int fft_conv_transform_weights(fftconv_handle hd, const float *wt, void *wf, size_t wf_bytes,
@@ -256,8 +259,8 @@ int fft_conv_bprop_weights(fftconv_handle hd, const float *gy, const void *wf, s
  * fprop of a small layer in ONE launch, on weights transformed ahead (wf from
  * fft_conv_transform_weights with pad 0): for the latency-bound regime, where the three launches
  * of fft_conv_fprop_weights cost more than the arithmetic (Section 6 plans such an integration
- * of the matrix product with the transform kernels).  One workgroup carries one sample through
- * transform, contraction and inverse; it needs no workspace.  Same result as fft_conv_fprop up
+ * of the matrix product with the transform kernels).  A sample goes through transform, contraction and
+ * inverse in one workgroup, or in several that share its result planes; no workspace is needed.  Same result as fft_conv_fprop up
  * to rounding.  Supported when the layer's basis is square and at most 16 (unpadded images),
  * f is a multiple of 4 that divides 32 (64 at basis 8), fo <= 32 (64) and
  * bins x f x fo <= 40000 (bins = N (N/2 + 1) of the layer's basis N; e.g. 16 x 16 planes at
@@ -268,9 +271,9 @@ int fft_conv_fprop_fused(fftconv_handle hd, const float *x, const void *wf, size
 
 /*
  * bprop of a small layer in ONE launch, the counterpart of fft_conv_fprop_fused (same weights
- * buffer wf, same support rule with the same f and fo, same error behaviour): one workgroup
- * carries one sample's fo gradient planes gy through transform, product GX_i = sum_j GY_j . W_ji
- * and inverse with crop to h x w.  gy [S, fo, h-kh+1, w-kw+1] (device, read only), gx
+ * buffer wf, same support rule with the same f and fo, same error behaviour): a sample's fo
+ * gradient planes gy go through transform, product GX_i = sum_j GY_j . W_ji and inverse with crop
+ * to h x w in one workgroup, or in several that share the planes of gx.  gy [S, fo, h-kh+1, w-kw+1] (device, read only), gx
  * [S, f, h, w] (device, overwritten).  Same result as fft_conv_bprop up to rounding.
  */
 int fft_conv_bprop_fused(fftconv_handle hd, const float *gy, const void *wf, size_t wf_bytes, float *gx,
@@ -356,11 +359,13 @@ int fft_conv_backward(fftconv_handle hd, const float *gy, float *gx, float *gw,
  *   "contraction"       per-bin contraction of one pass
  *   "contraction.pair"  the bprop and accGrad contractions of fft_conv_backward in one launch
  *   "ifft", "ifft.pair" inverse FFT + clip of one product, or of gx and gw in one launch
+ *   "contraction.ifft"  a contraction of at most four terms formed inside the inverse FFT of its result
  *   "fused"             the one-launch passes
- * fft_conv_fprop / bprop / accgrad / fprop_save give 3 or 4 entries (1 when the pass runs as one
- * launch); fft_conv_backward gives
- * fft of gy, then contraction and ifft for gx and again for gw (5), or 4 or 3 with shared launches.
- * Off by default.
+ * A pass gives its forward FFTs (1 or 2 entries, on weights transformed ahead 1), then contraction and
+ * ifft, or contraction.ifft; 1 entry when it runs as one launch.  fft_conv_backward gives the FFT of gy (1 or 2
+ * entries), then one of: contraction.pair and ifft.pair; contraction.pair, ifft (gx) and ifft (gw); both
+ * contractions (gx, gw) and ifft.pair; contraction and ifft for gx and again for gw.  Each of its gradients may be
+ * a contraction.ifft instead, before or after the other's entries.  Off by default.
  */
 int fftconv_set_profiling(fftconv_handle h, int enabled);
 int fftconv_last_kernel_ms(fftconv_handle h, float *ms_out, int capacity, int *count);

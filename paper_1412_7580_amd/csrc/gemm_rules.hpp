@@ -26,7 +26,7 @@ inline bool fast_addressing(const FreqLayout &lay, long stride, int bins) {
 // of 4 bytes or runs of four planes, where the gathers are the bound, nor for less than two whole K
 // tiles (16 images 160x160, 16 -> 48 channels: 129 -> 131).  Under fast addressing the longer tile's
 // per-lane offsets must fit, too.  What the split reduction takes (direct_pays: the first of these layers is at 75 us with it)
-// does not come here.
+// does not come here, but for a lone gradient that sums in the order of a shared launch of 64x64 tiles (lone_gradient()).
 inline bool narrow_tile(const GemmParams &prm, bool vec) {
     if (!vec || prm.layA.tsh < 3 || prm.K < 32) return false;
     if (!((prm.M <= 32 && prm.N >= 128) || (prm.N <= 32 && prm.M >= 128))) return false;
@@ -315,9 +315,10 @@ inline double lost_in_shared_tiles(const Prepared &q) {
     return narrow_tile(p, q.vec) ? 1e-4 * steps : 0;
 }
 
-// bprop and accGrad of a layer with four or fewer channels on a side, or of one sample: two launches
-// for the products mean two for the inverse transforms, too (bases up to 32 have a shared one), and
-// neither product runs beside the other.  That costs 12 us and more with bprop's reduction: 16 samples,
+// bprop and accGrad of a layer with four or fewer channels on a side, or of one sample.  Constants of a time when two launches
+// for the products meant two for the inverse transforms, too; since then separate products share an inverse launch while they
+// are small, and one of at most four terms may need no launch of its own, so that two launches cost less than this charges.
+// It charged 12 us and more with bprop's reduction: 16 samples,
 // 4 -> 16 channels, 13x13 15 us a backward pass in the shared launch against 30; 128 x 4 -> 384, 20x20 119 / 114, 128 x
 // 4 -> 128, 28x28 92 / 78.  With the thin side in bprop alone accGrad decides (256 x 64 -> 4, 32x32 91 /
 // 109; 256 x 384 -> 4, 20x20 194 / 172).  One sample: by the size of the gradient's spectrum (64 -> 128 channels,

@@ -196,8 +196,8 @@ hipError_t launch_cgemm_bins(const GemmProblem &g, LaunchCtx st, const GemmProbl
 hipError_t launch_product_inverse(const GemmProblem &g, float *out, int N, int h_out, int w_out, float scale,
                                   bool accumulate, LaunchCtx st, const PlaneView *view);
 
-// Two independent contractions in one launch (see cgemm_pair_kernel).  Possible when both
-// can use 16-byte gathers and neither is a case for the four-bins-per-line kernel.
+// Two independent contractions, bprop and accGrad of a layer, in one launch where that is the faster way
+// (shared_launch()).
 bool cgemm_pair_supported(const GemmProblem &g1, const GemmProblem &g2, const GemmSwitches *sw = nullptr);
 hipError_t launch_cgemm_pair(const GemmProblem &g1, const GemmProblem &g2, LaunchCtx st);
 
