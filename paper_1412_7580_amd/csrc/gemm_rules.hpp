@@ -147,7 +147,8 @@ inline bool shifted_pays(const GemmParams &p) {
 // 1.04 .. 1.14) and, up to one K tile, about two (1632 and 1728 tiles 0.93 .. 0.97; 1216 and 1408 1.0 .. 1.08, from 2048 1.0 .. 1.1, up to four terms
 // from 2304).  Three and more to one, with a side of 33 .. 64, read the operands twice for little padding: up to two K tiles only where the
 // others' results are single planes of every line (odd columns) and the tiles well filled (64 x 91 x 16 1.24, 60 x 65 x 8 1.27; 41 x 152 x 2,
-// six tenths, 0.93, 58 x 80 x 5 0.95, 34 x 78 x 1 0.90).
+// six tenths, 0.93, 58 x 80 x 5 0.95, 34 x 78 x 1 0.90); with both sides above 64 1.0 .. 1.37x, but for short reductions whose results
+// are whole quads of planes (128 x 112 x 6 0.91, 167 x 128 x 17 0.87, 102 x 80 x 3 0.95).
 inline bool shifted_alone_pays(const GemmParams &p, bool akf) {
     const long m = (p.M + 31) / 32, n = (p.N + 31) / 32, t32 = m * n, t64 = ((m + 1) / 2) * ((n + 1) / 2), tiles = p.bins * t64;
     const bool one_round = tiles <= 3 * 256;
@@ -156,7 +157,8 @@ inline bool shifted_alone_pays(const GemmParams &p, bool akf) {
         if (one_round) return !akf && p.K > 64;
         return p.K > 16 || (tiles > 1024 && (tiles < 1536 || tiles >= (p.K <= 4 ? 2304 : 2048)));
     }
-    if (t32 < 3 * t64 || (m > 2 && n > 2)) return true;
+    if (t32 < 3 * t64) return true;
+    if (m > 2 && n > 2) return p.N % 4 != 0 || p.K > (t32 == 4 * t64 ? 32 : 16);
     return p.K > 32 || (p.N % 2 == 1 && 8L * p.M * p.N >= 5 * 1024 * t32);
 }
 

@@ -69,6 +69,8 @@ def test_shifted_lines_only_where_they_are_faster(rules):
     assert shifted("bprop", 41, 217, 70, 38, 3) and not shifted("fprop", 40, 30, 90, 40, 3)
     assert shifted("bprop", 64, 91, 14, 48, 3) and not shifted("bprop", 152, 41, 2, 55, 3)          # ... and odd columns
     assert shifted("fprop", 66, 6, 130, 40, 3) and shifted("accgrad", 14, 81, 108, 51, 2)           # three by four
+    assert not shifted("accgrad", 17, 128, 167, 40, 3) and shifted("accgrad", 34, 128, 167, 40, 3)  # ... in whole quads of columns
+    assert not shifted("accgrad", 3, 80, 102, 36, 3) and shifted("accgrad", 3, 81, 102, 36, 3)
 
 
 def test_shared_launches(rules):
