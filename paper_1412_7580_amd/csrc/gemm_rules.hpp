@@ -378,7 +378,8 @@ inline Shared shared_launch(const Prepared &q1, const Prepared &q2, const GemmSw
 
 // Whether one gradient alone takes the waves of the shared direct launch, so that its product is the same bits with and without the
 // other, or a kernel of its own.  10000 lone gradients of random layers, 64x64 tiles / shared waves (whole backward calls): 1.0 .. 2x where
-// a tile of 32 is one of 64, but with runs of four planes for long reductions on many bins (4 x 21 x 339 on 704 bins 87 / 99), not with more
+// a tile of 32 is one of 64, but with runs of four planes for long reductions of many planes (4 x 21 x 339 on 704 bins 87 / 99, 46 x 4 x 298
+// 103 / 117; 2 x 7 x 328 64 / 57), not with more
 // than 9 tiles to 4 (512 x 317 x 4, 13x13 74.8 / 100.3 us), and between them with runs of eight (1.05 .. 1.2x).  With more than 16 steps
 // otherwise up to the grids that the split reduction alone stops at; with fewer, where the shared launch leaves most of its waves without a
 // chunk, while there are few tiles (runs of 16 and up to 8 steps: 1.05x below 4096, 0.90 .. 0.98 above; 9 .. 16: 1.0 below 1024, 0.91 .. 0.97; longer
@@ -388,7 +389,7 @@ inline bool lone_as_shared_pays(const Prepared &q) {
     const GemmParams &p = q.prm;
     const long t32 = tiles_32(p), t64 = tiles_64(p);
     const int tsh = p.layA.tsh;
-    if (tsh == 2 && t32 * p.K >= 80000) return false;
+    if (tsh == 2 && p.K > 48 && (double)p.bins * p.K * (p.M + p.N) >= 2.5e6) return false;
     if (t32 == t64) return true;
     if (4 * t32 > 9 * t64) return false;
     if (tsh == 3) return true;

@@ -93,7 +93,8 @@ def test_a_lone_gradient_on_the_waves_of_the_shared_launch(rules):
     for p, layer in (("bprop", (70, 5, 6, 13, 3)), ("accgrad", (70, 5, 6, 13, 3)), ("bprop", (33, 13, 140, 20, 3)),
                      ("accgrad", (4, 72, 68, 9, 3)), ("accgrad", (129, 16, 20, 13, 3)), ("bprop", (65, 65, 64, 13, 3)),
                      ("bprop", (75, 14, 7, 32, 3)), ("bprop", (163, 5, 4, 112, 5)), ("bprop", (8, 7, 16, 65, 3)),
-                     ("bprop", (70, 9, 13, 8, 3)), ("bprop", (66, 18, 15, 34, 3))):
+                     ("bprop", (70, 9, 13, 8, 3)), ("bprop", (66, 18, 15, 34, 3)), ("bprop", (2, 7, 328, 35, 3)),
+                     ("bprop", (128, 7, 32, 38, 3))):
         assert rules.pair(*_layer(*layer)) == "direct" and lone(p, *layer) == "direct+", (p, layer)
     assert rules.pair(*_layer(20, 33, 70, 20, 3)) == "scalar" and lone("bprop", 20, 33, 70, 20, 3) == "tile"
 
