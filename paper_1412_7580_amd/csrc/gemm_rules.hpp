@@ -264,7 +264,7 @@ inline hipError_t prepare(const GemmProblem &g, const GemmSwitches &sw, Prepared
 // lines of the weights for each: only small results above basis 14 (233 x 4 -> 316, 16x16 46.3 / 56.5; 280 x 4 -> 128, 18x18 43.1 / 51.5;
 // 379 x 4 -> 68, 24x24 54.9 / 70.9), on basis 16 not the smallest (1 x 4 -> 368 12.7 / 13.5), on 18 and 20 the smallest where a tile holds whole
 // quads or rows of columns (34 x 4 -> 8, 18x18 15.2 / 15.7, 301 x 4 -> 4 16.7 / 15.4; 10 x 4 -> 28, 20x20 14.3 / 16.5), on 24 with four columns (52 x 4
-// -> 28 19.2 / 23.1, 416 x 4 -> 4 20.8 / 18.9).  bprop is behind on basis 24 alone, where columns do not fill a tile (11 x 12 -> 4, 23x23 15.6 / 16.9).
+// -> 28 19.2 / 23.1, 416 x 4 -> 4 20.8 / 18.9, 1 x 4 -> 4 13.6 / 12.3).  bprop is behind on basis 24 alone, where columns do not fill a tile (11 x 12 -> 4, 23x23 15.6 / 16.9).
 inline bool product_inverse_pays(const Prepared &q, int basis) {
     if (q.thin != Thin::k || basis > 56) return false;
     const int N = q.prm.N;
@@ -274,11 +274,12 @@ inline bool product_inverse_pays(const Prepared &q, int basis) {
         return basis <= 24 || planes >= 1024;
     }
     if (basis > 24) return false;
-    if (!q.bkf) return basis <= 20 || N % 16 == 0 || planes >= 3000 || (N == 4 && planes >= 960);
+    const bool four = N == 4 && (planes == 4 || planes >= 960);
+    if (!q.bkf) return basis <= 20 || N % 16 == 0 || planes >= 3000 || four;
     if (basis <= 12) return true;
     if (basis == 14) return planes < 65536;
     if (basis == 16) return planes >= 1024 && planes < 65536;
-    if (basis == 24) return N == 4 && planes >= 960;
+    if (basis == 24) return four;
     return N == 4 || (planes < 12000 && (N == 16 || planes >= 2400));
 }
 

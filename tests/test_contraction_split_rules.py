@@ -115,7 +115,7 @@ def test_four_terms_and_full_grids_outside_the_inverse_transform(rules):
                   (280, 4, 128, 18, 3), (34, 4, 8, 18, 3), (10, 4, 28, 20, 3), (384, 4, 64, 20, 3), (491, 4, 112, 24, 3)):
         assert not product("fprop", *layer), layer
     assert not product("fprop", 1108, 4, 120, 13, 3) and product("fprop", 128, 4, 96, 13, 3)
-    for layer in ((64, 4, 64, 16, 3), (16, 4, 16, 20, 3), (301, 4, 4, 18, 3), (40, 4, 64, 20, 3), (416, 4, 4, 24, 3)):
+    for layer in ((64, 4, 64, 16, 3), (16, 4, 16, 20, 3), (301, 4, 4, 18, 3), (40, 4, 64, 20, 3), (416, 4, 4, 24, 3), (1, 4, 4, 24, 3)):
         assert product("fprop", *layer), layer
     for layer in ((11, 12, 4, 23, 7), (4, 308, 4, 23, 3), (106, 4, 4, 24, 3)):
         assert not product("bprop", *layer), layer
